@@ -268,10 +268,12 @@ def work(case):
     kind = c["kind"]
     if kind == "qr":
         return {"flops": factor, "bytes": 8.0 * (2 * m * n + mp * N + n * N + 2 * m * nr)}
+    # the adjoint's three products with m' rows, two of them triangular, and n x n work
+    adjoint = 4.0 * mp * n * n + 1.0 * n ** 3
     if kind == "lstsq":
-        return {"flops": factor + 6.0 * mp * n * n + 2.0 * n ** 3, "bytes": 8.0 * (2 * m * n + 2 * m * nr + n * nr)}
+        return {"flops": factor + adjoint, "bytes": 8.0 * (2 * m * n + 2 * m * nr + n * nr)}
     if kind == "grad":
-        return {"flops": factor + 6.0 * mp * n * n + 2.0 * n ** 3,
+        return {"flops": factor + adjoint,
                 "bytes": 8.0 * (2 * m * n + 2 * mp * n + 2 * n * n)}
     if kind == "solve":
         return {"flops": (2.0 * m * n + n * n) * nr, "bytes": 8.0 * (m * n + n * n / 2 + (m + n) * nr)}
