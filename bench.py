@@ -69,7 +69,7 @@ KERNEL_OF = {
     "trailing_product": "tn_lds_kernel<0, false>", "trailing_update": "nnw_kernel<0>",
     "split_reduce": "tn_reduce_kernel / nn_reduce_kernel", "recover": "line_kernel",
     "postorth": "postorth_kernel", "erase": "erase_kernel", "other": "zero_ints_kernel / fill_zero_kernel",
-    "solve": "trinv_kernel / gemv_t_kernel / trsv_step_kernel",
+    "solve": "gemv_t_kernel / trinv_kernel / trsv_flow_kernel",
 }
 
 

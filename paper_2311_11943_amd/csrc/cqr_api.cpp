@@ -1130,18 +1130,16 @@ cqr_status coded_qr_solve(cqr_plan p, const double* Qpost, int64_t ldqp, const d
     return CQR_ENOMEM;
   double* T = static_cast<double*>(ws);
   double* Y = T + ((8 * (size_t)nb * 64 * 64 + 255) & ~size_t(255)) / 8;
-  // inverses of the 64 x 64 diagonal blocks of R_1, all at once
-  prof(*p, PH_SOLVE, nb * 64.0 * 64 * 64 / 3, 8.0 * (n * 64.0 + nb * 64.0 * 64), st,
-       [&] { cqr::launch_trinv(R, ldr, n, T, st); });
   // Y = Qpost^T Bpost
   prof(*p, PH_SOLVE, 2.0 * m * n * nrhs, 8.0 * (m * n + m * nrhs + n * nrhs), st,
        [&] { cqr::launch_gemv_t(Qpost, ldqp, m, (int)n, Bpost, ldbp, nrhs, Y, n, st); });
-  // R_1 X = Y, 64-row blocks from the bottom
-  for (int64_t k0 = (nb - 1) * 64; k0 >= 0; k0 -= 64) {
-    const int w = (int)std::min<int64_t>(64, n - k0);
-    prof(*p, PH_SOLVE, 2.0 * (64.0 * w + k0 * w) * nrhs, 8.0 * (k0 * w + 64.0 * 64 + 2.0 * (k0 + w) * nrhs), st,
-         [&] { cqr::launch_trsv_step(R, ldr, T, Y, n, X, ldx, nrhs, k0, w, st); });
-  }
+  // inverses of the 64 x 64 diagonal blocks of R_1, all at once (X is first
+  // written here, after Bpost's last read)
+  prof(*p, PH_SOLVE, nb * 64.0 * 64 * 64 / 3, 8.0 * (n * 64.0 + nb * 64.0 * 64 + n * nrhs), st,
+       [&] { cqr::launch_trinv(R, ldr, n, T, st, X, ldx, nrhs); });
+  // R_1 X = Y
+  prof(*p, PH_SOLVE, ((double)n * n + 128.0 * n) * nrhs, 8.0 * (0.5 * n * n + nb * 64.0 * 64 + 2.0 * n * nrhs), st,
+       [&] { cqr::launch_trsv_flow(R, ldr, T, Y, n, X, ldx, nrhs, n, st); });
   return hip_status();
 }
 

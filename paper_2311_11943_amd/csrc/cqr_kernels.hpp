@@ -223,7 +223,9 @@ void launch_postorth(const PostArgs& a, hipStream_t st);
 // coded solve: Y = Q^T B (Q m x n), then blocked back substitution with R_1
 void launch_gemv_t(const double* Q, int64_t ldq, int64_t m, int n, const double* B, int64_t ldb, int nrhs,
                    double* Y, int64_t ldy, hipStream_t st);
-void launch_trinv(const double* R, int64_t ldr, int64_t n, double* T, hipStream_t st);
+// inverted 64 x 64 diagonal blocks of R; X != nullptr: X (n x nrhs) marked unsolved for launch_trsv_flow
+void launch_trinv(const double* R, int64_t ldr, int64_t n, double* T, hipStream_t st, double* X = nullptr,
+                  int64_t ldx = 0, int nrhs = 0);
 // adjoint helpers
 void launch_transpose(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows, int64_t cols,
                       double scale, bool upper, hipStream_t st);
@@ -237,8 +239,9 @@ void launch_fold(const FoldArgs& a, hipStream_t st);
 void launch_blockdiag(const double* T, double* Y, int64_t ldy, int64_t n, hipStream_t st);
 // C *= s (rows x cols)
 void launch_scale(double* C, int64_t ldc, int64_t rows, int64_t cols, double s, hipStream_t st);
-void launch_trsv_step(const double* R, int64_t ldr, const double* T, double* Y, int64_t ldy, double* X,
-                      int64_t ldx, int nrhs, int64_t k0, int w, hipStream_t st);
+// R X = Y after launch_trinv(R, ..., T, st, X, ldx, nrhs)
+void launch_trsv_flow(const double* R, int64_t ldr, double* T, const double* Y, int64_t ldy, double* X, int64_t ldx,
+                      int nrhs, int64_t n, hipStream_t st);
 // The allocation-free solve's scratch: a file-scope device array of
 // kSolveScratchBytes, one copy per device.  *ptr receives the current
 // device's copy's address (looked up on the first call on each device).
