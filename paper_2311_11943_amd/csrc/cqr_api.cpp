@@ -353,6 +353,19 @@ void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B,
   }
 }
 
+// C = A^T B (N x N, K rows) of which only the lower triangle is read
+void tn_lower(cqr_plan_s& p, const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
+              int64_t ldc, const cqr::Scratch& s, hipStream_t st) {
+  cqr::TnArgs a = cqr::tn_setup_lower(A, lda, B, ldb, N, K, C, ldc, s);
+  a.prio = 1;
+  const double share = a.lower ? 0.5 : 1.0;
+  const double fl = share * 2.0 * N * N * (double)K, by = 16.0 * (double)K * N, out = share * 8.0 * (double)N * N;
+  const double pb = share * partial_bytes(a.nsplit, a.ntiles);
+  prof(p, PH_ADJOINT, fl, by + (a.nsplit > 1 ? pb : out), st, [&] { cqr::launch_tn_product(a, cqr::TAG_PANEL, st); });
+  if (a.nsplit > 1)
+    prof(p, PH_REDUCE, (a.nsplit - 1.0) * share * N * N, pb + out, st, [&] { cqr::launch_tn_reduce(a, st); });
+}
+
 void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64_t lda, const double* B,
         int64_t ldb, int64_t M, int N, int K, const cqr::Scratch& s, hipStream_t st) {
   if (M <= 0 || N <= 0 || K <= 0) return;
@@ -1139,7 +1152,7 @@ cqr_status coded_qr_solve(cqr_plan p, const double* Qpost, int64_t ldqp, const d
        [&] { cqr::launch_trinv(R, ldr, n, T, st, X, ldx, nrhs); });
   // R_1 X = Y
   prof(*p, PH_SOLVE, ((double)n * n + 128.0 * n) * nrhs, 8.0 * (0.5 * n * n + nb * 64.0 * 64 + 2.0 * n * nrhs), st,
-       [&] { cqr::launch_trsv_flow(R, ldr, T, Y, n, X, ldx, nrhs, n, st); });
+       [&] { cqr::launch_trsv_flow(R, ldr, T, Y, n, X, ldx, nrhs, n, false, st); });
   return hip_status();
 }
 
@@ -1161,12 +1174,41 @@ namespace {
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// C = Cin - sign A B with triangular operands (tri: TRI_* flags; Cin ==
+// nullptr: zero); where the LDS-staged kernels do not take the operands, C is
+// prepared and updated by the general ones.
+void nn_tri(cqr_plan_s& p, double* C, int64_t ldc, const double* Cin, int64_t ldcin, double sign, int tri,
+            const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M, int N, int K, const cqr::Scratch& s,
+            hipStream_t st) {
+  cqr::NnArgs a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
+  a.Cin = Cin; a.ldcin = ldcin; a.sign = sign; a.tri = tri;
+  const double share = tri == 0 ? 1.0 : (tri & cqr::TRI_C_LOWER) ? 1.0 / 3 : 0.5;
+  bool launched = false;
+  prof(p, PH_ADJOINT, share * 2.0 * M * N * (double)K, 8.0 * ((double)M * K + (double)K * N + 2.0 * M * N), st,
+       [&] { launched = cqr::launch_nn_adj(a, st); });
+  if (launched) return;
+  // C -= A B as it is for sign 1; for sign -1, -(-Cin - A B)
+  if (!Cin)
+    prof(p, PH_ADJOINT, 0.0, 8.0 * M * N, st, [&] { cqr::launch_fill_zero(C, ldc, M, N, st); });
+  else if (Cin != C)
+    prof(p, PH_ADJOINT, 0.0, 16.0 * M * N, st, [&] { cqr::launch_copy(Cin, ldcin, C, ldc, M, N, st); });
+  if (sign < 0.0 && Cin)
+    prof(p, PH_ADJOINT, 0.0, 16.0 * M * N, st, [&] { cqr::launch_scale(C, ldc, M, N, -1.0, st); });
+  nn(p, PH_ADJOINT, C, ldc, A, lda, B, ldb, M, N, K, s, st);
+  if (sign < 0.0)
+    prof(p, PH_ADJOINT, 0.0, 16.0 * M * N, st, [&] { cqr::launch_scale(C, ldc, M, N, -1.0, st); });
+}
+
+// Largest block of the triangular inverse whose pairs share a launch
+// (launch_inv_level); larger pairs fill the chip one by one.
+constexpr int64_t kInvBatch = 512;
+
 // Rinv = R_1^{-1} (n x n, ld n) by recursive doubling: the 64 x 64 diagonal
 // blocks are inverted at once and laid out as a block-diagonal Rinv; then,
 // for h = 64, 128, 256, ..., every pair of adjacent h-blocks [i, i+h) and
 // [i+h, i+2h) gets its off-diagonal block T12 = -T11 R12 T22 from the two
-// inverted diagonal blocks (W = R12 T22 into Wtmp, then T12 -= T11 W), on the
-// MFMA update kernels: n^3/3 flops in products (s: the split partials).
+// inverted diagonal blocks (W = R12 T22 into Wtmp, n x n, then T12 = -T11 W):
+// n^3/6 flops in products (s: the split partials of the general kernels).
 void upper_inverse(cqr_plan_s& p, const double* R, int64_t ldr, double* Rinv, double* Wtmp, double* T,
                    const cqr::Scratch& s, hipStream_t st) {
   const int64_t n = p.cfg.n, nb = (n + 63) / 64;
@@ -1174,17 +1216,19 @@ void upper_inverse(cqr_plan_s& p, const double* R, int64_t ldr, double* Rinv, do
        [&] { cqr::launch_trinv(R, ldr, n, T, st); });
   prof(p, PH_ADJOINT, 0.0, 8.0 * n * n, st, [&] { cqr::launch_blockdiag(T, Rinv, n, n, st); });
   for (int64_t h = 64; h < n; h *= 2) {
+    if (h <= kInvBatch) {
+      for (bool second : {false, true})
+        prof(p, PH_ADJOINT, 0.5 * (double)h * h * n, 12.0 * (double)h * n, st,
+             [&] { cqr::launch_inv_level(R, ldr, Rinv, Wtmp, n, h, second, st); });
+      continue;
+    }
     for (int64_t i = 0; i + h < n; i += 2 * h) {
       const int64_t h2 = std::min(h, n - i - h);
-      const double* R12 = R + i + (i + h) * ldr;
-      const double* T11 = Rinv + i + i * n;
-      const double* T22 = Rinv + (i + h) + (i + h) * n;
-      double* T12 = Rinv + i + (i + h) * n;
-      // Wtmp = -R12 T22, negated to R12 T22; T12 (zero) -= T11 Wtmp
-      prof(p, PH_ADJOINT, 0.0, 8.0 * h * h2, st, [&] { cqr::launch_fill_zero(Wtmp, h, h, h2, st); });
-      nn(p, PH_ADJOINT, Wtmp, h, R12, ldr, T22, n, h, (int)h2, (int)h2, s, st);
-      prof(p, PH_ADJOINT, 0.0, 16.0 * h * h2, st, [&] { cqr::launch_scale(Wtmp, h, h, h2, -1.0, st); });
-      nn(p, PH_ADJOINT, T12, n, T11, n, Wtmp, h, h, (int)h2, (int)h, s, st);
+      double* W = Wtmp + i + (i + h) * n;
+      nn_tri(p, W, n, nullptr, 0, -1.0, cqr::TRI_B_UPPER, R + i + (i + h) * ldr, ldr, Rinv + (i + h) + (i + h) * n, n,
+             h, (int)h2, (int)h2, s, st);
+      nn_tri(p, Rinv + i + (i + h) * n, n, nullptr, 0, 1.0, cqr::TRI_A_UPPER, Rinv + i + i * n, n, W, n, h, (int)h2,
+             (int)h, s, st);
     }
   }
 }
@@ -1219,24 +1263,23 @@ cqr_status coded_qr_backward(cqr_plan p, const double* Q, int64_t ldq, const dou
   double* X = take(8 * (size_t)mp * n);
   const double nn2 = 8.0 * n * n;
   upper_inverse(*p, R, ldr, Rinv, W1, T, s, st);
-  // W2 = M1 = Q~^T dQ~
-  tn(*p, PH_ADJOINT, Q, ldq, dQ, lddq, (int)n, (int)n, mp, W2, n, nullptr, 0, s, st);
-  // W1 = M1^T;  W2 = triu(dR)^T;  W1 -= R W2, so W1 = dQ~^T Q~ - R dR^T = -M
-  prof(*p, PH_ADJOINT, 0.0, 2 * nn2, st, [&] { cqr::launch_transpose(W2, n, W1, n, n, n, 1.0, false, st); });
+  // copyltu reads only M's lower triangle, so only that of both its products
+  // is formed:  W1 = dQ~^T Q~;  W2 = triu(dR)^T;  W1 -= R W2, so W1 = -M
+  // (D and X, not yet in use, take its split partials)
+  cqr::Scratch sd = s;
+  sd.part = D;
+  sd.npart = 2 * mp * n / (kTile * kTile);
+  if (sd.npart < s.npart) sd = s;
+  tn_lower(*p, dQ, lddq, Q, ldq, (int)n, mp, W1, n, sd, st);
   prof(*p, PH_ADJOINT, 0.0, 2 * nn2, st, [&] { cqr::launch_transpose(dR, lddr, W2, n, n, n, 1.0, true, st); });
-  nn(*p, PH_ADJOINT, W1, n, R, ldr, W2, n, n, (int)n, (int)n, s, st);
+  nn_tri(*p, W1, n, W1, n, 1.0, cqr::TRI_C_LOWER | cqr::TRI_A_UPPER, R, ldr, W2, n, n, (int)n, (int)n, s, st);
   // W1 <- copyltu(W1) = -copyltu(M)
   prof(*p, PH_ADJOINT, 0.0, nn2, st, [&] { cqr::launch_copyltu(W1, n, n, st); });
   // D = dQ~ - Q~ W1 = dQ~ + Q~ copyltu(M)
-  {
-    hipError_t e = hipMemcpy2DAsync(D, 8 * mp, dQ, 8 * lddq, 8 * mp, n, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  nn(*p, PH_ADJOINT, D, mp, Q, ldq, W1, n, mp, (int)n, (int)n, s, st);
-  // W2 = -R^{-T};  X = 0;  X -= D W2, so X = D R^{-T} = dA~
-  prof(*p, PH_ADJOINT, 0.0, 2 * nn2, st, [&] { cqr::launch_transpose(Rinv, n, W2, n, n, n, -1.0, false, st); });
-  prof(*p, PH_ADJOINT, 0.0, 8.0 * mp * n, st, [&] { cqr::launch_fill_zero(X, mp, mp, n, st); });
-  nn(*p, PH_ADJOINT, X, mp, D, mp, W2, n, mp, (int)n, (int)n, s, st);
+  nn_tri(*p, D, mp, dQ, lddq, 1.0, 0, Q, ldq, W1, n, mp, (int)n, (int)n, s, st);
+  // X = D R^{-T} (W2 = R^{-T}, lower triangular) = dA~
+  prof(*p, PH_ADJOINT, 0.0, 2 * nn2, st, [&] { cqr::launch_transpose(Rinv, n, W2, n, n, n, 1.0, false, st); });
+  nn_tri(*p, X, mp, nullptr, 0, -1.0, cqr::TRI_B_LOWER, D, mp, W2, n, mp, (int)n, (int)n, s, st);
   // dA = dA~_top + G_v^T dA~_bottom
   cqr::FoldArgs f{};
   f.X = X; f.ldx = mp; f.dA = dA; f.ldd = ldda;
@@ -1246,15 +1289,10 @@ cqr_status coded_qr_backward(cqr_plan p, const double* Q, int64_t ldq, const dou
   return hip_status();
 }
 
-// Split partials of the triangular inverse's products (the update kernels
-// split K over at most 512 workgroups).
-constexpr int64_t kSolvePartTiles = 1024;
-
 size_t coded_qr_solve_backward_workspace_bytes(cqr_plan p, int32_t nrhs) {
   if (!p || nrhs < 1) return 0;
-  const size_t n = (size_t)p->cfg.n, nb = (n + 63) / 64;
-  return 2 * up256(8 * n * n) + up256(8 * nb * 64 * 64) + up256(8 * n * (size_t)nrhs) +
-         up256(8 * (size_t)kSolvePartTiles * kTile * kTile);
+  const size_t n = (size_t)p->cfg.n, m = (size_t)p->cfg.m, nb = (n + 63) / 64;
+  return up256(8 * nb * 64 * 64) + up256(8 * n * (size_t)nrhs) + up256(8 * m * (size_t)nrhs);
 }
 
 cqr_status coded_qr_solve_backward(cqr_plan p, const double* Qpost, int64_t ldqp, const double* R, int64_t ldr,
@@ -1272,29 +1310,25 @@ cqr_status coded_qr_solve_backward(cqr_plan p, const double* Qpost, int64_t ldqp
     return CQR_ENOMEM;
   char* w = static_cast<char*>(ws);
   auto take = [&](size_t bytes) { double* q = reinterpret_cast<double*>(w); w += up256(bytes); return q; };
-  double* Rinv = take(8 * (size_t)n * n);
-  double* Ytmp = take(8 * (size_t)n * n);
   double* T = take(8 * (size_t)nb * 64 * 64);
   double* DY = take(8 * (size_t)n * nrhs);
-  cqr::Scratch s{};
-  s.part = take(8 * (size_t)kSolvePartTiles * kTile * kTile);
-  s.npart = kSolvePartTiles;
-  upper_inverse(*p, R, ldr, Rinv, Ytmp, T, s, st);
-  // dy = R_1^{-T} dX = Rinv^T dX
-  prof(*p, PH_ADJOINT, 2.0 * n * n * nrhs, 8.0 * (n * n + 2.0 * n * nrhs), st,
-       [&] { cqr::launch_gemv_t(Rinv, n, n, (int)n, dX, lddx, nrhs, DY, n, st); });
+  double* GB = take(8 * (size_t)m * nrhs);
+  // dy = R_1^{-T} dX: the solve's substitution with R_1 transposed
+  prof(*p, PH_ADJOINT, nb * 64.0 * 64 * 64 / 3, 8.0 * (n * 64.0 + nb * 64.0 * 64 + n * nrhs), st,
+       [&] { cqr::launch_trinv(R, ldr, n, T, st, DY, n, nrhs); });
+  prof(*p, PH_ADJOINT, ((double)n * n + 128.0 * n) * nrhs, 8.0 * (0.5 * n * n + nb * 64.0 * 64 + 2.0 * n * nrhs), st,
+       [&] { cqr::launch_trsv_flow(R, ldr, T, dX, lddx, DY, n, nrhs, n, true, st); });
   // dR_1 = -triu(dy x^T)
   prof(*p, PH_ADJOINT, 2.0 * n * n * nrhs, 8.0 * n * n, st,
-       [&] { cqr::launch_outer(DY, n, X, ldx, n, n, nrhs, -1.0, true, dR, lddr, st); });
-  // dQ~[:m] = G_0 (Bpost dy^T), dQ~[m:] = 0
-  prof(*p, PH_ADJOINT, 2.0 * m * n * nrhs, 8.0 * m * n, st,
-       [&] { cqr::launch_outer(Bpost, ldbp, DY, n, m, n, nrhs, 1.0, false, dQ, lddq, st); });
+       [&] { cqr::launch_outer(DY, n, X, ldx, n, n, n, nrhs, -1.0, true, dR, lddr, st); });
+  // dQ~[:m] = G_0 (Bpost dy^T) = (G_0 Bpost) dy^T, dQ~[m:] = 0
   cqr::PostArgs a{};
   a.pr = p->cfg.pr; a.kv = p->cfg.kv; a.bs = p->bs;
   for (size_t e = 0; e < p->gv.size(); ++e) a.gv[e] = p->gv[e];
-  a.src = dQ; a.lds = lddq; a.dst = dQ; a.ldd = lddq; a.cols = n;
-  prof(*p, PH_ADJOINT, 0.0, 16.0 * m * n, st, [&] { cqr::launch_postorth(a, st); });
-  prof(*p, PH_ADJOINT, 0.0, 8.0 * (mp - m) * n, st, [&] { cqr::launch_fill_zero(dQ + m, lddq, mp - m, n, st); });
+  a.src = Bpost; a.lds = ldbp; a.dst = GB; a.ldd = m; a.cols = nrhs;
+  prof(*p, PH_ADJOINT, 0.0, 16.0 * m * nrhs, st, [&] { cqr::launch_postorth(a, st); });
+  prof(*p, PH_ADJOINT, 2.0 * m * n * nrhs, 8.0 * mp * n, st,
+       [&] { cqr::launch_outer(GB, m, DY, n, m, mp, n, nrhs, 1.0, false, dQ, lddq, st); });
   // dB = G_0 (Qpost dy)
   prof(*p, PH_ADJOINT, 2.0 * m * n * nrhs, 8.0 * (m * n + m * nrhs), st,
        [&] { cqr::launch_gemv_n(Qpost, ldqp, m, (int)n, DY, n, nrhs, dB, lddb, st); });

@@ -582,7 +582,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   __shared__ double sB[2][128 * LW];
   const int tilesM = a.ntiles / a.tilesN;
   const int qm = (tilesM + 1) / 2;
-  const int tp = blockIdx.x % qm, tq = blockIdx.x / qm, split = blockIdx.y;
+  int tp = blockIdx.x % qm, tq = blockIdx.x / qm;
+  const int split = blockIdx.y;
+  if (a.lower) {                       // blocks on and below the diagonal, row by row
+    tp = (int)((sqrtf(8.0f * blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    if (tp * (tp + 1) / 2 > (int)blockIdx.x) --tp;
+    if ((tp + 1) * (tp + 2) / 2 <= (int)blockIdx.x) ++tp;
+    tq = blockIdx.x - tp * (tp + 1) / 2;
+  }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
   const int wi = wave & 1, wj = wave >> 1;
   const int ia0 = 64 * wi, jb0 = 32 * wj;
@@ -1061,12 +1068,66 @@ __global__ __launch_bounds__(256) void tn_direct_kernel(TnArgs a) {
   tn_store(a, acc, tile, split, wave, lane, i0, j0, false);
 }
 
-// Sum the split partials in split order; write C (and C2 +=).  One block per
-// wave quadrant of a tile, thread (qg, lane) owns 4 of the lane's 16 values.
+// Sum the split partials in split order; write C (and C2 +=).  A workgroup of G
+// groups of 64 threads takes U of a wave quadrant's 16 element slots per lane;
+// each group sums a contiguous range of the splits and the groups' sums are
+// added in order.  Bound by reading the partials: few output tiles and many
+// splits (a Gram product of a tall matrix: one tile, 288 splits) would
+// otherwise leave 4 workgroups a tile reading them one after the other.
+template <int G, int U>
+__global__ __launch_bounds__(64 * G) void tn_reduce_split_kernel(TnArgs a) {
+  if (a.prio) __builtin_amdgcn_s_setprio(2);
+  __shared__ double red[G][U][64];
+  constexpr int kSlots = 16 / U;               // workgroups per quadrant
+  const int tile = blockIdx.x / (4 * kSlots), wave = blockIdx.x / kSlots & 3, q0 = blockIdx.x % kSlots * U;
+  const int tm = tile / a.tilesN, tn = tile % a.tilesN;
+  if (a.lower && (tn >> 1) > (tm >> 1)) return;
+  const int grp = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  // the element this thread finishes: slot q = q0 + grp (groups below U)
+  const int q = q0 + grp % U;
+  const int i = tm * 64 + (wave & 1) * 32 + 16 * (q >> 3) + li;
+  const int j = tn * 64 + (wave >> 1) * 32 + 16 * (q >> 2 & 1) + colsub(q & 3, g, a.f32);
+  const bool out = grp < U && i < a.M && j < a.N;
+  const bool add = out && a.C2 && i < a.M2;
+  const double old = add ? a.C2[i + (int64_t)j * a.ldc2] : 0.0;
+  const int per = (a.nsplit + G - 1) / G, s0 = grp * per, s1 = std::min(a.nsplit, s0 + per);
+  const double* base = a.part + part_off(0, a.ntiles, tile, wave) + q0 * 64 + lane;
+  const int64_t sstride = (int64_t)a.ntiles * 4 * 1024;
+  double v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = 0.0;
+  for (int sp0 = s0; sp0 < s1; sp0 += 16) {
+    double t[16][U];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int sp = std::min(sp0 + k, s1 - 1);         // clamped: extra loads are discarded
+#pragma unroll
+      for (int u = 0; u < U; ++u) t[k][u] = base[sp * sstride + u * 64];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] += sp0 + k < s1 ? t[k][u] : 0.0;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) red[grp][u][lane] = v[u];
+  __syncthreads();
+  if (!out) return;
+  double x = 0.0;
+#pragma unroll
+  for (int e = 0; e < G; ++e) x += red[e][grp][lane];
+  a.C[i + (int64_t)j * a.ldc] = x;
+  if (add) a.C2[i + (int64_t)j * a.ldc2] = old + x;
+}
+
+// The same for few splits: one block per wave quadrant of a tile, thread
+// (qg, lane) owns 4 of the lane's 16 values and sums all splits.
 __global__ __launch_bounds__(256) void tn_reduce_kernel(TnArgs a) {
   if (a.prio) __builtin_amdgcn_s_setprio(2);
   const int tile = blockIdx.x >> 2, wave = blockIdx.x & 3;
   const int tm = tile / a.tilesN, tn = tile % a.tilesN;
+  if (a.lower && (tn >> 1) > (tm >> 1)) return;
   const int qg = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int i = tm * 64 + (wave & 1) * 32 + 16 * (qg >> 1) + li;
   const int jq = tn * 64 + (wave >> 1) * 32 + 16 * (qg & 1);         // + colsub(u, g)
@@ -1158,6 +1219,25 @@ TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int 
   return a;
 }
 
+// A square product of which only the lower triangle is read: the 128 x 128
+// kernel leaves the blocks above the diagonal out (the others compute all of
+// C), which halves its work.  Split as pick_split_quad does, for the blocks
+// that run.  The grid holds only those: empty workgroups in a full grid would
+// leave the XCDs, which take workgroups in turn, with unequal shares.
+TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
+                      int64_t ldc, const Scratch& s) {
+  const int t = (N + 2 * kTile - 1) / (2 * kTile), tiles = (N + kTile - 1) / kTile;
+  // (at least 1024 rows a split: its partials then take an eighth of the bytes
+  // of its operands)
+  const int ns = (int)std::min<int64_t>(pick_split_quad(t * (t + 1) / 2, K, s.npart, tiles * tiles),
+                                        std::max<int64_t>(1, K / 1024));
+  TnArgs a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s);
+  if (!a.quad) return a;
+  a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s, ns);
+  a.lower = 1;
+  return a;
+}
+
 void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return;
   const dim3 grid(a.ntiles, a.nsplit);
@@ -1171,7 +1251,8 @@ void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
     return;
   }
   if (a.quad) {
-    const dim3 gridq((unsigned)((a.ntiles / a.tilesN + 1) / 2 * ((a.tilesN + 1) / 2)), a.nsplit);
+    const unsigned qm = (a.ntiles / a.tilesN + 1) / 2, qn = (a.tilesN + 1) / 2;
+    const dim3 gridq(a.lower ? qm * (qm + 1) / 2 : qm * qn, a.nsplit);
     if (a.f32) {
       hipLaunchKernelGGL(tnf_kernel, gridq, dim3(512), 0, st, a);
       return;
@@ -1213,7 +1294,14 @@ void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
 
 void launch_tn_reduce(const TnArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0 || a.nsplit <= 1) return;
-  hipLaunchKernelGGL(tn_reduce_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a);
+  // one batch of 16 loads per thread covers up to 16 splits; beyond that the
+  // splits are shared by 4 or 16 groups of threads
+  if (a.nsplit <= 16)
+    hipLaunchKernelGGL(tn_reduce_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a);
+  else if (a.nsplit <= 64)
+    hipLaunchKernelGGL((tn_reduce_split_kernel<4, 4>), dim3(a.ntiles * 16), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((tn_reduce_split_kernel<16, 1>), dim3(a.ntiles * 64), dim3(1024), 0, st, a);
 }
 
 // --------------------------------------------------------------------------
@@ -2568,6 +2656,27 @@ NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const doub
   return a;
 }
 
+// Tile and k range [klo, khi) of workgroup b in the adjoint's products, whose
+// operands may be triangular; false for a tile that is not needed.  The XCDs
+// take workgroups in turn and the tiles' work is uneven, so they are dealt with
+// the row index fastest (every XCD gets each column's rows in equal shares,
+// long columns first; xcd_tile's contiguous ranges would give some XCDs twice
+// the work of others), rotated by the column where rows differ too.
+__device__ __forceinline__ bool nn_tri_tile(const NnArgs& a, int b, int tilesM, int T, int& tm, int& tn, int& klo,
+                                            int& khi) {
+  tn = b / tilesM;
+  tm = b - tn * tilesM;
+  if (a.tri & TRI_C_LOWER) {
+    tm += tn;
+    if (tm >= tilesM) return false;
+  }
+  const int i0 = tm * T, j0 = tn * T;
+  if (a.tri & TRI_A_UPPER) klo = i0;
+  if ((a.tri & TRI_B_LOWER) && j0 > klo) klo = j0;
+  if ((a.tri & TRI_B_UPPER) && j0 + T < khi) khi = j0 + T;
+  return true;
+}
+
 // In-place rank-K update C (M x N) -= A (M x K) B (K x N) for K >= 64 (the
 // trailing update, long unsplit re-projections), with
 // the product kernel's pipeline: 64 x 64 output tile per block, 4 waves each
@@ -2587,7 +2696,12 @@ __device__ __forceinline__ void nnw_body(const NnArgs& a, double (*sA)[64 * (SK 
   constexpr int TPC = SK / 2;        // B staging: threads per column (one k pair each)
   constexpr int CPP = 256 / TPC;     // B staging: columns per pass
   int tm, tn;
-  xcd_tile(blockIdx.x, a.ntiles, a.ntiles / a.tilesN, a.tilesN, tm, tn);
+  int klo = 0, khi = a.K;
+  if constexpr (TAG == TAG_ADJ) {
+    if (!nn_tri_tile(a, blockIdx.x, a.ntiles / a.tilesN, 64, tm, tn, klo, khi)) return;
+  } else {
+    xcd_tile(blockIdx.x, a.ntiles, a.ntiles / a.tilesN, a.tilesN, tm, tn);
+  }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
   const int ia0 = (wave & 1) * 32, jb0 = (wave >> 1) * 32;
   const int64_t ib = (int64_t)tm * 64, jb = (int64_t)tn * 64;
@@ -2598,26 +2712,29 @@ __device__ __forceinline__ void nnw_body(const NnArgs& a, double (*sA)[64 * (SK 
   for (int e = 0; e < 16; ++e) {
     const int x = e >> 3, y = (e >> 2) & 1, r = e & 3;
     const int64_t i = ib + ia0 + 16 * x + li, j = jb + jb0 + 16 * y + colsub(r, g, false);
-    cval[e] = a.C[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldc];
+    if constexpr (TAG == TAG_ADJ)
+      cval[e] = a.Cin ? a.Cin[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldcin] : 0.0;
+    else
+      cval[e] = a.C[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldc];
   }
   // staging of A: thread loads one v2d (rows 2 ip, 2 ip + 1) of k rows kr + 8 q
   const int ip = tid & 31, kr = tid >> 5;
   const int64_t ia = ib + 2 * ip;
-  const double* ga = a.A + (ia + 1 < a.M ? ia : 0) + (int64_t)kr * a.lda;
+  const double* ga = a.A + (ia + 1 < a.M ? ia : 0) + (int64_t)(klo + kr) * a.lda;
   // staging of B: thread loads one v2d (k pair lq) of columns lc + CPP q
   const int lc = tid / TPC, lq = tid % TPC;
   const double* gb[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int64_t j = jb + lc + CPP * q;
-    gb[q] = a.B + (j < a.N ? j : 0) * a.ldb + 2 * lq;
+    gb[q] = a.B + klo + (j < a.N ? j : 0) * a.ldb + 2 * lq;
   }
   Acc acc[2][2];
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 2; ++y) acc[x][y] = Acc{0, 0, 0, 0};
-  const int nsl = a.K / SK;
+  const int nsl = (khi - klo) / SK;
   auto compute = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < SK; kk += 16) {
@@ -2682,7 +2799,9 @@ __device__ __forceinline__ void nnw_body(const NnArgs& a, double (*sA)[64 * (SK 
   for (int e = 0; e < 16; ++e) {
     const int x = e >> 3, y = (e >> 2) & 1, r = e & 3;
     const int64_t i = ib + ia0 + 16 * x + li, j = jb + jb0 + 16 * y + colsub(r, g, false);
-    if (i < a.M && j < a.N) a.C[i + j * a.ldc] = cval[e] - acc[x][y][r];
+    double v = acc[x][y][r];
+    if constexpr (TAG == TAG_ADJ) v *= a.sign;
+    if (i < a.M && j < a.N) a.C[i + j * a.ldc] = cval[e] - v;
   }
 }
 
@@ -2729,19 +2848,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   __shared__ double sB[2][128 * LW];
   const int tilesM = (int)((a.M + 127) / 128), tilesN = (a.N + 127) / 128;
   int tm, tn;
-  xcd_tile(blockIdx.x, tilesM * tilesN, tilesM, tilesN, tm, tn);
+  int klo = 0, khi = a.K;
+  if constexpr (TAG == TAG_ADJ) {
+    if (!nn_tri_tile(a, blockIdx.x, tilesM, 128, tm, tn, klo, khi)) return;
+  } else {
+    xcd_tile(blockIdx.x, tilesM * tilesN, tilesM, tilesN, tm, tn);
+  }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
   const int ia0 = 64 * (wave & 1), jb0 = 32 * (wave >> 1);
   const int64_t ib = (int64_t)tm * 128, jb = (int64_t)tn * 128;
   const int ip = tid & 63, kr = tid >> 6;
   const int64_t ia = ib + 2 * ip;
-  const double* ga = a.A + (ia + 1 < a.M ? ia : 0) + (int64_t)kr * a.lda;
+  const double* ga = a.A + (ia + 1 < a.M ? ia : 0) + (int64_t)(klo + kr) * a.lda;
   const int lc = tid / TPC, lq = tid % TPC;
   const double* gb[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int64_t j = jb + lc + CPP * q;
-    gb[q] = a.B + (j < a.N ? j : 0) * a.ldb + 2 * lq;
+    gb[q] = a.B + klo + (j < a.N ? j : 0) * a.ldb + 2 * lq;
   }
   v4d acc[4][2];
 #pragma unroll
@@ -2770,7 +2894,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
           for (int y = 0; y < 2; ++y) acc[x][y] = mfma(xb[y][s], xa[x][s], acc[x][y]);
     }
   };
-  const int nsl = a.K / SK;
+  const int nsl = (khi - klo) / SK;
   v2d ra[2], rb[2];
   auto load = [&](int64_t k) {
 #pragma unroll
@@ -2809,14 +2933,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t j = jb + jb0 + 16 * y + colsub(r, g, false);
-        cv[y][r] = a.C[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldc];
+        if constexpr (TAG == TAG_ADJ)
+          cv[y][r] = a.Cin ? a.Cin[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldcin] : 0.0;
+        else
+          cv[y][r] = a.C[(i < a.M ? i : 0) + (j < a.N ? j : 0) * a.ldc];
       }
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t j = jb + jb0 + 16 * y + colsub(r, g, false);
-        if (i < a.M && j < a.N) a.C[i + j * a.ldc] = cv[y][r] - acc[x][y][r];
+        double v = acc[x][y][r];
+        if constexpr (TAG == TAG_ADJ) v *= a.sign;
+        if (i < a.M && j < a.N) a.C[i + j * a.ldc] = cv[y][r] - v;
       }
   }
 }
@@ -2859,6 +2988,20 @@ void launch_nn_product(const NnArgs& a, int tag, hipStream_t st) {
     case TAG_REPROJ: nn_launch_tag<TAG_REPROJ>(a, st); break;
     default: nn_launch_tag<TAG_PANEL>(a, st); break;
   }
+}
+
+// The adjoint's products: C = Cin - sign A B with C, Cin apart and triangular
+// operands' zero tiles left out.  The kernel by size as in nn_launch_tag;
+// false, launching nothing, for operands the LDS-staged kernels do not take.
+bool launch_nn_adj(const NnArgs& a, hipStream_t st) {
+  if (!nnw_ok(a)) return false;
+  // (fewer 128 x 128 blocks than the chip holds leave it idle: 64 x 64 tiles then)
+  const int64_t blocks = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+  if (nnq_ok(a) && blocks >= 512)
+    hipLaunchKernelGGL((nnq_kernel<TAG_ADJ>), dim3((unsigned)blocks), dim3(512), 0, st, a);
+  else
+    hipLaunchKernelGGL((nnw16_kernel<TAG_ADJ>), dim3(a.ntiles), dim3(256), 0, st, a);
+  return true;
 }
 
 bool launch_nn_chol(const NnArgs& a, const CholArgs& c, hipStream_t st) {

@@ -81,7 +81,7 @@ struct Scratch {
 
 // Kernel-instance tags: each use of a product kernel gets its own symbol, so
 // per-kernel profiles map onto the steps of the factorization.
-enum : int { TAG_TRAIL = 0, TAG_REPROJ = 1, TAG_PANEL = 2 };
+enum : int { TAG_TRAIL = 0, TAG_REPROJ = 1, TAG_PANEL = 2, TAG_ADJ = 3 };
 
 // C (M x N) [= or +=] A^T B, A: K x M (lda), B: K x N (ldb), split over K.
 struct TnArgs {
@@ -102,6 +102,7 @@ struct TnArgs {
   int bf3;            // split-BF16 product (tnb_kernel): each FP64 operand as hi + mid + lo
                       // BF16 parts, six part products on BF16 MFMA with FP32 sums over
                       // 32 k-values, FP64 sums across them (output layout as f32)
+  int lower;          // square product, 128 x 128 blocks above the diagonal left out (quad only)
 };
 
 // Choose the split of C = A^T B (stored to C; rows below M2 -- all rows
@@ -114,6 +115,9 @@ struct TnArgs {
 // product R_bar = Qbar^T Q_t.
 TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int M, int N, int64_t K, double* C,
                 int64_t ldc, double* C2, int64_t ldc2, const Scratch& s, int force_split = 0, int lowp = 0);
+// C = A^T B (N x N) of which only the lower triangle is read
+TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
+                      int64_t ldc, const Scratch& s);
 // The product; with nsplit == 1 it stores C (and C2) itself, else partials.
 void launch_tn_product(const TnArgs& a, int tag, hipStream_t st);
 // Sum the partials into C (and C2) in split order (nsplit > 1 only).
@@ -136,13 +140,21 @@ struct NnArgs {
   int vec;            // B 16-byte aligned with even ldb (vector B loads)
   double* part;
   int prio;           // raise the waves' issue priority (panel-chain products)
+  // launch_nn_adj only: C = Cin - sign A B (Cin == nullptr: zero), tri: TRI_* flags
+  const double* Cin; int64_t ldcin;
+  double sign;
+  int tri;
 };
+// Structure of a product's operands, taken tile by tile: A zero for k < i, B
+// zero for k < j or for k > j, only C's lower triangle read.
+enum : int { TRI_A_UPPER = 1, TRI_B_LOWER = 2, TRI_B_UPPER = 4, TRI_C_LOWER = 8 };
 // The update is FP64 in every precision mode: it is a column operation on the
 // encoded matrix and must keep the checksum relations to FP64 rounding.
 NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M,
                 int N, int K, const Scratch& s);
 void launch_nn_product(const NnArgs& a, int tag, hipStream_t st);
 void launch_nn_reduce(const NnArgs& a, hipStream_t st);   // nsplit > 1 only
+bool launch_nn_adj(const NnArgs& a, hipStream_t st);
 
 // Arguments of the panel Cholesky kernel (Gram matrix W in, T = R^{-1} and R1
 // to scratch, on the second pass R2 R1 to Rout and T^T X to Rbar).
@@ -230,18 +242,25 @@ void launch_trinv(const double* R, int64_t ldr, int64_t n, double* T, hipStream_
 void launch_transpose(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows, int64_t cols,
                       double scale, bool upper, hipStream_t st);
 void launch_copyltu(double* C, int64_t ldc, int64_t n, hipStream_t st);
-void launch_outer(const double* U, int64_t ldu, const double* V, int64_t ldv, int64_t rows, int64_t cols, int k,
-                  double scale, bool upper, double* C, int64_t ldc, hipStream_t st);
+// C (rows x cols) = scale U V^T (U rowsu x k: zero rows from rowsu on; upper: zero below the diagonal)
+void launch_outer(const double* U, int64_t ldu, const double* V, int64_t ldv, int64_t rowsu, int64_t rows,
+                  int64_t cols, int k, double scale, bool upper, double* C, int64_t ldc, hipStream_t st);
 void launch_gemv_n(const double* A, int64_t lda, int64_t m, int n, const double* x, int64_t ldx, int nrhs,
                    double* y, int64_t ldy, hipStream_t st);
 void launch_fold(const FoldArgs& a, hipStream_t st);
 // Y (n x n) = block diagonal of the 64 x 64 tiles of T (tile k at T + 4096 k)
 void launch_blockdiag(const double* T, double* Y, int64_t ldy, int64_t n, hipStream_t st);
+// dst = src (rows x cols)
+void launch_copy(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t rows, int64_t cols, hipStream_t st);
 // C *= s (rows x cols)
 void launch_scale(double* C, int64_t ldc, int64_t rows, int64_t cols, double s, hipStream_t st);
-// R X = Y after launch_trinv(R, ..., T, st, X, ldx, nrhs)
+// one level of the triangular inverse by doubling (h a multiple of 64): for every pair of
+// adjacent h-blocks W = R12 T22 (second = false), then T12 = -T11 W (second = true)
+void launch_inv_level(const double* R, int64_t ldr, double* Rinv, double* W, int64_t n, int64_t h, bool second,
+                      hipStream_t st);
+// R X = Y (or R^T X = Y) after launch_trinv(R, ..., T, st, X, ldx, nrhs)
 void launch_trsv_flow(const double* R, int64_t ldr, double* T, const double* Y, int64_t ldy, double* X, int64_t ldx,
-                      int nrhs, int64_t n, hipStream_t st);
+                      int nrhs, int64_t n, bool trans, hipStream_t st);
 // The allocation-free solve's scratch: a file-scope device array of
 // kSolveScratchBytes, one copy per device.  *ptr receives the current
 // device's copy's address (looked up on the first call on each device).

@@ -18,26 +18,32 @@ constexpr int kSolveBlock = 64;      // diagonal block of the back substitution
 constexpr int kRhsChunk = 4;         // right-hand sides per pass
 constexpr long long kUnset = -1;     // bit pattern of an entry of X not yet solved (a NaN)
 
+// Y = Q^T B: WPC waves share a column of Q (its m entries are contiguous), a
+// wave takes every WPC-th run of 64 rows; their sums are added in order.  Bound
+// by reading Q: one wave per column leaves a tall matrix with few columns too
+// little in flight (65536 x 512, one right-hand side: 140 us with one wave per
+// column, 68 with four).
+template <int WPC>
 __global__ __launch_bounds__(kSolveThreads) void gemv_t_kernel(const double* Q, int64_t ldq, int64_t m, int n,
                                                                const double* B, int64_t ldb, int nrhs, double* Y,
                                                                int64_t ldy) {
-  const int lane = threadIdx.x & 63;
-  const int col = blockIdx.x * (kSolveThreads / 64) + (threadIdx.x >> 6);
-  if (col >= n) return;
-  const double* q = Q + (int64_t)col * ldq;
+  __shared__ double part[kSolveThreads / 64][kRhsChunk];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = blockIdx.x * (kSolveThreads / 64 / WPC) + wave / WPC, w0 = wave % WPC;
+  const double* q = Q + (int64_t)(col < n ? col : 0) * ldq;
   constexpr int kBatch = 8;   // rows per lane whose loads are issued together
   for (int r0 = 0; r0 < nrhs; r0 += kRhsChunk) {
     const int nr = nrhs - r0 < kRhsChunk ? nrhs - r0 : kRhsChunk;
     double acc[kRhsChunk] = {0.0, 0.0, 0.0, 0.0};
-    int64_t i = lane;
-    for (; i + (kBatch - 1) * 64 < m; i += kBatch * 64) {
+    int64_t i = w0 * 64 + lane;
+    for (; i + (kBatch - 1) * 64 * WPC < m; i += kBatch * 64 * WPC) {
       double qv[kBatch], bv[kBatch][kRhsChunk];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        qv[j] = q[i + j * 64];
+        qv[j] = q[i + j * 64 * WPC];
 #pragma unroll
         for (int t = 0; t < kRhsChunk; ++t)
-          bv[j][t] = t < nr ? B[i + j * 64 + (int64_t)(r0 + t) * ldb] : 0.0;
+          bv[j][t] = t < nr ? B[i + j * 64 * WPC + (int64_t)(r0 + t) * ldb] : 0.0;
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -45,7 +51,7 @@ __global__ __launch_bounds__(kSolveThreads) void gemv_t_kernel(const double* Q, 
 #pragma unroll
         for (int t = 0; t < kRhsChunk; ++t) acc[t] += qv[j] * bv[j][t];
     }
-    for (; i < m; i += 64) {
+    for (; i < m; i += 64 * WPC) {
       const double v = q[i];
 #pragma unroll
       for (int t = 0; t < kRhsChunk; ++t)
@@ -56,7 +62,21 @@ __global__ __launch_bounds__(kSolveThreads) void gemv_t_kernel(const double* Q, 
       double v = acc[t];
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0 && r0 + t < nrhs) Y[col + (int64_t)(r0 + t) * ldy] = v;
+      if (WPC == 1) {
+        if (lane == 0 && col < n && t < nr) Y[col + (int64_t)(r0 + t) * ldy] = v;
+      } else if (lane == 0) {
+        part[wave][t] = v;
+      }
+    }
+    if (WPC > 1) {
+      __syncthreads();
+      if (w0 == 0 && lane < nr && col < n) {
+        double v = 0.0;
+#pragma unroll
+        for (int e = 0; e < WPC; ++e) v += part[wave + e][lane];
+        Y[col + (int64_t)(r0 + lane) * ldy] = v;
+      }
+      __syncthreads();
     }
   }
 }
@@ -189,7 +209,10 @@ __device__ __forceinline__ void flow_fma8(double (&acc)[NR], const double (&m)[8
     }
 }
 
-template <int NR>
+// TRANS: R_1^T X = Y, the same walk from the top block down, with R's tiles and
+// T transposed (a thread then holds 16 consecutive rows of columns lane and
+// lane + 64; VEC: as 16-byte loads).
+template <int NR, bool TRANS, bool VEC>
 __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R, int64_t ldr, double* T,
                                                                  const double* Y, int64_t ldy, double* X, int64_t ldx,
                                                                  int nrhs, int64_t n, int nblk, int chunks) {
@@ -202,17 +225,38 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
   __syncthreads();
   const int ticket = s_ticket;
   if (ticket >= nblk * chunks) return;
-  const int k = nblk - 1 - ticket / chunks, r0 = (ticket % chunks) * NR;
+  const int k = TRANS ? ticket / chunks : nblk - 1 - ticket / chunks, r0 = (ticket % chunks) * NR;
   const int64_t k0 = (int64_t)k * kFlowRows;
   const int nr = nrhs - r0 < NR ? nrhs - r0 : NR;
   const bool two = k0 + kSolveBlock < n;       // the block reaches past its upper 64 rows
 
   // the tile of block j: rows lane and lane + 64, columns 16 wave .. 16 wave + 15
+  // (TRANS: columns lane and lane + 64 of this block, rows 16 wave .. of block j;
+  // blocks above another are whole)
   const double* ra = R + (k0 + lane < n ? k0 + lane : 0) + (int64_t)(16 * wave) * ldr;
   const double* rb = R + (k0 + 64 + lane < n ? k0 + 64 + lane : 0) + (int64_t)(16 * wave) * ldr;
+  if (TRANS) {
+    ra = R + 16 * wave + (k0 + lane < n ? k0 + lane : 0) * ldr;
+    rb = R + 16 * wave + (k0 + 64 + lane < n ? k0 + 64 + lane : 0) * ldr;
+  }
   auto load = [&](double (&v)[32], int j) {
     const int64_t c0 = (int64_t)j * kFlowRows;
-    if (c0 + kFlowRows <= n) {
+    if constexpr (TRANS && VEC) {
+#pragma unroll
+      for (int t = 0; t < 16; t += 2) {
+        const v2d xa = *reinterpret_cast<const v2d*>(ra + c0 + t), xb = *reinterpret_cast<const v2d*>(rb + c0 + t);
+        v[t] = xa.x;
+        v[t + 1] = xa.y;
+        v[16 + t] = xb.x;
+        v[17 + t] = xb.y;
+      }
+    } else if constexpr (TRANS) {
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        v[t] = ra[c0 + t];
+        v[16 + t] = rb[c0 + t];
+      }
+    } else if (c0 + kFlowRows <= n) {
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
         v[t] = ra[(c0 + t) * ldr];
@@ -228,9 +272,11 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
     }
   };
   double va[32], vb[32];
-  if (nblk - 1 > k) load(va, nblk - 1);
+  const int first = TRANS ? 0 : nblk - 1, step = TRANS ? 1 : -1;
+  const int steps = TRANS ? k : nblk - 1 - k;      // blocks solved before this one
+  if (steps > 0) load(va, first);
   // the two inverted diagonal blocks and R_1[upper 64 rows, lower 64 columns]:
-  // row `lane`, columns 8 wave .. 8 wave + 7; T's entries below its diagonal
+  // row `lane`, columns 8 wave .. 8 wave + 7 (TRANS: of their transposes); T's entries below its diagonal
   // are zero (one of them holds the counter)
   double ta[8], tb[8], rab[8];
   {
@@ -238,9 +284,10 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int c = 8 * wave + e;
-      ta[e] = lane <= c ? t0[lane + c * kSolveBlock] : 0.0;
-      tb[e] = two && lane <= c ? t0[kSolveBlock * kSolveBlock + lane + c * kSolveBlock] : 0.0;
-      rab[e] = k0 + kSolveBlock + c < n ? R[k0 + lane + (k0 + kSolveBlock + c) * ldr] : 0.0;
+      const int i = TRANS ? c : lane, l = TRANS ? lane : c;      // the entry's row and column
+      ta[e] = i <= l ? t0[i + l * kSolveBlock] : 0.0;
+      tb[e] = two && i <= l ? t0[kSolveBlock * kSolveBlock + i + l * kSolveBlock] : 0.0;
+      rab[e] = k0 + kSolveBlock + l < n ? R[k0 + i + (k0 + kSolveBlock + l) * ldr] : 0.0;
     }
   }
   // hand-over and the block's own rows: thread (row pr, right-hand side pu)
@@ -279,16 +326,17 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
         ab[u] += v[17 + t] * x.y;
       }
   };
-  for (int j = nblk - 1; j > k; j -= 2) {
-    if (j - 1 > k) load(vb, j - 1);
+  for (int e = 0; e < steps; e += 2) {
+    const int j = first + step * e;
+    if (e + 1 < steps) load(vb, j + step);
     __builtin_amdgcn_sched_barrier(0);
     await(j);
     subtract(va, j);
-    if (j - 1 > k) {
-      if (j - 2 > k) load(va, j - 2);
+    if (e + 1 < steps) {
+      if (e + 2 < steps) load(va, j + 2 * step);
       __builtin_amdgcn_sched_barrier(0);
-      await(j - 1);
-      subtract(vb, j - 1);
+      await(j + step);
+      subtract(vb, j + step);
     }
   }
 #pragma unroll
@@ -297,14 +345,14 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
     red[wave][u][64 + lane] = ab[u];
   }
   __syncthreads();
-  double y = y0;                // of row pr, right-hand side pu
-  if (pu < NR) {
+  if (pu < NR) {                // row pr, right-hand side pu
+    double y = y0;
 #pragma unroll
     for (int e = 0; e < kFlowWaves; ++e) y -= red[e][pu][pr];
-    yk[pu][pr] = y;
+    yk[pu][pr] = k0 + pr < n ? y : 0.0;     // (rows past n hold sums of clamped loads)
   }
   __syncthreads();
-  // x_b = T_b y_b;  y_a -= R_ab x_b;  x_a = T_a y_a
+  // x_b = T_b y_b;  y_a -= R_ab x_b;  x_a = T_a y_a (TRANS: x_a first)
   auto matvec = [&](const double (&m)[8], const double (*v)[kFlowRows], int off) {
     double s[NR];
 #pragma unroll
@@ -320,27 +368,38 @@ __global__ __launch_bounds__(kFlowThreads) void trsv_flow_kernel(const double* R
     }
     return x;                   // of row pr < 64, right-hand side pu
   };
-  if (two) {
-    const double xb = matvec(tb, yk, kSolveBlock);
-    if (pu < NR && pr < kSolveBlock) {
-      xs[0][pu][pr] = xb;
-      if (k0 + kSolveBlock + pr < n && pu < nr)
-        flow_store(X + k0 + kSolveBlock + pr + (int64_t)(r0 + pu) * ldx, xb);
+  // solve 64 rows (h = 0: upper, 1: lower) with their inverted block
+  const bool mine = pu < NR && pr < kSolveBlock;
+  auto solve = [&](const double (&m)[8], int h) {
+    const double x = matvec(m, yk, kSolveBlock * h);
+    if (mine) {
+      xs[0][pu][pr] = x;
+      const int64_t r = k0 + kSolveBlock * h + pr;
+      if (r < n && pu < nr) flow_store(X + r + (int64_t)(r0 + pu) * ldx, x);
     }
     __syncthreads();
+  };
+  const int h0 = TRANS ? 0 : 1;
+  if (TRANS || two) {
+    if (TRANS) solve(ta, 0); else solve(tb, 1);
+    if (!two) return;
     const double d = matvec(rab, xs[0], 0);
-    if (pu < NR && pr < kSolveBlock) yk[pu][pr] = y - d;
+    if (mine) yk[pu][kSolveBlock * (1 - h0) + pr] -= d;
     __syncthreads();
   }
-  const double xa = matvec(ta, yk, 0);
-  if (pr < kSolveBlock && pu < nr && k0 + pr < n) flow_store(X + k0 + pr + (int64_t)(r0 + pu) * ldx, xa);
+  if (TRANS) solve(tb, 1); else solve(ta, 0);
 }
 
 void launch_gemv_t(const double* Q, int64_t ldq, int64_t m, int n, const double* B, int64_t ldb, int nrhs,
                    double* Y, int64_t ldy, hipStream_t st) {
+  // four waves per column while that keeps the grid within 1024 workgroups
+  // (n = 4096: one wave per column already reads at the rate of a large copy)
   const int per = kSolveThreads / 64;
-  hipLaunchKernelGGL(gemv_t_kernel, dim3((n + per - 1) / per), dim3(kSolveThreads), 0, st, Q, ldq, m, n, B, ldb,
-                     nrhs, Y, ldy);
+  if (n <= 1024)
+    hipLaunchKernelGGL(gemv_t_kernel<4>, dim3(n), dim3(kSolveThreads), 0, st, Q, ldq, m, n, B, ldb, nrhs, Y, ldy);
+  else
+    hipLaunchKernelGGL(gemv_t_kernel<1>, dim3((n + per - 1) / per), dim3(kSolveThreads), 0, st, Q, ldq, m, n, B, ldb,
+                       nrhs, Y, ldy);
 }
 
 void launch_trinv(const double* R, int64_t ldr, int64_t n, double* T, hipStream_t st, double* X, int64_t ldx,
@@ -350,18 +409,24 @@ void launch_trinv(const double* R, int64_t ldr, int64_t n, double* T, hipStream_
 }
 
 void launch_trsv_flow(const double* R, int64_t ldr, double* T, const double* Y, int64_t ldy, double* X, int64_t ldx,
-                      int nrhs, int64_t n, hipStream_t st) {
+                      int nrhs, int64_t n, bool trans, hipStream_t st) {
   const int nblk = (int)((n + kFlowRows - 1) / kFlowRows);
   auto go = [&](auto kern, int per) {
     const int chunks = (nrhs + per - 1) / per;
     hipLaunchKernelGGL(kern, dim3((unsigned)nblk * chunks), dim3(kFlowThreads), 0, st, R, ldr, T, Y, ldy, X, ldx, nrhs,
                        n, nblk, chunks);
   };
+  const bool vec = reinterpret_cast<uintptr_t>(R) % 16 == 0 && ldr % 2 == 0;
   // one right-hand side by itself: a quarter of the LDS reads on the chain
-  if (nrhs == 1)
-    go(trsv_flow_kernel<1>, 1);
-  else
-    go(trsv_flow_kernel<kRhsChunk>, kRhsChunk);
+  if (nrhs == 1) {
+    if (!trans) go(trsv_flow_kernel<1, false, false>, 1);
+    else if (vec) go(trsv_flow_kernel<1, true, true>, 1);
+    else go(trsv_flow_kernel<1, true, false>, 1);
+  } else {
+    if (!trans) go(trsv_flow_kernel<kRhsChunk, false, false>, kRhsChunk);
+    else if (vec) go(trsv_flow_kernel<kRhsChunk, true, true>, kRhsChunk);
+    else go(trsv_flow_kernel<kRhsChunk, true, false>, kRhsChunk);
+  }
 }
 
 // Scratch memory of the allocation-free solve (coded_qr_solve_noalloc): the
