@@ -67,7 +67,7 @@ KERNEL_OF = {
     "panel_gram": "tn_lds_kernel<2, false>", "panel_chol": "chol_kernel", "panel_transform": "apply_kernel / nn1_apply_kernel",
     "inpanel_projection": "tn/nn <2, false>",
     "trailing_product": "tn_lds_kernel<0, false>", "trailing_update": "nnw_kernel<0>",
-    "split_reduce": "tn_reduce_kernel / nn_reduce_kernel", "recover": "line_kernel",
+    "split_reduce": "tn_reduce_kernel / nn_reduce_kernel", "recover": "lines_kernel",
     "postorth": "postorth_kernel", "erase": "erase_kernel", "other": "zero_ints_kernel / fill_zero_kernel",
     "solve": "gemv_t_kernel / trinv_kernel / trsv_flow_kernel",
 }

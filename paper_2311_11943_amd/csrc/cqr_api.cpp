@@ -981,10 +981,10 @@ cqr_status coded_qr_erase(cqr_plan p, double* Q, int64_t ldq, double* R, int64_t
     rs.insert(r.begin(), r.end());
   }
   auto flush = [&](double* base, int64_t ld, int rows, int cols, std::vector<int64_t>& offs) {
-    for (size_t i = 0; i < offs.size(); i += 64) {
+    for (size_t i = 0; i < offs.size(); i += cqr::kEraseMax) {
       cqr::EraseArgs a{};
       a.base = base; a.ld = ld; a.rows = rows; a.cols = cols;
-      a.nblk = (int)std::min<size_t>(64, offs.size() - i);
+      a.nblk = (int)std::min<size_t>(cqr::kEraseMax, offs.size() - i);
       for (int k = 0; k < a.nblk; ++k) a.off[k] = offs[i + k];
       prof(*p, PH_ERASE, 0.0, 8.0 * rows * cols * a.nblk, st, [&] { cqr::launch_erase(a, st); });
     }
@@ -1011,31 +1011,52 @@ cqr_status coded_qr_recover(cqr_plan p, double* Q, int64_t ldq, double* R, int64
     qs.insert(q.begin(), q.end());
     rs.insert(r.begin(), r.end());
   }
-  std::vector<cqr::LineArgs> launches;
+  // One code line, blocks `slot` elements apart from `off`: its outputs in
+  // groups of kMaxOut, added to the last launch of the same matrix while they fit.
+  std::vector<cqr::LinesArgs> launches;
+  auto add_line = [&](const std::vector<double>& gen, int ndata, int nchk, const LineJob& job, double* base, int64_t ld,
+                      int64_t rows, int64_t slot, int64_t off) -> cqr_status {
+    if (job.lost_d.empty() && job.lost_c.empty()) return CQR_OK;
+    std::vector<int> srcs, outs;
+    std::vector<double> coef;
+    const cqr_status e = plan_line(gen, ndata, nchk, job, srcs, outs, coef);
+    if (e != CQR_OK) return e;
+    const int ns = (int)srcs.size();
+    for (size_t o0 = 0; o0 < outs.size(); o0 += kMaxOut) {
+      const int no = (int)std::min<size_t>(kMaxOut, outs.size() - o0);
+      int used = 0;
+      bool fits = !launches.empty() && launches.back().base == base && launches.back().slot == slot &&
+                  launches.back().nlines < cqr::kLinesMax;
+      if (fits) {
+        const cqr::LineSpec& l = launches.back().line[launches.back().nlines - 1];
+        used = l.coef + l.nsrc * l.nout;
+        fits = used + no * ns <= cqr::kLinesCoef;
+      }
+      if (!fits) {
+        launches.emplace_back();
+        cqr::LinesArgs& a = launches.back();
+        a.base = base; a.ld = ld; a.slot = slot; a.rows = (int)rows; a.cols = (int)p->bw;
+        a.nlines = 0;
+        used = 0;
+      }
+      cqr::LinesArgs& a = launches.back();
+      cqr::LineSpec& l = a.line[a.nlines++];
+      l.off = off; l.coef = used; l.nsrc = (uint8_t)ns; l.nout = (uint8_t)no;
+      for (int s = 0; s < ns; ++s) l.src[s] = (uint8_t)srcs[s];
+      for (int o = 0; o < no; ++o) {
+        l.dst[o] = (uint8_t)outs[o0 + o];
+        for (int s = 0; s < ns; ++s) a.coef[used + o * ns + s] = coef[(o0 + o) * ns + s];
+      }
+    }
+    return CQR_OK;
+  };
   // Q: every block column J, vertical code  chk_k = sum_t g~_v[k][t] data_t.
   for (int J = 0; J < pc + kh; ++J) {
     LineJob job;
     for (int I = 0; I < pr; ++I) if (qs.count({I, J})) job.lost_d.push_back(I);
     for (int k = 0; k < kv; ++k) if (qs.count({pr + k, J})) job.lost_c.push_back(k);
-    if (job.lost_d.empty() && job.lost_c.empty()) continue;
-    std::vector<int> srcs, outs;
-    std::vector<double> coef;
-    cs = plan_line(p->gv, pr, kv, job, srcs, outs, coef);
+    cs = add_line(p->gv, pr, kv, job, Q, ldq, p->bs, p->bs, (int64_t)J * p->bw * ldq);
     if (cs != CQR_OK) return cs;
-    auto off = [&](int slot) { return (int64_t)slot * p->bs + (int64_t)J * p->bw * ldq; };
-    const int ns = (int)srcs.size();
-    for (size_t o0 = 0; o0 < outs.size(); o0 += kMaxOut) {
-      cqr::LineArgs a{};
-      a.base = Q; a.ld = ldq; a.rows = (int)p->bs; a.cols = (int)p->bw;
-      a.nsrc = ns;
-      a.nout = (int)std::min<size_t>(kMaxOut, outs.size() - o0);
-      for (int s = 0; s < ns; ++s) a.src[s] = off(srcs[s]);
-      for (int o = 0; o < a.nout; ++o) {
-        a.dst[o] = off(outs[o0 + o]);
-        for (int s = 0; s < ns; ++s) a.coef[o][s] = coef[(o0 + o) * ns + s];
-      }
-      launches.push_back(a);
-    }
   }
   // R without a horizontal code: every block column J, the vertical code of
   // R's block rows (the same generator as Q's).
@@ -1044,25 +1065,8 @@ cqr_status coded_qr_recover(cqr_plan p, double* Q, int64_t ldq, double* R, int64
       LineJob job;
       for (int I = 0; I < pr; ++I) if (rs.count({I, J})) job.lost_d.push_back(I);
       for (int k = 0; k < kv; ++k) if (rs.count({pr + k, J})) job.lost_c.push_back(k);
-      if (job.lost_d.empty() && job.lost_c.empty()) continue;
-      std::vector<int> srcs, outs;
-      std::vector<double> coef;
-      cs = plan_line(p->gv, pr, kv, job, srcs, outs, coef);
+      cs = add_line(p->gv, pr, kv, job, R, ldr, p->hr, p->hr, (int64_t)J * p->bw * ldr);
       if (cs != CQR_OK) return cs;
-      auto off = [&](int slot) { return (int64_t)slot * p->hr + (int64_t)J * p->bw * ldr; };
-      const int ns = (int)srcs.size();
-      for (size_t o0 = 0; o0 < outs.size(); o0 += kMaxOut) {
-        cqr::LineArgs a{};
-        a.base = R; a.ld = ldr; a.rows = (int)p->hr; a.cols = (int)p->bw;
-        a.nsrc = ns;
-        a.nout = (int)std::min<size_t>(kMaxOut, outs.size() - o0);
-        for (int s = 0; s < ns; ++s) a.src[s] = off(srcs[s]);
-        for (int o = 0; o < a.nout; ++o) {
-          a.dst[o] = off(outs[o0 + o]);
-          for (int s = 0; s < ns; ++s) a.coef[o][s] = coef[(o0 + o) * ns + s];
-        }
-        launches.push_back(a);
-      }
     }
   }
   // R: every block row i, horizontal code  chk_k = sum_t g~_h[t][k] data_t.
@@ -1074,31 +1078,18 @@ cqr_status coded_qr_recover(cqr_plan p, double* Q, int64_t ldq, double* R, int64
       LineJob job;
       for (int J = 0; J < pc; ++J) if (rs.count({i, J})) job.lost_d.push_back(J);
       for (int k = 0; k < kh; ++k) if (rs.count({i, pc + k})) job.lost_c.push_back(k);
-      if (job.lost_d.empty() && job.lost_c.empty()) continue;
-      std::vector<int> srcs, outs;
-      std::vector<double> coef;
-      cs = plan_line(genT, pc, kh, job, srcs, outs, coef);
+      cs = add_line(genT, pc, kh, job, R, ldr, p->hr, p->bw * ldr, (int64_t)i * p->hr);
       if (cs != CQR_OK) return cs;
-      auto off = [&](int slot) { return (int64_t)i * p->hr + (int64_t)slot * p->bw * ldr; };
-      const int ns = (int)srcs.size();
-      for (size_t o0 = 0; o0 < outs.size(); o0 += kMaxOut) {
-        cqr::LineArgs a{};
-        a.base = R; a.ld = ldr; a.rows = (int)p->hr; a.cols = (int)p->bw;
-        a.nsrc = ns;
-        a.nout = (int)std::min<size_t>(kMaxOut, outs.size() - o0);
-        for (int s = 0; s < ns; ++s) a.src[s] = off(srcs[s]);
-        for (int o = 0; o < a.nout; ++o) {
-          a.dst[o] = off(outs[o0 + o]);
-          for (int s = 0; s < ns; ++s) a.coef[o][s] = coef[(o0 + o) * ns + s];
-        }
-        launches.push_back(a);
-      }
     }
   }
   for (const auto& a : launches) {
     const double el = (double)a.rows * a.cols;
-    prof(*p, PH_RECOVER, 2.0 * el * a.nsrc * a.nout, 8.0 * el * (a.nsrc + a.nout), st,
-         [&] { cqr::launch_line(a, st); });
+    double fl = 0.0, by = 0.0;
+    for (int l = 0; l < a.nlines; ++l) {
+      fl += 2.0 * el * a.line[l].nsrc * a.line[l].nout;
+      by += 8.0 * el * (a.line[l].nsrc + a.line[l].nout);
+    }
+    prof(*p, PH_RECOVER, fl, by, st, [&] { cqr::launch_lines(a, st); });
   }
   return hip_status();
 }

@@ -12,23 +12,33 @@ constexpr int kMaxGrid = 32;     // p_r, p_c upper bound
 constexpr int kLeaf = 64;        // widest panel leaf factored by Cholesky QR
 constexpr int kTile = 64;        // output tile of the split-K product kernel
 
-// Linear combination of blocks along one code line: out_o = sum_s coef[o][s] * src_s.
-struct LineArgs {
-  double* base;
-  int64_t ld;
-  int rows, cols;
-  int nsrc, nout;
-  int64_t src[kMaxLine];
-  int64_t dst[kMaxOut];
-  double coef[kMaxOut][kMaxLine];
+// Code lines decoded by one launch.  Line l's blocks lie `slot` elements apart
+// from base + off; out_o = sum_s coef[o * nsrc + s] src_s.
+constexpr int kLinesMax = 16;    // lines a launch
+constexpr int kLinesCoef = 640;  // coefficients a launch (5 KB of kernel arguments); one line has at most 256
+struct LineSpec {
+  int64_t off;
+  int coef;                      // first coefficient
+  uint8_t nsrc, nout;
+  uint8_t src[kMaxLine];
+  uint8_t dst[kMaxOut];
 };
+struct LinesArgs {
+  double* base;
+  int64_t ld, slot;
+  int rows, cols, nlines;
+  LineSpec line[kLinesMax];
+  double coef[kLinesCoef];
+};
+static_assert(kMaxOut * kMaxLine <= kLinesCoef, "a line's coefficients fit one launch");
 
+constexpr int kEraseMax = 256;   // blocks an erasure launch
 struct EraseArgs {
   double* base;
   int64_t ld;
   int rows, cols;
   int nblk;
-  int64_t off[64];
+  int64_t off[kEraseMax];
 };
 
 struct EncodeArgs {
@@ -229,7 +239,7 @@ void launch_fill_zero(double* p, int64_t ld, int64_t rows, int64_t cols, hipStre
 void launch_encode_rows(const EncodeArgs& a, hipStream_t st);
 // the whole encoding in one pass: checksum rows (g), columns (gc) and corner
 void launch_encode_fused(const EncodeArgs& a, hipStream_t st);
-void launch_line(const LineArgs& a, hipStream_t st);
+void launch_lines(const LinesArgs& a, hipStream_t st);
 void launch_erase(const EraseArgs& a, hipStream_t st);
 void launch_postorth(const PostArgs& a, hipStream_t st);
 // coded solve: Y = Q^T B (Q m x n), then blocked back substitution with R_1
