@@ -332,6 +332,12 @@ int tag_of(int phase) {
 // the update stream's kernels, the chain sets the pace of the factorization.
 int chain_phase(int phase) { return phase != PH_TRAIL_TN && phase != PH_TRAIL_NN; }
 
+// First tile of the Gram partials in the split-partial area: the split
+// re-projection update, whose partials are read by the launch that writes the
+// Gram partials, takes at most 512 tiles (nn_setup), the Gram partials at most
+// 512 (panel_first_blocks), of at least 1024.
+constexpr int kGramPartTile = 512;
+
 double partial_bytes(int nsplit, int ntiles) { return 8.0 * nsplit * ntiles * cqr::kTile * cqr::kTile; }
 
 void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B, int64_t ldb, int M, int N,
@@ -381,17 +387,6 @@ void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64
   } else {
     prof(p, phase, fl, by + upd, st, [&] { cqr::launch_nn_product(a, tag, st); });
   }
-}
-
-// The second pass (pass 2) gets the panel P (for its column-wise breakdown
-// fallback) and, when an update already started from the panel's first
-// pass, that panel's fallback flag.
-void chol(cqr_plan_s& p, const double* W, int64_t ldw, int w, int pass, double* Rout, int64_t ldr, const double* X,
-          int64_t ldx, double* Rbar, int panel, const cqr::Scratch& s, hipStream_t st, double* Tcopy = nullptr,
-          double* P = nullptr, int64_t ldp = 0, int* fb = nullptr) {
-  prof(p, PH_CHOL, 2.0 * w * w * w * (X ? 2.0 : 1.0),
-       8.0 * w * w * (pass == 1 ? 3.0 : (X ? 6.0 : 4.0) + (Tcopy ? 1.0 : 0.0)), st,
-       [&] { cqr::launch_chol(W, ldw, w, pass, Rout, ldr, X, ldx, Rbar, panel, s, st, Tcopy, P, ldp, p.mp, fb); });
 }
 
 // Column-wise panel modes (CGS2, ICGS, MGS): a grid of workgroups
@@ -446,56 +441,58 @@ void tn_tmul(cqr_plan_s& p, const cqr::TnArgs& a, const double* T, int w, double
 }
 
 // The split re-projection update C -= A B with the panel's first Cholesky
-// pass (c) run by one extra block of the same launch, then the split
-// reduction fused with the pass's transform C <- C T (the result also stored
-// to X when X != nullptr).  Returns false, launching nothing, when the update
-// would not split over K; the caller then runs the update, the Cholesky and
-// the transform separately.
+// pass (c) run by one extra block of the same launch; the partials (a: their
+// split) are left for panel_first.  Returns false, launching nothing, when the
+// update would not split over K; the caller then runs the update by itself.
 bool nn_chol(cqr_plan_s& p, double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb,
-             int64_t M, int N, int K, const cqr::CholArgs& c, const cqr::Scratch& s, hipStream_t st,
-             double* X = nullptr, int64_t ldx = 0) {
-  if (M <= 0 || N <= 0 || K <= cqr::kLeaf || c.w > cqr::kLeaf) return false;
-  cqr::NnArgs a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
+             int64_t M, int N, int K, const cqr::CholArgs& c, const cqr::Scratch& s, hipStream_t st, cqr::NnArgs& a) {
+  a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
   a.prio = 1;
-  if (a.nsplit <= 1 || a.tilesN != 1 || N != c.w) return false;
+  if (K <= cqr::kLeaf || a.nsplit <= 1 || a.tilesN != 1 || N != c.w || c.w > cqr::kLeaf) return false;
   const double fl = 2.0 * M * N * (double)K + 2.0 * c.w * c.w * c.w;
   const double by = 8.0 * ((double)M * K + (double)K * N) + 24.0 * c.w * c.w;
   bool launched = false;
   prof(p, PH_REPROJ_NN, fl, by + partial_bytes(a.nsplit, a.ntiles), st,
        [&] { launched = cqr::launch_nn_chol(a, c, st); });
-  if (!launched) return false;
-  prof(p, PH_REDUCE, (double)a.nsplit * M * N + 2.0 * M * N * N,
-       partial_bytes(a.nsplit, a.ntiles) + (X ? 24.0 : 16.0) * (double)M * N, st,
-       [&] { cqr::launch_nn_reduce_apply(a, c.T, c.w, X, ldx, st); });
-  return true;
-}
-
-// The second pass's transform P <- P T (T = the pass's R^{-1} in scratch) and
-// the lookahead update C -= P B (B: w x w) in one launch; false, launching
-// nothing, when the shapes do not allow it.
-bool apply_update(cqr_plan_s& p, double* C, int64_t ldc, double* P, int64_t ldq, const double* B, int64_t ldb,
-                  int w, const cqr::Scratch& s, hipStream_t st) {
-  const int64_t mp = p.mp;
-  const cqr::NnArgs a = cqr::nn_setup(C, ldc, P, ldq, B, ldb, mp, w, w, s);
-  if (a.tilesN != 1 || a.K != w || w > cqr::kLeaf) return false;
-  bool launched = false;
-  prof(p, PH_APPLY, 4.0 * mp * w * w, 8.0 * (4.0 * mp * w + 2.0 * w * w), st,
-       [&] { launched = cqr::launch_nn1_apply(a, s.T, w, st); });
   return launched;
 }
 
-void apply(cqr_plan_s& p, double* P, int64_t ldq, int w, const cqr::Scratch& s, hipStream_t st) {
-  const int64_t mp = p.mp;
-  prof(p, PH_APPLY, 2.0 * mp * w * w, 16.0 * mp * w, st, [&] { cqr::launch_apply(P, ldq, mp, w, s, st); });
+// A leaf's panel in two Cholesky-QR passes from its Gram matrix W (ld ldw):
+// first pass's transform with the second pass's Gram product, the sum of its
+// partials, second pass with the update of the next panel Qn (nullptr: none).
+// split: the re-projection's partials (launched by nn_chol, with the first
+// pass's Cholesky), or nullptr.
+cqr::PanelArgs panel_args(cqr_plan_s& p, double* P, int64_t ldq, int w, double* Qn, const double* W, int64_t ldw,
+                          const cqr::NnArgs* split, double* R, int64_t ldr, int64_t c, int panel,
+                          const cqr::Scratch& s) {
+  cqr::PanelArgs a{};
+  a.P = P; a.ldp = ldq; a.mrows = p.mp; a.w = w;
+  a.Qn = Qn;
+  a.part = split ? split->part : nullptr;
+  a.nsplit = split ? split->nsplit : 1;
+  a.ntiles = split ? split->ntiles : 1;
+  a.T = s.T;
+  a.c = cqr::chol_args(W, ldw, w, panel, s);
+  // the split partials end before the Gram partials begin
+  a.gpart = s.part + (int64_t)kGramPartTile * kTile * kTile;
+  a.G = s.G;
+  a.Rout = R + c + c * ldr;
+  a.Rbar = R + c + (c + w) * ldr;
+  a.ldr = ldr;
+  return a;
 }
 
-// One Cholesky-QR pass on the panel P (m' x w): Gram product (+ reduction),
-// Cholesky factor and inverse, then P <- P R^{-1}.
-void cholqr_pass(cqr_plan_s& p, double* P, int64_t ldq, int w, int pass, double* Rout, int64_t ldr, int panel,
-                 const cqr::Scratch& s, hipStream_t st) {
-  tn(p, PH_GRAM, P, ldq, P, ldq, w, w, p.mp, s.G, w, nullptr, 0, s, st);
-  chol(p, s.G, w, w, pass, Rout, ldr, nullptr, 0, nullptr, panel, s, st, nullptr, P, ldq);
-  apply(p, P, ldq, w, s, st);
+void panel_first(cqr_plan_s& p, const cqr::PanelArgs& a, bool chol, hipStream_t st) {
+  const double m = (double)p.mp, w = a.w, nx = a.Qn ? 2.0 : 1.0, sp = a.nsplit > 1 ? a.nsplit : 0.0;
+  const double pb = partial_bytes(cqr::panel_first_blocks(p.mp), a.Qn ? 2 : 1);
+  prof(p, PH_APPLY, (2.0 + 2.0 * nx) * m * w * w + sp * m * w, 8.0 * m * w * (1.0 + nx + sp + (a.X ? 1.0 : 0.0)) + pb,
+       st, [&] { cqr::launch_panel_first(a, chol, st); });
+  prof(p, PH_REDUCE, pb / 8.0, pb, st, [&] { cqr::launch_panel_reduce(a, st); });
+}
+
+void panel_second(cqr_plan_s& p, const cqr::PanelArgs& a, hipStream_t st) {
+  const double m = (double)p.mp, w = a.w, nx = a.Qn ? 2.0 : 1.0;
+  prof(p, PH_CHOL, 2.0 * nx * m * w * w, 16.0 * nx * m * w, st, [&] { cqr::launch_panel_second(a, st); });
 }
 
 // Panel of w columns starting at column c: leaves of <= kLeaf columns are
@@ -511,8 +508,10 @@ void factor_panel(cqr_plan_s& p, double* Q, int64_t ldq, double* R, int64_t ldr,
       colpanel(p, P, ldq, w, R + c + c * ldr, ldr, panel, s, st);
       return;
     }
-    cholqr_pass(p, P, ldq, w, 1, nullptr, 0, panel, s, st);
-    cholqr_pass(p, P, ldq, w, 2, R + c + c * ldr, ldr, panel, s, st);
+    tn(p, PH_GRAM, P, ldq, P, ldq, w, w, p.mp, s.G, w, nullptr, 0, s, st);
+    const cqr::PanelArgs a = panel_args(p, P, ldq, w, nullptr, s.G, w, nullptr, R, ldr, c, panel, s);
+    panel_first(p, a, true, st);
+    panel_second(p, a, st);
     return;
   }
   int h = (w / 2 + 15) / 16 * 16;
@@ -808,60 +807,53 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
       const double* W1 = s.G;
       int64_t ldw1 = b;
       bool chol1 = false;   // first Cholesky pass already launched
-      // Early update (with the first pass inside the re-projection's
-      // launches): panel k's update of the columns [c1 + b, N) starts on the
+      cqr::NnArgs split{};
+      if (p->cfg.reproject && k > 0) {
+        // S = Q[:, :c0]^T P (rows < c0, also added into R[:c0, panel]);  P -= Q[:, :c0] S.
+        // The first Cholesky pass needs only the Gram rows and the update only
+        // S, so when the update splits over K the Cholesky runs in its launch
+        // and the first pass's transform sums its partials.
+        tn(*p, PH_REPROJ_TN, Q, ldq, P, ldq, (int)c1, (int)b, mp, s.S, c1, R + c0 * ldr, ldr, s, st, (int)c0);
+        W1 = s.S + c0;
+        ldw1 = c1;
+        chol1 = nn_chol(*p, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0,
+                        cqr::chol_args(W1, ldw1, (int)b, k, s), s, st, split);
+        if (!chol1) nn(*p, PH_REPROJ_NN, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0, s, st);
+      } else {
+        tn(*p, PH_GRAM, P, ldq, P, ldq, (int)b, (int)b, mp, s.G, b, nullptr, 0, s, st);
+      }
+      // With lookahead the second pass also updates the next panel, whose
+      // columns must first carry panel k-1's update from the side stream.  (The
+      // wait is queued before panel k's early update records its own event.)
+      if (hipError_t e = join_side(); e != hipSuccess) return hip_fail(e);
+      // Early update: panel k's update of the columns [c1 + b, N) starts on the
       // side stream from the first-pass panel P1, which the first pass's
       // transform also stores to X, while the chain runs the second pass.  Its
       // reduction folds in the second pass's R2^{-1} (R_t = R2^{-T} P1^T Q_t =
       // P^T Q_t), and the update Q_t -= P R_t waits for the finished panel P.
       // X alternates between two buffers: the chain writes panel k+1's copy
       // before it waits for panel k's update.
-      double* X = (next && c1 + b < N && s.X) ? s.X + (k & 1) * s.xstride : nullptr;
-      if (p->cfg.reproject && k > 0) {
-        // S = Q[:, :c0]^T P (rows < c0, also added into R[:c0, panel]);  P -= Q[:, :c0] S.
-        // The first Cholesky pass needs only the Gram rows and the update only
-        // S, so when the update splits over K the Cholesky runs in its launch
-        // and the transform P <- P R1^{-1} in its split reduction.
-        tn(*p, PH_REPROJ_TN, Q, ldq, P, ldq, (int)c1, (int)b, mp, s.S, c1, R + c0 * ldr, ldr, s, st, (int)c0);
-        W1 = s.S + c0;
-        ldw1 = c1;
-        chol1 = nn_chol(*p, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0,
-                        cqr::chol_args(W1, ldw1, (int)b, 1, nullptr, 0, nullptr, 0, nullptr, k, s), s, st, X, s.ldx);
-        if (!chol1) nn(*p, PH_REPROJ_NN, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0, s, st);
-      } else {
-        tn(*p, PH_GRAM, P, ldq, P, ldq, (int)b, (int)b, mp, s.G, b, nullptr, 0, s, st);
+      const bool early = next && c1 + b < N && s.X;
+      cqr::PanelArgs pa = panel_args(*p, P, ldq, (int)b, next ? Q + c1 * ldq : nullptr, W1, ldw1,
+                                     chol1 ? &split : nullptr, R, ldr, c0, k, s);
+      if (early) {
+        pa.X = s.X + (k & 1) * s.xstride;
+        pa.ldx = s.ldx;
+        pa.Tcopy = s.T2;
+        pa.fb = s.fb + k;
       }
-      if (!chol1) {
-        chol(*p, W1, ldw1, (int)b, 1, nullptr, 0, nullptr, 0, nullptr, k, s, st);
-        apply(*p, P, ldq, (int)b, s, st);
-      }
-      const bool early = chol1 && X;
-      // (recorded before the chain's wait below, so the side stream's product
-      // does not wait for the chain to pass it)
-      if (early)
-        if (hipError_t e = hipEventRecord(p->ev_main, st); e != hipSuccess) return hip_fail(e);
-      // Second pass.  With lookahead the same product also gives
-      // X = P1^T Q_next, and the Cholesky kernel forms the next panel's
-      // coefficients R[panel, next] = (P1 R2^{-1})^T Q_next = R2^{-T} X.
-      // Q_next must first carry panel k-1's update from the side stream.  (The
-      // wait is queued before panel k's early update records its own event.)
-      if (hipError_t e = join_side(); e != hipSuccess) return hip_fail(e);
+      panel_first(*p, pa, !chol1, st);
       cqr::TnArgs ea{};
       if (early) {
-        if (hipError_t e = hipStreamWaitEvent(p->side, p->ev_main, 0); e != hipSuccess) return hip_fail(e);
-        ea = tn_early(*p, X, s.ldx, Q + (c1 + b) * ldq, ldq, (int)b, (int)(N - c1 - b), s2, p->side, lowp);
+        hipError_t e = hipEventRecord(p->ev_main, st);
+        if (e == hipSuccess) e = hipStreamWaitEvent(p->side, p->ev_main, 0);
+        if (e != hipSuccess) return hip_fail(e);
+        ea = tn_early(*p, pa.X, s.ldx, Q + (c1 + b) * ldq, ldq, (int)b, (int)(N - c1 - b), s2, p->side, lowp);
       }
-      tn(*p, PH_GRAM, P, ldq, P, ldq, (int)b, next ? 2 * (int)b : (int)b, mp, s.G, b, nullptr, 0, s, st);
-      chol(*p, s.G, b, (int)b, 2, R + c0 + c0 * ldr, ldr, next ? s.G + b * b : nullptr, b,
-           next ? R + c0 + c1 * ldr : nullptr, k, s, st, early ? s.T2 : nullptr, P, ldq, early ? s.fb + k : nullptr);
-      // P <- P1 R2^{-1}, and with lookahead Q_next -= P R[panel, next] (one
-      // launch)
-      const bool fused = next &&
-                         apply_update(*p, Q + c1 * ldq, ldq, P, ldq, R + c0 + c1 * ldr, ldr, (int)b, s, st);
-      if (!fused) apply(*p, P, ldq, (int)b, s, st);
+      // P <- P1 R2^{-1}, and with lookahead R[panel, next] = (P1 R2^{-1})^T
+      // Q_next, Q_next -= P R[panel, next]
+      panel_second(*p, pa, st);
       if (next) {
-        if (!fused)
-          nn(*p, PH_TRAIL_NN, Q + c1 * ldq, ldq, P, ldq, R + c0 + c1 * ldr, ldr, mp, (int)b, (int)b, s, st);
         if (early) {
           // the early update's reduction and rank-b update, after the panel
           hipError_t e = hipEventRecord(p->ev_apply, st);

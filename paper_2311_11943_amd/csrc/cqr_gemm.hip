@@ -66,25 +66,26 @@ __device__ __forceinline__ int64_t part_off(int sp, int ntiles, int tile, int wa
 }
 
 // Sum over splits of four element slots q = 4 qg + u (u < 4) of one wave's
-// partial tiles, lane `lane`, in split order.  Batches of 16 splits have all
+// partial tiles, lane `lane`, in split order.  Batches of kB splits have all
 // their loads issued before the first addition.
+template <int kB = 16>
 __device__ __forceinline__ void sum_partials4(const double* part, int nsplit, int ntiles, int tile, int wave,
                                               int qg, int lane, double (&v)[4]) {
 #pragma unroll
   for (int u = 0; u < 4; ++u) v[u] = 0.0;
   const double* base = part + part_off(0, ntiles, tile, wave) + 4 * qg * 64 + lane;
   const int64_t sstride = (int64_t)ntiles * 4 * 1024;
-  for (int sp0 = 0; sp0 < nsplit; sp0 += 16) {
-    double t[16][4];
+  for (int sp0 = 0; sp0 < nsplit; sp0 += kB) {
+    double t[kB][4];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < kB; ++k) {
       const int sp = std::min(sp0 + k, nsplit - 1);       // clamped: extra loads are discarded
 #pragma unroll
       for (int u = 0; u < 4; ++u) t[k][u] = base[sp * sstride + u * 64];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < kB; ++k)
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] += (sp0 + k < nsplit) ? t[k][u] : 0.0;
   }
@@ -1292,8 +1293,7 @@ void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
   }
 }
 
-void launch_tn_reduce(const TnArgs& a, hipStream_t st) {
-  if (a.M <= 0 || a.N <= 0 || a.nsplit <= 1) return;
+static void launch_tn_sum(const TnArgs& a, hipStream_t st) {
   // one batch of 16 loads per thread covers up to 16 splits; beyond that the
   // splits are shared by 4 or 16 groups of threads
   if (a.nsplit <= 16)
@@ -1302,6 +1302,11 @@ void launch_tn_reduce(const TnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((tn_reduce_split_kernel<4, 4>), dim3(a.ntiles * 16), dim3(256), 0, st, a);
   else
     hipLaunchKernelGGL((tn_reduce_split_kernel<16, 1>), dim3(a.ntiles * 64), dim3(1024), 0, st, a);
+}
+
+void launch_tn_reduce(const TnArgs& a, hipStream_t st) {
+  if (a.M <= 0 || a.N <= 0 || a.nsplit <= 1) return;
+  launch_tn_sum(a, st);
 }
 
 // --------------------------------------------------------------------------
@@ -1369,24 +1374,25 @@ __device__ __forceinline__ void chol_diag16(int lane, int o, double (*Rl)[kLeaf 
   }
 }
 
-// Exact path: blocked right-looking Cholesky of the 64 x 64 W in Rl (16 x 16
-// blocks) and the inverse T = R^{-1} in Tl.  Block step b: wave 0 factors the
-// diagonal block (R_bb, T_bb); the row panel R_bc = T_bb^T W_bc (c > b) and
-// the trailing update W_cd -= R_bc^T R_bd (b < c <= d) run on MFMA, one
-// 16 x 16 block per wave.  Then T's off-diagonal blocks, one block column per
-// wave: T_ab = -T_aa sum_{c=a+1..b} R_ac T_cb for a = b-1 down to 0.  About a
-// dozen block barriers instead of one per pivot.
-__device__ __forceinline__ void chol_blocked(int tid, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
+// Exact path: blocked right-looking Cholesky of W (16 nb columns, nb <= 4) in
+// Rl (16 x 16 blocks) and the inverse T = R^{-1} in Tl, which comes in as the
+// identity.  Block step b: wave 0 factors the diagonal block (R_bb, T_bb); the
+// row panel R_bc = T_bb^T W_bc (c > b) and the trailing update W_cd -= R_bc^T
+// R_bd (b < c <= d) run on MFMA, one 16 x 16 block per wave.  Then T's
+// off-diagonal blocks, one block column per wave: T_ab = -T_aa sum_{c=a+1..b}
+// R_ac T_cb for a = b-1 down to 0.  About three block barriers per 16 columns.
+__device__ __forceinline__ void chol_blocked(int tid, int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
                                              double* prow, const double* dg, bool& bad) {
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
 #pragma unroll 1
-  for (int b = 0; b < 4; ++b) {
+  for (int b = 0; b < nb; ++b) {
     const int o = 16 * b;
     if (wave == 0) chol_diag16(lane, o, Rl, Tl, prow, dg, bad);
     __syncthreads();
+    if (b + 1 == nb) break;
     // row panel R_bc = T_bb^T W_bc, in place
     const int c = b + 1 + wave;
-    if (c < 4) {
+    if (c < nb) {
       v4d acc = v4d{0, 0, 0, 0};
       mma16(acc, lane, 1, [&](int i, int k) { return Tl[o + k][o + i]; },
             [&](int k, int j) { return Rl[o + k][16 * c + j]; });
@@ -1397,9 +1403,9 @@ __device__ __forceinline__ void chol_blocked(int tid, double (*Rl)[kLeaf + 1], d
     // trailing update W_cd -= R_bc^T R_bd over the upper blocks b < c <= d
     int p = 0;
 #pragma unroll 1
-    for (int cc = b + 1; cc < 4; ++cc)
+    for (int cc = b + 1; cc < nb; ++cc)
 #pragma unroll 1
-      for (int dd = cc; dd < 4; ++dd, ++p) {
+      for (int dd = cc; dd < nb; ++dd, ++p) {
         if ((p & 3) != wave) continue;
         v4d acc = v4d{0, 0, 0, 0};
         mma16(acc, lane, 1, [&](int i, int k) { return Rl[o + k][16 * cc + i]; },
@@ -1409,36 +1415,27 @@ __device__ __forceinline__ void chol_blocked(int tid, double (*Rl)[kLeaf + 1], d
       }
     __syncthreads();
   }
-  if (wave < 3) {
-    // block column bc = wave + 1 of T
-    const int bc = wave + 1;
+  // block column wave of T (the blocks below the diagonal are zero in T as it
+  // comes in, and zeroed in R here: the columns left of block row `wave`)
 #pragma unroll 1
-    for (int a = bc - 1; a >= 0; --a) {
-      v4d acc = v4d{0, 0, 0, 0};
+  for (int a = wave < nb ? wave - 1 : -1; a >= 0; --a) {
+    v4d acc = v4d{0, 0, 0, 0};
 #pragma unroll 1
-      for (int cb = a + 1; cb <= bc; ++cb)
-        mma16(acc, lane, 1, [&](int i, int k) { return Rl[16 * a + i][16 * cb + k]; },
-              [&](int k, int j) { return Tl[16 * cb + k][16 * bc + j]; });
+    for (int cb = a + 1; cb <= wave; ++cb)
+      mma16(acc, lane, 1, [&](int i, int k) { return Rl[16 * a + i][16 * cb + k]; },
+            [&](int k, int j) { return Tl[16 * cb + k][16 * wave + j]; });
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Tl[16 * a + li][16 * bc + 4 * r + g] = acc[r];
-      __builtin_amdgcn_wave_barrier();
-      v4d t = v4d{0, 0, 0, 0};
-      mma16(t, lane, 1, [&](int i, int k) { return Tl[16 * a + i][16 * a + k]; },
-            [&](int k, int j) { return Tl[16 * a + k][16 * bc + j]; });
-      __builtin_amdgcn_wave_barrier();
+    for (int r = 0; r < 4; ++r) Tl[16 * a + li][16 * wave + 4 * r + g] = acc[r];
+    __builtin_amdgcn_wave_barrier();
+    v4d t = v4d{0, 0, 0, 0};
+    mma16(t, lane, 1, [&](int i, int k) { return Tl[16 * a + i][16 * a + k]; },
+          [&](int k, int j) { return Tl[16 * a + k][16 * wave + j]; });
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Tl[16 * a + li][16 * bc + 4 * r + g] = -t[r];
-    }
-  } else {
-    // the blocks below the diagonal of R and T are zero
-    for (int e = lane; e < 6 * 256; e += 64) {
-      const int blk = e >> 8, q = e & 255;
-      const int cb = blk < 3 ? 1 + blk : (blk < 5 ? 2 + (blk - 3) : 3);   // (1,0) (2,0) (3,0) (2,1) (3,1) (3,2)
-      const int db = blk < 3 ? 0 : (blk < 5 ? 1 : 2);
-      Rl[16 * cb + (q & 15)][16 * db + (q >> 4)] = 0.0;
-      Tl[16 * cb + (q & 15)][16 * db + (q >> 4)] = 0.0;
-    }
+    for (int r = 0; r < 4; ++r) Tl[16 * a + li][16 * wave + 4 * r + g] = -t[r];
+    __builtin_amdgcn_wave_barrier();
   }
+  for (int e = lane; e < 16 * 16 * wave; e += 64) Rl[16 * wave + (e & 15)][e >> 4] = 0.0;
   __syncthreads();
 }
 
@@ -1574,48 +1571,28 @@ void launch_tn_reduce_tmul(const TnArgs& a, const double* T, int w, double* out,
   hipLaunchKernelGGL(tn_reduce_tmul_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a, T, w, out, ldo, fb, P, ldp);
 }
 
-// C = T^T X with T (64 x 64, upper triangular, row-major LDS) and X (w x w,
-// column-major global, ld ldx, read straight from L2); C[i][j] (i, j < w) to
-// the column-major global matrix out (ld ldo).  Wave v computes rows
-// 16v..16v+15; (T^T)[i][k] = T[k][i] vanishes for k > i.
-__device__ __forceinline__ void tmul_global_store(int tid, const double (*Tl)[kLeaf + 1], const double* X,
-                                                  int64_t ldx, int w, double* out, int64_t ldo) {
+// acc = T^T X with T (64 x 64, upper triangular, row-major LDS): wave v forms
+// rows 16v..16v+15, acc[y][r] = (T^T X)[16v + li][16y + 4r + g].  (T^T)[i][k] =
+// T[k][i] vanishes for k > i.  X(k, j): X's entries.
+template <class FX>
+__device__ __forceinline__ void tmul(int tid, const double (*Tl)[kLeaf + 1], v4d (&acc)[4], FX X) {
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
-  v4d acc[4];
 #pragma unroll
   for (int y = 0; y < 4; ++y) acc[y] = v4d{0, 0, 0, 0};
-  // every k block the wave needs (k0 <= 16 wave) is requested before the
-  // first product, so the L2 round trips overlap
-  double xb[4][4][4];
+#pragma unroll 1
+  for (int c = 0; c <= wave; ++c) {
+    double xb[4][4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int y = 0; y < 4; ++y)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = 16 * c + 4 * g + s, j = 16 * y + li;
-        xb[c][y][s] = (c <= wave && k < w && j < w) ? X[k + (int64_t)j * ldx] : 0.0;
-      }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    if (c > wave) break;
+      for (int y = 0; y < 4; ++y) xb[s][y] = X(16 * c + 4 * g + s, 16 * y + li);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const int k = 16 * c + 4 * g + s;
-      const double xa = Tl[k][16 * wave + li];
+      const double xa = Tl[16 * c + 4 * g + s][16 * wave + li];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[y] = mfma(xb[c][y][s], xa, acc[y]);
+      for (int y = 0; y < 4; ++y) acc[y] = mfma(xb[s][y], xa, acc[y]);
     }
   }
-  const int i = 16 * wave + li;
-#pragma unroll
-  for (int y = 0; y < 4; ++y)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = 16 * y + 4 * r + g;
-      if (i < w && j < w) out[i + (int64_t)j * ldo] = acc[y][r];
-    }
 }
 
 // Breakdown fallback of the second pass: the column-wise CGS2 product
@@ -1636,163 +1613,472 @@ __device__ void colwise_product_store(double* P, int64_t ldp, int64_t mrows, int
 }
 
 // The second pass's breakdown fallback, kept out of line so that its loops
-// do not add to the registers of the Cholesky path: CGS2 of the panel into
-// Rl, and the next panel's coefficients P^T Q_next when Rbar is given.
-// Returns false for a zero column (exact rank deficiency).
-__device__ __attribute__((noinline)) bool chol_fallback(const CholArgs& a, double (*Rl)[kLeaf + 1],
+// do not add to the registers of the usual path: CGS2 of the panel into Rl,
+// the next panel's coefficients Rbar = P^T Q_next when Q_next is given, and
+// its update Q_next -= P Rbar, all by this workgroup.  Returns false for a
+// zero column (exact rank deficiency).
+__device__ __attribute__((noinline)) bool chol_fallback(const PanelArgs& a, double (*Rl)[kLeaf + 1],
                                                         ColwiseLds<256>* L) {
   const bool ok = colwise_panel<256>(a.P, a.ldp, a.mrows, a.w, Rl, *L);
-  if (a.X)
-    colwise_product_store<256>(a.P, a.ldp, a.mrows, a.w, a.P + (int64_t)a.w * a.ldp, a.ldp, a.w, a.Rbar, a.ldr,
-                               *L);
+  if (a.Qn) {
+    colwise_product_store<256>(a.P, a.ldp, a.mrows, a.w, a.Qn, a.ldp, a.w, a.Rbar, a.ldr, *L);
+    for (int jn = 0; jn < a.w; ++jn) {
+      if ((int)threadIdx.x < a.w) L->s2[threadIdx.x] = a.Rbar[threadIdx.x + (int64_t)jn * a.ldr];
+      __syncthreads();
+      for (int64_t r = threadIdx.x; r < a.mrows; r += 256) {
+        double x = a.Qn[r + jn * a.ldp];
+        for (int c = 0; c < a.w; ++c) x -= a.P[r + c * a.ldp] * L->s2[c];
+        a.Qn[r + jn * a.ldp] = x;
+      }
+      __syncthreads();
+    }
+  }
   return ok;
 }
 
-// The kernel body on caller-provided LDS (Rl, Tl: 64 x 65 each; prow: 16;
-// dg: 64; flags: 3 ints; L: the column-wise routine's reduction space, pass 2
-// only).  PASS1_ONLY drops the second-pass code.
-//
-// Breakdown (a Cholesky pivot at most kCholBreak times its diagonal entry):
-// on the first pass R1 = T1 = I are returned, so the transform leaves the
-// panel as it is, and the breakdown is flagged in info[1]; on the second pass
-// (flagged, or breaking down itself) the panel is orthogonalised column by
-// column by CGS2 in this workgroup, T = I is returned, R_panel = R_cgs2 R1,
-// the next panel's coefficients are computed from the finished panel
-// directly, the panel is marked in a.fb for the update that started from its
-// first pass, and info[2] counts the fallback.  Only a panel that is exactly
-// rank-deficient (a zero column after projection) sets info[0].
-template <bool PASS1_ONLY>
-__device__ __forceinline__ void chol_body(const CholArgs& a, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                          double* prow, double* dg, int* flags, ColwiseLds<256>* L) {
-  const int pass = PASS1_ONLY ? 1 : a.pass;
-  int& s_exact = flags[0];
-  int& s_bad = flags[1];
-  int& s_fb = flags[2];
-  const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6, w = a.w;
-  if (tid == 0) {
-    s_exact = (pass == 1);
-    s_bad = 0;
-    s_fb = pass == 2 ? a.info[1] : 0;
-  }
-  // W (w x w) into Rl, identity-padded: all loads issued first
-  {
-    double v[16];
+// W (w x w Gram matrix, ld ldw) into Rl, identity-padded, Tl the identity, dg
+// the diagonal; true if some entry is further than 1e-8 from the identity's.
+// flag: a word of LDS.
+__device__ __forceinline__ bool gram_load(int tid, const double* W, int64_t ldw, int w, double (*Rl)[kLeaf + 1],
+                                          double (*Tl)[kLeaf + 1], double* dg, int* flag) {
+  const int tx = tid & 63, ty = tid >> 6;
+  if (tid == 0) *flag = 0;
+  double v[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int k = ty + 4 * q;   // column
-      v[q] = (tx < w && k < w) ? a.W[tx + (int64_t)k * a.ldw] : (tx == k ? 1.0 : 0.0);
-    }
-    bool far = false;
+  for (int q = 0; q < 16; ++q) {
+    const int k = ty + 4 * q;   // column (outside W: entry (0, 0), not used)
+    const bool in = tx < w && k < w;
+    v[q] = W[in ? tx + (int64_t)k * ldw : 0];
+    v[q] = in ? v[q] : (tx == k ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  bool far = false;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int k = ty + 4 * q;
+    const double id = tx == k ? 1.0 : 0.0;
+    Rl[tx][k] = v[q];
+    Tl[tx][k] = id;
+    if (k == tx) dg[tx] = v[q];
+    far |= !(fabs(v[q] - id) <= 1e-8);
+  }
+  if (far) *flag = 1;
+  __syncthreads();
+  return *flag != 0;
+}
+
+// First Cholesky-QR pass by one workgroup: R1 <- chol(W), T <- R1^{-1} (both
+// left in Rl and Tl).  Breakdown (a pivot at most kCholBreak times its diagonal
+// entry): R1 = T = I, so the transform leaves the panel as it is, and info[1]
+// tells the second pass.  store: write R1 (and T, if a.T) and info[1].
+__device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
+                                           double* prow, double* dg, int* flag, bool store) {
+  const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6, w = a.w;
+  gram_load(tid, a.W, a.ldw, w, Rl, Tl, dg, flag);
+  __syncthreads();
+  if (tid == 0) *flag = 0;
+  bool bad = false;
+  chol_blocked(tid, (w + 15) / 16, Rl, Tl, prow, dg, bad);    // (barriers inside)
+  if (bad) *flag = 1;
+  __syncthreads();
+  const bool broke = *flag != 0;
+  if (broke) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int k = ty + 4 * q;
-      Rl[tx][k] = v[q];
-      if (k == tx) dg[tx] = v[q];
-      far |= !(fabs(v[q] - (tx == k ? 1.0 : 0.0)) <= 1e-8);
+      Rl[tx][k] = Tl[tx][k] = (tx == k) ? 1.0 : 0.0;
     }
     __syncthreads();
-    if (pass == 2 && far) s_exact = 1;
   }
-  __syncthreads();
-  if (s_fb) {
-    // the first pass broke down: nothing to factor here
-  } else if (s_exact) {
-    bool bad = false;
-    chol_blocked(tid, Rl, Tl, prow, dg, bad);
-    if (bad) s_bad = 1;
+  if (!store) return;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int k = ty + 4 * q;
+    if (tx < w && k < w) {
+      if (a.T) a.T[tx + k * w] = Tl[tx][k];
+      a.R1[tx + k * w] = Rl[tx][k];
+    }
+  }
+  if (tid == 0) a.info[1] = broke;
+}
+
+// The exact factorization in a second pass that needs it (rare): out of line,
+// so that its registers do not add to those of the usual path.
+__device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
+                                                     double* prow, const double* dg) {
+  bool bad = false;
+  chol_blocked(threadIdx.x, nb, Rl, Tl, prow, dg, bad);
+  return bad;
+}
+
+// First pass's transform, and the second pass's Gram product from the same
+// rows: a workgroup walks strips of 16 rows of the panel; each strip of
+// P (- the split partials of the re-projection update) is multiplied by
+// T = R1^{-1} on MFMA, stored to P (and X), and at once multiplied into
+// P1^T [P1 | Q_next], whose 64 x 64 blocks stay in registers until the
+// workgroup's last strip and are left as split partials (tile 0: Gram, tile 1:
+// Q_next) for tn_reduce_split_kernel.  The panel is thus read once for both,
+// and the Gram product has no launch of its own.  CHOL: the workgroup runs the
+// first pass's Cholesky itself (each of them the same: cheaper than a launch
+// of one workgroup before this one); otherwise T comes from memory (the
+// factorization ran beside the split update, nn_chol_kernel).
+// Latency-bound: 16-row strips let a short panel fill many workgroups.  FULL:
+// w = 64, no column masks; NEXT: with Q_next.
+template <bool CHOL, bool FULL, bool NEXT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void panel_first_kernel(PanelArgs a) {
+  __builtin_amdgcn_s_setprio(2);   // panel chain
+  __shared__ double sT[kLeaf][kLeaf + 1];
+  __shared__ double sR[CHOL ? kLeaf : 1][kLeaf + 1];
+  __shared__ double sP[16][kLeaf + 1];      // the strip before, then after the transform
+  __shared__ double sQ[NEXT ? 16 : 1][kLeaf + 1];   // Q_next's rows of the strip
+  __shared__ double prow[16];
+  __shared__ double dg[kLeaf];
+  __shared__ int flag;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int w = FULL ? kLeaf : a.w;
+  const int strips = (int)((a.mrows + 15) / 16);
+  // element u of this thread: row li of the strip, column 16 wave + 4 u + g
+  double pv[4], qv[4] = {0.0, 0.0, 0.0, 0.0};
+  // (rows and columns outside the panel read row or column 0 and count as zero)
+  auto load = [&](int s) {
+    const int64_t i = (int64_t)s * 16 + li, ic = i < a.mrows ? i : 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = 16 * wave + 4 * u + g;
+      const int64_t o = ic + (j < w ? j : 0) * a.ldp;
+      pv[u] = a.P[o];
+      if (NEXT) qv[u] = a.Qn[o];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool ok = i < a.mrows && 16 * wave + 4 * u + g < w;
+      pv[u] = ok ? pv[u] : 0.0;
+      qv[u] = NEXT && ok ? qv[u] : 0.0;
+    }
+  };
+  if ((int)blockIdx.x < strips) load(blockIdx.x);
+  if constexpr (CHOL) {
+    chol_first(a.c, sR, sT, prow, dg, &flag, blockIdx.x == 0);
   } else {
-    // W = I + E with |E| <= 1e-8: R = I + F, F = strict upper part of E plus
-    // half its diagonal; R^{-1} = I - F up to O(|E|^2), below rounding.
+    double tv[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = tid + 256 * q, k = e & 63, j = e >> 6;
+      tv[q] = (k < w && j < w) ? a.T[k + j * w] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int e = tid + 256 * q;
+      sT[e & 63][e >> 6] = tv[q];
+    }
+  }
+  const int ia0 = (wave & 1) * 32, jb0 = (wave >> 1) * 32;     // quadrant of the Gram blocks
+  v4d gg[2][2], gq[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) gg[x][y] = gq[x][y] = v4d{0, 0, 0, 0};
+  for (int s = blockIdx.x; s < strips; s += gridDim.x) {
+    if (a.nsplit > 1) {
+      double v[4];
+      sum_partials4<8>(a.part, a.nsplit, a.ntiles, s >> 2, s & 3, wave, lane, v);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int j = 16 * wave + 4 * u + g;
+        pv[u] = j < w && (int64_t)s * 16 + li < a.mrows ? pv[u] - v[u] : 0.0;
+      }
+    }
+    __syncthreads();          // T is staged; the previous strip's reads are done
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      sP[li][16 * wave + 4 * u + g] = pv[u];
+      if (NEXT) sQ[li][16 * wave + 4 * u + g] = qv[u];
+    }
+    __syncthreads();
+    if (s + (int)gridDim.x < strips) load(s + gridDim.x);
+    __builtin_amdgcn_sched_barrier(0);
+    v4d acc = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int k0 = 0; k0 < kLeaf; k0 += 16)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * g + e;
+        acc = mfma(sT[k][16 * wave + li], sP[li][k], acc);
+      }
+    __syncthreads();
+    const int64_t i = (int64_t)s * 16 + li;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = 16 * wave + 4 * r + g;
+      sP[li][j] = acc[r];
+      if (i < a.mrows && j < w) {
+        a.P[i + j * a.ldp] = acc[r];
+        if (a.X) a.X[i + j * a.ldx] = acc[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = 4 * g + e;
+      double xa[2], xb[2], xq[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        xa[t] = sP[k][ia0 + 16 * t + li];
+        xb[t] = sP[k][jb0 + 16 * t + li];
+        xq[t] = NEXT ? sQ[k][jb0 + 16 * t + li] : 0.0;
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          gg[x][y] = mfma(xb[y], xa[x], gg[x][y]);
+          if (NEXT) gq[x][y] = mfma(xq[y], xa[x], gq[x][y]);
+        }
+    }
+  }
+  const int tiles = NEXT ? 2 : 1;
+  double* mine = a.gpart + part_off(blockIdx.x, tiles, 0, wave) + lane;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int q = (x * 2 + y) * 4 + r;
+        mine[q * 64] = gg[x][y][r];
+        if (NEXT) mine[4096 + q * 64] = gq[x][y][r];
+      }
+}
+
+// Second Cholesky-QR pass from its Gram matrix G = P1^T P1 (and G_next = P1^T
+// Q_next): P <- P1 T with T = R2^{-1}, and Q_next -= P Rbar with Rbar = T^T
+// G_next, 64 rows at a time.  Every workgroup forms T itself: after a first
+// pass W = I + E with |E| <= 1e-8, so R2 = I + F (F the strict upper part of E
+// plus half its diagonal) and T = I - F up to O(|E|^2), below rounding; where
+// E is larger, the exact factorization runs, in each workgroup the same.  That
+// costs less than a launch of one workgroup that the transform has to wait for.
+// The last workgroup takes no rows: it stores R_panel = R2 R1, Rbar and the
+// copy of T for the early update.
+// Breakdown (flagged by the first pass, or a pivot here): the last workgroup
+// orthogonalises the panel column by column with CGS2 and updates Q_next, the
+// others leave it alone; R_panel = R_cgs2 R1, the panel is marked in a.fb for
+// the update that started from its first pass, and info[2] counts it.  Only a
+// panel that is exactly rank-deficient (a zero column after projection) sets
+// info[0].
+template <bool FULL, bool NEXT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void panel_second_kernel(PanelArgs a) {
+  __builtin_amdgcn_s_setprio(2);   // panel chain
+  __shared__ double sT[kLeaf][kLeaf + 1];
+  __shared__ double sB[kLeaf][kLeaf + 1];   // W and R2, then Rbar
+  __shared__ double prow[16];
+  __shared__ double dg[kLeaf];
+  __shared__ int flag, flag2;
+  __shared__ ColwiseLds<256> L;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int w = FULL ? kLeaf : a.w;
+  const int tx = lane, ty = wave;
+  const bool last = blockIdx.x + 1 == gridDim.x;
+  const int tiles = (int)((a.mrows + 63) / 64);
+  // rows i = 64 tile + 16 wave + li: columns 4 m + g of P, 16 y + 4 r + g of Q_next
+  // (outside the panel: row or column 0, meeting zeros of T, or not stored)
+  double xa[16], cv[16];
+  auto load = [&](double (&v)[16], const double* M, int tile) {
+    const int64_t i = (int64_t)tile * 64 + 16 * wave + li, ic = i < a.mrows ? i : 0;
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const int j = 4 * m + g;
+      v[m] = M[ic + (j < w ? j : 0) * a.ldp];
+    }
+  };
+  auto mask = [&](double (&v)[16]) {
+    if (!FULL) {
+#pragma unroll
+      for (int m = 0; m < 16; ++m) v[m] = 4 * m + g < w ? v[m] : 0.0;
+    }
+  };
+  const double* Gn = a.G + (int64_t)kLeaf * w;    // P1^T Q_next (ld w)
+  double xr[16];
+  if (!last) {
+    load(xa, a.P, blockIdx.x);
+    if (NEXT) {
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int k = ty + 4 * q;
+        const bool in = tx < w && k < w;
+        xr[q] = Gn[in ? tx + k * w : 0];
+        xr[q] = in ? xr[q] : 0.0;
+      }
+    }
+  }
+  const bool broke1 = a.c.info[1] != 0;
+  const bool far = gram_load(tid, a.G, w, w, sB, sT, dg, &flag);
+  if (tid == 0) flag2 = 0;
+  __syncthreads();
+  if (!far) {
     double f[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int i = ty + 4 * q;
-      f[q] = (i < tx) ? Rl[i][tx] : (i == tx ? 0.5 * (Rl[i][i] - 1.0) : 0.0);
+      const double e = sB[i][tx];
+      f[q] = (i < tx) ? e : (i == tx ? 0.5 * (e - 1.0) : 0.0);
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int i = ty + 4 * q;
       const double id = (i == tx) ? 1.0 : 0.0;
-      Rl[i][tx] = id + f[q];
-      Tl[i][tx] = id - f[q];
+      sB[i][tx] = id + f[q];
+      sT[i][tx] = id - f[q];
     }
+  } else if (!broke1) {
+    if (chol_exact((w + 15) / 16, sB, sT, prow, dg)) flag2 = 1;
   }
   __syncthreads();
-  bool rank_deficient = false;
-  if (pass == 1 && s_bad) {
-    // leave the panel as it is: R1 = T1 = I; the second pass takes over
+  const bool fallback = broke1 || flag2 != 0;
+  if (!last) {
+    if (fallback) return;
+    if (NEXT) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int k = ty + 4 * q;
-      Rl[tx][k] = Tl[tx][k] = (tx == k) ? 1.0 : 0.0;
-    }
-    if (tid == 0) a.info[1] = 1;
-    __syncthreads();
-  }
-  if constexpr (!PASS1_ONLY) {
-    if (pass == 2 && (s_fb || s_bad)) {
-      // column-wise CGS2 of the panel in place: R_cgs2 into Rl, T = I, and
-      // the next panel's coefficients from the finished panel
-      rank_deficient = !chol_fallback(a, Rl, L);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int k = ty + 4 * q;
-        Tl[tx][k] = (tx == k) ? 1.0 : 0.0;
-      }
-      if (tid == 0) {
-        a.info[1] = 0;
-        a.info[2] += 1;
-        if (a.fb) *a.fb = 1;
-      }
+      for (int q = 0; q < 16; ++q) sB[tx][ty + 4 * q] = xr[q];
       __syncthreads();
+      v4d rb[4];
+      tmul(tid, sT, rb, [&](int k, int j) { return sB[k][j]; });
+      __syncthreads();
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sB[16 * wave + li][16 * y + 4 * r + g] = rb[y][r];
     }
+    __syncthreads();
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x - 1) {
+      mask(xa);
+      if (NEXT) load(cv, a.Qn, tile);         // used after the products
+      __builtin_amdgcn_sched_barrier(0);
+      v4d pf[4], acc[4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) pf[y] = acc[y] = v4d{0, 0, 0, 0};
+#pragma unroll
+      for (int m = 0; m < 16; ++m)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) pf[y] = mfma(sT[4 * m + g][16 * y + li], xa[m], pf[y]);
+      if (tile + (int)gridDim.x - 1 < tiles) load(xa, a.P, tile + gridDim.x - 1);
+      // the accumulators hold P[i][4 m + g] for m = 4 y + r: the operand of the
+      // second product, lane for lane
+      if (NEXT) {
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) acc[y] = mfma(sB[4 * m + g][16 * y + li], pf[m >> 2][m & 3], acc[y]);
+      }
+      const int64_t i = (int64_t)tile * 64 + 16 * wave + li;
+      if (i < a.mrows) {
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int j = 16 * y + 4 * r + g;
+            if (FULL || j < w) {
+              a.P[i + j * a.ldp] = pf[y][r];
+              if (NEXT) a.Qn[i + j * a.ldp] = cv[4 * y + r] - acc[y][r];
+            }
+          }
+      }
+    }
+    return;
   }
-  // T (and R1 on the first pass) to global, column-major w x w
+  // the last workgroup: R1 for R_panel = R2 R1, Rbar, T's copy
+  double r1v[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int k = ty + 4 * q;
-    if (tx < w && k < w) {
-      a.T[tx + k * w] = Tl[tx][k];
-      if (pass == 1) a.R1[tx + k * w] = Rl[tx][k];
-      if (pass == 2 && a.Tcopy) a.Tcopy[tx + k * w] = Tl[tx][k];
-    }
+    r1v[q] = (tx < w && k < w) ? a.c.R1[tx + k * w] : (tx == k ? 1.0 : 0.0);
   }
-  if constexpr (!PASS1_ONLY) {
-    if (pass == 2) {
-      // R1 for R_panel = R2 R1, requested before T^T X so both loads overlap
-      double r1v[16];
+  bool rank_deficient = false;
+  if (fallback) {
+    rank_deficient = !chol_fallback(a, sB, &L);
+    if (tid == 0) {
+      a.c.info[2] += 1;
+      if (a.fb) *a.fb = 1;
+    }
+    __syncthreads();
+  } else {
+    if (a.Tcopy) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int k = ty + 4 * q;
-        r1v[q] = (tx < w && k < w) ? a.R1[tx + k * w] : (tx == k ? 1.0 : 0.0);
+        if (tx < w && k < w) a.Tcopy[tx + k * w] = sT[tx][k];
       }
-      // the next panel's update coefficients: (P1 T)^T Q_next = T^T X (after a
-      // fallback they were formed from the finished panel itself)
-      if (a.X && !(s_fb || s_bad)) tmul_global_store(tid, Tl, a.X, a.ldx, w, a.Rbar, a.ldr);
-      // R_panel = R2 R1 with R1 staged in Tl (T is stored)
-      __syncthreads();
+    }
+    if (NEXT) {
+      v4d rb[4];
+      tmul(tid, sT, rb, [&](int k, int j) { return k < w && j < w ? Gn[k + j * w] : 0.0; });
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int k = ty + 4 * q;
-        Tl[tx][k] = r1v[q];
-      }
-      __syncthreads();
-      lds_mm_store<false, true>(tid, Rl, Tl, w, w, a.Rout, a.ldr);
+      for (int y = 0; y < 4; ++y)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * wave + li, j = 16 * y + 4 * r + g;
+          if (i < w && j < w) a.Rbar[i + (int64_t)j * a.ldr] = rb[y][r];
+        }
     }
   }
-  if (tid == 0 && rank_deficient && a.info[0] == 0) a.info[0] = 1 + a.panel;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) sT[tx][ty + 4 * q] = r1v[q];
+  __syncthreads();
+  lds_mm_store<false, true>(tid, sB, sT, w, w, a.Rout, a.ldr);
+  if (tid == 0 && rank_deficient && a.c.info[0] == 0) a.c.info[0] = 1 + a.c.panel;
 }
 
-__global__ __launch_bounds__(256) void chol_kernel(CholArgs a) {
-  __builtin_amdgcn_s_setprio(2);   // the panel chain sets the pace of the factorization
-  __shared__ double Rl[kLeaf][kLeaf + 1];
-  __shared__ double Tl[kLeaf][kLeaf + 1];
-  __shared__ double prow[16];
-  __shared__ double dg[kLeaf];
-  __shared__ int flags[3];
-  __shared__ ColwiseLds<256> L;
-  chol_body<false>(a, Rl, Tl, prow, dg, flags, &L);
+// Workgroups of the first pass: strips of 16 rows shared evenly by at most 128
+// of them (their partial Gram blocks, 64 KB each with Q_next, are written and
+// read back), 256 for panels of more than 32768 rows, where the rows' own bytes
+// outweigh the partials'.
+int panel_first_blocks(int64_t mrows) {
+  const int64_t strips = (mrows + 15) / 16, cap = mrows > 32768 ? 256 : 128;
+  const int64_t per = (strips + cap - 1) / cap;
+  return (int)((strips + per - 1) / per);
+}
+
+void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st) {
+  const dim3 grid((unsigned)panel_first_blocks(a.mrows));
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
+  const bool full = a.w == kLeaf, next = a.Qn != nullptr;
+  switch ((chol ? 4 : 0) | (full ? 2 : 0) | (next ? 1 : 0)) {
+    case 0: go(panel_first_kernel<false, false, false>); break;
+    case 1: go(panel_first_kernel<false, false, true>); break;
+    case 2: go(panel_first_kernel<false, true, false>); break;
+    case 3: go(panel_first_kernel<false, true, true>); break;
+    case 4: go(panel_first_kernel<true, false, false>); break;
+    case 5: go(panel_first_kernel<true, false, true>); break;
+    case 6: go(panel_first_kernel<true, true, false>); break;
+    default: go(panel_first_kernel<true, true, true>); break;
+  }
+}
+
+// The Gram partials of launch_panel_first summed into G (ld w; G_next from
+// column kLeaf on).
+void launch_panel_reduce(const PanelArgs& a, hipStream_t st) {
+  TnArgs t{};
+  t.M = t.M2 = a.w; t.N = a.Qn ? kLeaf + a.w : a.w;
+  t.nsplit = panel_first_blocks(a.mrows);
+  t.tilesN = t.ntiles = a.Qn ? 2 : 1;
+  t.C = a.G; t.ldc = a.w;
+  t.part = a.gpart;
+  t.prio = 1;
+  launch_tn_sum(t, st);
+}
+
+void launch_panel_second(const PanelArgs& a, hipStream_t st) {
+  const int64_t tiles = (a.mrows + 63) / 64;
+  const int64_t per = (tiles + 254) / 255;
+  const dim3 grid((unsigned)((tiles + per - 1) / per + 1));
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
+  const bool next = a.Qn != nullptr;
+  if (a.w == kLeaf) {
+    if (next) go(panel_second_kernel<true, true>); else go(panel_second_kernel<true, false>);
+  } else {
+    if (next) go(panel_second_kernel<false, true>); else go(panel_second_kernel<false, false>);
+  }
 }
 
 // A panel leaf orthogonalised column by column (the CGS2, ICGS and MGS panel
@@ -2110,89 +2396,12 @@ void launch_colpanel(const ColArgs& a, hipStream_t st) {
   go(colgrid_kernel<CG_FINISH>, a.w - 1);
 }
 
-CholArgs chol_args(const double* W, int64_t ldw, int w, int pass, double* Rout, int64_t ldr, const double* X,
-                   int64_t ldx, double* Rbar, int panel, const Scratch& s) {
+CholArgs chol_args(const double* W, int64_t ldw, int w, int panel, const Scratch& s) {
   CholArgs c{};
   c.W = W; c.ldw = ldw;
-  c.w = w; c.pass = pass; c.panel = panel;
-  c.T = s.T; c.R1 = s.R1; c.Rout = Rout; c.ldr = ldr; c.info = s.info;
-  c.X = X; c.ldx = ldx; c.Rbar = Rbar;
-  c.Tcopy = nullptr;
-  c.P = nullptr; c.ldp = 0; c.mrows = 0;
-  c.fb = nullptr;
+  c.w = w; c.panel = panel;
+  c.T = s.T; c.R1 = s.R1; c.info = s.info;
   return c;
-}
-
-void launch_chol(const double* W, int64_t ldw, int w, int pass, double* Rout, int64_t ldr, const double* X,
-                 int64_t ldx, double* Rbar, int panel, const Scratch& s, hipStream_t st, double* Tcopy, double* P,
-                 int64_t ldp, int64_t mrows, int* fb) {
-  CholArgs c = chol_args(W, ldw, w, pass, Rout, ldr, X, ldx, Rbar, panel, s);
-  c.Tcopy = Tcopy;
-  c.P = P; c.ldp = ldp; c.mrows = mrows;
-  c.fb = fb;
-  hipLaunchKernelGGL(chol_kernel, dim3(1), dim3(256), 0, st, c);
-}
-
-// --------------------------------------------------------------------------
-// In-place panel transform P <- P T (T upper triangular, w <= 64 columns).
-// Each block stages 64 rows of P in LDS, then 4 waves (16 rows each) form
-// the product with MFMA.
-// --------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void apply_kernel(double* P, int64_t ldp, int64_t mrows, int w,
-                                                    const double* T) {
-  __builtin_amdgcn_s_setprio(2);   // panel chain
-  __shared__ double tileP[kLeaf][64 + 1];   // [col][row]
-  __shared__ double tileT[kLeaf][kLeaf + 1];   // [k][j]
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-  {
-    // every load of the block in flight at once: 16 of P and 16 of T per thread
-    const int64_t row = r0 + tx;
-    const bool rok = row < mrows;
-    double vp[16], vt[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int c = ty + 4 * q;
-      vp[q] = (rok && c < w) ? P[row + (int64_t)c * ldp] : 0.0;
-      vt[q] = (tx < w && c < w) ? T[tx + c * w] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int c = ty + 4 * q;
-      tileP[c][tx] = vp[q];
-      tileT[tx][c] = vt[q];
-    }
-  }
-  __syncthreads();
-  const int wave = ty, lane = tx, li = lane & 15, g = lane >> 4;
-  const int rl = wave * 16 + li;
-  v4d acc[4];
-#pragma unroll
-  for (int y = 0; y < 4; ++y) acc[y] = v4d{0, 0, 0, 0};
-#pragma unroll 4
-  for (int k0 = 0; k0 < kLeaf; k0 += 16) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int k = k0 + 4 * g + s;
-      const double xa = tileP[k][rl];
-#pragma unroll
-      for (int y = 0; y < 4; ++y) acc[y] = mfma(tileT[k][16 * y + li], xa, acc[y]);
-    }
-  }
-  const int64_t row = r0 + rl;
-  if (row >= mrows) return;
-#pragma unroll
-  for (int y = 0; y < 4; ++y)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = 16 * y + 4 * r + g;
-      if (j < w) P[row + (int64_t)j * ldp] = acc[y][r];
-    }
-}
-
-void launch_apply(double* P, int64_t ldp, int64_t mrows, int w, const Scratch& s, hipStream_t st) {
-  const int blocks = (int)((mrows + 63) / 64);
-  hipLaunchKernelGGL(apply_kernel, dim3(blocks), dim3(256), 0, st, P, ldp, mrows, w, (const double*)s.T);
 }
 
 // --------------------------------------------------------------------------
@@ -2359,74 +2568,6 @@ __global__ __launch_bounds__(256) void nn1_kernel(NnArgs a) {
   }
 }
 
-// The second pass's panel transform and the lookahead update in one launch:
-// P <- P1 T (T: w x w upper triangular, w = K <= 64), then C -= P B.  Each
-// block owns 64 rows of P and of C.  A lane's accumulators of the first
-// product hold P[i][4m + g] for m = 4y + r, which is exactly the operand the
-// lane supplies to the second product, so the transformed strip never leaves
-// the registers; it is also stored to P (the panel's final columns).
-__global__ __launch_bounds__(256) void nn1_apply_kernel(NnArgs a, const double* T, int w) {
-  __builtin_amdgcn_s_setprio(2);   // panel chain
-  __shared__ double sT[NK][64 + 1];
-  __shared__ double sB[NK][64 + 1];
-  const NnTile t = nn_tile(a, blockIdx.x);
-  double cval[16], xa[16], tv[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int j = t.jb + 16 * (e >> 2) + colsub(e & 3, t.g, false);
-    cval[e] = a.C[t.ic + (int64_t)(j < a.N ? j : 0) * a.ldc];
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = t.tid + 256 * q, k = e & 63, j = e >> 6;
-    tv[q] = (k < w && j < w) ? T[k + j * w] : 0.0;
-  }
-  // A = P1 (zero past K) in registers, the B slab into LDS
-  if (a.K == NK && a.vec) {
-    v2d rb[8];
-    nn_load_a(a, t, 0, xa);
-    nn_load_b(t, 0, rb);
-    __builtin_amdgcn_sched_barrier(0);
-    nn_put_b(sB, t, rb);
-  } else {
-    nn_load_tail(a, t, 0, a.K, xa, sB);
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = t.tid + 256 * q;
-    sT[e & 63][e >> 6] = tv[q];
-  }
-  __syncthreads();
-  v4d pf[4];
-#pragma unroll
-  for (int y = 0; y < 4; ++y) pf[y] = v4d{0, 0, 0, 0};
-  nn_mma(pf, sT, t, xa);
-#pragma unroll
-  for (int y = 0; y < 4; ++y)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) xa[4 * y + r] = pf[y][r];
-  v4d acc[4];
-#pragma unroll
-  for (int y = 0; y < 4; ++y) acc[y] = v4d{0, 0, 0, 0};
-  nn_mma(acc, sB, t, xa);
-  if (!t.aok) return;
-  double* P = const_cast<double*>(a.A);
-#pragma unroll
-  for (int y = 0; y < 4; ++y)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = 16 * y + 4 * r + t.g;
-      if (j < w) P[t.i + (int64_t)j * a.lda] = pf[y][r];
-      if (j < a.N) a.C[t.i + (int64_t)j * a.ldc] = cval[y * 4 + r] - acc[y][r];
-    }
-}
-
-bool launch_nn1_apply(const NnArgs& a, const double* T, int w, hipStream_t st) {
-  if (a.M <= 0 || a.N <= 0 || a.K != w || w > NK || a.tilesN != 1) return false;
-  hipLaunchKernelGGL(nn1_apply_kernel, dim3(a.ntiles), dim3(256), 0, st, a, T, w);
-  return true;
-}
-
 // Long K: slabs of 64 with the next slab's A and B loads in flight while the
 // current slab is multiplied (A register sets alternate explicitly).  SPLIT:
 // the block's K range is one split and its partial tile is stored for
@@ -2524,18 +2665,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 // instead of after them on the panel chain.  Block column x = ntiles holds the
 // Cholesky (its y > 0 blocks exit at once); both uses share the LDS layout
 // size (two 64 x 65 double arrays).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void nn_chol_kernel(NnArgs a,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void nn_chol_kernel(NnArgs a,
                                                                                                CholArgs c) {
   __builtin_amdgcn_s_setprio(2);
   __shared__ double smem[2 * NK * (64 + 1)];
   __shared__ double prow[16];
   __shared__ double dg[kLeaf];
-  __shared__ int flags[3];
+  __shared__ int flag;
   if ((int)blockIdx.x == a.ntiles) {
     if (blockIdx.y == 0)
-      chol_body<true>(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
-                      reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), prow, dg, flags,
-                      nullptr);
+      chol_first(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
+                 reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), prow, dg, &flag, true);
     return;
   }
   nn_body<true, TAG_REPROJ>(a, reinterpret_cast<double (*)[NK][64 + 1]>(smem), blockIdx.x, blockIdx.y);
@@ -2566,70 +2706,6 @@ __global__ __launch_bounds__(256) void nn_reduce_kernel(NnArgs a) {
     const int j = jq + colsub(u, g, false);
     if (j < a.N) a.C[i + (int64_t)j * a.ldc] = old[u] - v[u];
   }
-}
-
-// The split reduction of a panel update (N = w <= 64 columns) followed by
-// the panel transform P <- P T (T: w x w, upper triangular): each block's 16 x
-// 64 strip of C - sum(partials) is staged in LDS and multiplied by T on MFMA
-// (wave q forms output columns 16q .. 16q + 15) before it is stored, so the
-// transform needs no launch or pass over P of its own.
-__global__ __launch_bounds__(256) void nn_reduce_apply_kernel(NnArgs a, const double* T, int w, double* X,
-                                                              int64_t ldx) {
-  __builtin_amdgcn_s_setprio(2);   // panel chain
-  __shared__ double sP[16][64 + 1];
-  __shared__ double sT[64][64 + 1];
-  const int tile = blockIdx.x >> 2, wave = blockIdx.x & 3;
-  const int qg = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
-  const int64_t i = (int64_t)tile * 64 + wave * 16 + li;
-  const bool aok = i < a.M;
-  const int64_t ic = aok ? i : 0;
-  double old[4], tv[16];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = 16 * qg + colsub(u, g, false);
-    old[u] = a.C[ic + (int64_t)(j < a.N ? j : 0) * a.ldc];
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = threadIdx.x + 256 * q, k = e & 63, j = e >> 6;
-    tv[q] = (k < w && j < w) ? T[k + j * w] : 0.0;
-  }
-  double v[4];
-  sum_partials4(a.part, a.nsplit, a.ntiles, tile, wave, qg, lane, v);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = 16 * qg + colsub(u, g, false);
-    sP[li][j] = j < w ? old[u] - v[u] : 0.0;   // columns past w hold clamped loads
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    sT[e & 63][e >> 6] = tv[q];
-  }
-  __syncthreads();
-  v4d acc = v4d{0, 0, 0, 0};
-#pragma unroll
-  for (int k0 = 0; k0 < 64; k0 += 16)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int k = k0 + 4 * g + s;
-      acc = mfma(sT[k][16 * qg + li], sP[li][k], acc);
-    }
-  if (!aok) return;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = 16 * qg + 4 * r + g;
-    if (j < w) {
-      a.C[i + (int64_t)j * a.ldc] = acc[r];
-      if (X) X[i + (int64_t)j * ldx] = acc[r];
-    }
-  }
-}
-
-bool launch_nn_reduce_apply(const NnArgs& a, const double* T, int w, double* X, int64_t ldx, hipStream_t st) {
-  if (a.M <= 0 || a.nsplit <= 1 || a.tilesN != 1 || a.N != w || w > kLeaf) return false;
-  hipLaunchKernelGGL(nn_reduce_apply_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a, T, w, X, ldx);
-  return true;
 }
 
 NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M,

@@ -74,13 +74,13 @@ struct FoldArgs {
 // Scratch regions inside the caller's workspace (all device pointers).
 struct Scratch {
   int* info;          // [0]: 0, or 1 + the first panel that is exactly rank-deficient;
-                      // [1]: first Cholesky pass of the current leaf broke down;
+                      // [1]: whether the current leaf's first Cholesky pass broke down;
                       // [2]: leaves orthogonalised by the column-wise fallback
   int* fb;            // per panel: 1 if its second pass took the column-wise fallback
   double* part;       // split-K partial tiles
   int64_t npart;      // capacity in tiles (of kTile*kTile doubles)
   double* S;          // projection coefficients (and the fused first-pass Gram)
-  double* G;          // second-pass Gram and lookahead product (kLeaf x 2 kLeaf)
+  double* G;          // Gram matrix and lookahead product (kLeaf x 2 kLeaf)
   double* T;          // inverse Cholesky factor (kLeaf x kLeaf)
   double* R1;         // first-pass Cholesky factor (kLeaf x kLeaf)
   double* X;          // two first-pass panel copies (ldx x b each, xstride doubles apart)
@@ -166,18 +166,34 @@ void launch_nn_product(const NnArgs& a, int tag, hipStream_t st);
 void launch_nn_reduce(const NnArgs& a, hipStream_t st);   // nsplit > 1 only
 bool launch_nn_adj(const NnArgs& a, hipStream_t st);
 
-// Arguments of the panel Cholesky kernel (Gram matrix W in, T = R^{-1} and R1
-// to scratch, on the second pass R2 R1 to Rout and T^T X to Rbar).
+// First Cholesky-QR pass: R1 = chol(W) and T = R1^{-1} (w x w, ld w).
 struct CholArgs {
   const double* W; int64_t ldw;     // w x w Gram matrix
-  int w, pass, panel;
-  double* T; double* R1; double* Rout; int64_t ldr; int* info;
-  const double* X; int64_t ldx;     // pass 2, optional: w x w product P1^T Q_next
-  double* Rbar;                     // T^T X (ld ldr)
-  double* Tcopy;                    // pass 2, optional: second destination of T (w x w, ld w)
-  double* P; int64_t ldp; int64_t mrows;   // pass 2: the panel (for the column-wise fallback)
-  int* fb;                          // pass 2, optional: set to 1 when the fallback ran
+  int w, panel;
+  double* T; double* R1; int* info;
 };
+
+// A panel leaf P (mrows x w, w <= kLeaf) in its two Cholesky-QR passes
+// (panel_first_kernel, the sum of its Gram partials, panel_second_kernel).
+struct PanelArgs {
+  double* P; int64_t ldp; int64_t mrows; int w;
+  double* Qn;                       // the next panel (w columns, ld ldp), or nullptr
+  // first pass: P <- (P - sum of the split partials) T
+  const double* part; int nsplit, ntiles;
+  const double* T;                  // or formed from c.W by the kernel itself
+  CholArgs c;
+  double* X; int64_t ldx;           // second destination of the first pass's panel (or nullptr)
+  double* gpart;                    // Gram partials (panel_first_blocks x 2 tiles)
+  double* G;                        // P1^T P1 (ld w) and, from column kLeaf on, P1^T Q_next
+  // second pass
+  double* Rout; double* Rbar; int64_t ldr;   // R_panel = R2 R1; the next panel's coefficients
+  double* Tcopy;                    // copy of R2^{-1} (w x w, ld w), or nullptr
+  int* fb;                          // set to 1 when the column-wise fallback ran (or nullptr)
+};
+int panel_first_blocks(int64_t mrows);
+void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st);
+void launch_panel_reduce(const PanelArgs& a, hipStream_t st);
+void launch_panel_second(const PanelArgs& a, hipStream_t st);
 
 // One panel leaf orthogonalised column by column (colgrid_kernel): the rows
 // are split over up to kColGridMax workgroups, and each launch takes one step
@@ -198,40 +214,12 @@ struct ColArgs {
 };
 void launch_colpanel(const ColArgs& a, hipStream_t st);
 
-CholArgs chol_args(const double* W, int64_t ldw, int w, int pass, double* Rout, int64_t ldr, const double* X,
-                   int64_t ldx, double* Rbar, int panel, const Scratch& s);
-
-// Upper Cholesky factor of the panel Gram matrix W (w x w, ld ldw, w <= kLeaf).
-// pass 1: R1 <- chol(W), T <- R1^{-1}.  pass 2: R2 <- chol(W), T <- R2^{-1},
-// Rout (ldr) <- R2 R1, and, if X != nullptr, Rbar (ldr) <- T^T X (X: w x w,
-// ld ldx).  On the second pass T is also stored to Tcopy when it is not
-// nullptr.
-// Breakdown (a pivot at most 1e-14 times its diagonal entry): pass 1 returns
-// R1 = T = I and flags info[1]; pass 2 (flagged or breaking down) then
-// orthogonalises the panel P (mrows x w, ld ldp) column by column with CGS2,
-// returns T = I, Rout = R_cgs2 R1, Rbar = P^T Q_next from the finished panel
-// (Q_next: the w columns after P), sets *fb (if given) and counts the
-// fallback in info[2]; a zero column after projection sets info[0].
-void launch_chol(const double* W, int64_t ldw, int w, int pass, double* Rout, int64_t ldr, const double* X,
-                 int64_t ldx, double* Rbar, int panel, const Scratch& s, hipStream_t st, double* Tcopy = nullptr,
-                 double* P = nullptr, int64_t ldp = 0, int64_t mrows = 0, int* fb = nullptr);
+CholArgs chol_args(const double* W, int64_t ldw, int w, int panel, const Scratch& s);
 
 // The split re-projection update (launch_nn_product with nsplit > 1) with the
 // first Cholesky pass described by c run by one extra block of the same
 // launch; returns false, launching nothing, when the update does not split.
 bool launch_nn_chol(const NnArgs& a, const CholArgs& c, hipStream_t st);
-// The split reduction of a panel update (a.N = w <= 64 columns, one column
-// tile) fused with the panel transform C <- C T (T: w x w, ld w); the result
-// is also stored to X (ld ldx) when X != nullptr.  False, launching nothing,
-// for any other shape.
-bool launch_nn_reduce_apply(const NnArgs& a, const double* T, int w, double* X, int64_t ldx, hipStream_t st);
-// The panel transform A <- A T (A: M x w, the update's left operand; T: w x w,
-// ld w) and the rank-w update C -= A B in one launch (K = w <= 64, one column
-// tile, FP64); false, launching nothing, for any other shape.
-bool launch_nn1_apply(const NnArgs& a, const double* T, int w, hipStream_t st);
-
-// P <- P T in place (T = s.T, w x w upper triangular), P is mrows x w.
-void launch_apply(double* P, int64_t ldp, int64_t mrows, int w, const Scratch& s, hipStream_t st);
 
 void launch_zero_ints(int* p, int n, hipStream_t st);
 void launch_fill_zero(double* p, int64_t ld, int64_t rows, int64_t cols, hipStream_t st);
