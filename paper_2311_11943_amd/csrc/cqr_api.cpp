@@ -25,6 +25,7 @@ using cqr::kTile;
 struct cqr_plan_s {
   cqr_config cfg;
   int64_t bs, bw, hr, mp, N;
+  int64_t pw = 0;          // columns factored at once (inner_width)
   // no horizontal code (K_h = 0, K_v > 0): R carries K_v checksum block rows
   // of the vertical code below its n rows, so R has rrows rows
   bool rcode = false;
@@ -107,6 +108,38 @@ bool invert(std::vector<double> a, int n, std::vector<double>& inv) {
     }
   }
   return true;
+}
+
+// Columns a factorization takes at once.  The panel width b of the
+// configuration sets the boundaries at which calls may be split and failures
+// strike; between them, with re-projection every division of the columns gives
+// the same factors up to rounding, so the width follows what runs fastest, for b
+// a multiple of 64: single leaves (64) while the encoded matrix is at most 1 GiB,
+// where their short chain beats the wide panels' better products (n = 8192: 77 ms
+// against 93 with 128 columns and 82 with 256; n = 4096: 12.9 against 16.4 and
+// 19.8); about 512 columns up to 2.5 GiB (n = 12288: 209 ms, 250 with leaves, 215
+// with 256), 1024 beyond (n = 16384: 461 ms, 483 with 512, 536 with 256, 577 with
+// 128).  Without re-projection, in the column-wise modes and in reduced precision
+// (whose coefficients depend on the division) it is b.  This is the largest
+// width of the factorization; panel_width() narrows it towards the last columns.
+int64_t inner_width(const cqr_plan_s& p) {
+  const cqr_config& c = p.cfg;
+  if (c.panel != CQR_PANEL_CHOLQR2 || c.precision != CQR_FP64 || !c.reproject || !c.lookahead || c.b % kLeaf)
+    return c.b;
+  const int64_t bytes = 8 * p.mp * p.N;
+  if (bytes <= (int64_t)1 << 30) return kLeaf;
+  const int64_t target = bytes <= (int64_t)5 << 29 ? 512 : 1024;
+  return std::max<int64_t>(c.b, target / c.b * c.b);
+}
+
+// Width of the panel that starts at column c.  What a re-projection leaves of a
+// panel's components along earlier columns (rounding of the columns' norms)
+// grows relatively as the columns lose their components along the panel's own
+// first ones, by about sqrt((m - c) / (m - c - width)): a panel wider than b
+// takes at most an eighth of the dimensions left, which keeps that below 1.07.
+int64_t panel_width(const cqr_plan_s& p, int64_t c) {
+  if (p.pw <= p.cfg.b) return p.pw;
+  return std::max<int64_t>(p.cfg.b, std::min(p.pw, (p.cfg.m - c) / 8 / p.cfg.b * p.cfg.b));
 }
 
 // Blocks a failed node holds.  Q blocks are (I, J) on the (p_r+K_v) x (p_c+K_h)
@@ -332,6 +365,14 @@ int tag_of(int phase) {
 // the update stream's kernels, the chain sets the pace of the factorization.
 int chain_phase(int phase) { return phase != PH_TRAIL_TN && phase != PH_TRAIL_NN; }
 
+// Smallest encoded matrix whose panels are updated in pairs: smaller ones stay
+// in the 256 MB cache before HBM, and the pairs' extra launches cost more than
+// the bytes they save (5120 x 2560: 7.06 ms in pairs, 6.65 without; 5120 x 5120:
+// 12.9 against 13.3).
+constexpr int64_t kPairBytes = (int64_t)160 << 20;
+// Panels after a pair that take each of its panels' updates by itself.
+constexpr int kPairNear = 4;
+
 // First tile of the Gram partials in the split-partial area: the split
 // re-projection update, whose partials are read by the launch that writes the
 // Gram partials, takes at most 512 tiles (nn_setup), the Gram partials at most
@@ -346,6 +387,7 @@ void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B,
   if (M <= 0 || N <= 0) return;
   cqr::TnArgs a = cqr::tn_setup(A, lda, B, ldb, M, N, K, C, ldc, C2, ldc2, s, 0, lowp);
   if (M2 >= 0) a.M2 = M2;
+  a.seq = p.cfg.precision != CQR_FP64;
   a.prio = chain_phase(phase);
   const double fl = 2.0 * M * N * (double)K, by = 8.0 * ((double)K * M + (double)K * N);
   const double out = 8.0 * (double)M * N * (C2 ? 3.0 : 1.0);
@@ -474,20 +516,30 @@ cqr::PanelArgs panel_args(cqr_plan_s& p, double* P, int64_t ldq, int w, double* 
   a.T = s.T;
   a.c = cqr::chol_args(W, ldw, w, panel, s);
   // the split partials end before the Gram partials begin
-  a.gpart = s.part + (int64_t)kGramPartTile * kTile * kTile;
+  a.gpart = p.cfg.precision == CQR_FP64 ? s.part + (int64_t)kGramPartTile * kTile * kTile : nullptr;
   a.G = s.G;
+  a.Gn = s.G + (a.gpart ? kLeaf : w) * w;
   a.Rout = R + c + c * ldr;
   a.Rbar = R + c + (c + w) * ldr;
   a.ldr = ldr;
   return a;
 }
 
-void panel_first(cqr_plan_s& p, const cqr::PanelArgs& a, bool chol, hipStream_t st) {
-  const double m = (double)p.mp, w = a.w, nx = a.Qn ? 2.0 : 1.0, sp = a.nsplit > 1 ? a.nsplit : 0.0;
-  const double pb = partial_bytes(cqr::panel_first_blocks(p.mp), a.Qn ? 2 : 1);
+// (In reduced precision the Gram product runs by itself, in the order of sums
+// it has always had: the coefficients are rounded from the column state, so a
+// rounding-level change of a panel moves them by an FP32 rounding here and there
+// and the R blocks decoded from unfinished columns by some 1e-9, more than any
+// FP64 result moves.)
+void panel_first(cqr_plan_s& p, const cqr::PanelArgs& a, bool chol, const cqr::Scratch& s, hipStream_t st) {
+  const bool gram = a.gpart != nullptr;
+  const double m = (double)p.mp, w = a.w, nx = gram ? (a.Qn ? 2.0 : 1.0) : 0.0, sp = a.nsplit > 1 ? a.nsplit : 0.0;
+  const double pb = gram ? partial_bytes(cqr::panel_first_blocks(p.mp, true), a.Qn ? 2 : 1) : 0.0;
   prof(p, PH_APPLY, (2.0 + 2.0 * nx) * m * w * w + sp * m * w, 8.0 * m * w * (1.0 + nx + sp + (a.X ? 1.0 : 0.0)) + pb,
        st, [&] { cqr::launch_panel_first(a, chol, st); });
-  prof(p, PH_REDUCE, pb / 8.0, pb, st, [&] { cqr::launch_panel_reduce(a, st); });
+  if (gram)
+    prof(p, PH_REDUCE, pb / 8.0, pb, st, [&] { cqr::launch_panel_reduce(a, st); });
+  else
+    tn(p, PH_GRAM, a.P, a.ldp, a.P, a.ldp, a.w, a.Qn ? 2 * a.w : a.w, p.mp, a.G, a.w, nullptr, 0, s, st);
 }
 
 void panel_second(cqr_plan_s& p, const cqr::PanelArgs& a, hipStream_t st) {
@@ -500,9 +552,10 @@ void panel_second(cqr_plan_s& p, const cqr::PanelArgs& a, hipStream_t st) {
 // ICGS and MGS panel modes); wider panels are split, the right part projected
 // (twice) against the left part before being factored.
 void factor_panel(cqr_plan_s& p, double* Q, int64_t ldq, double* R, int64_t ldr, int64_t c, int w,
-                  int panel, const cqr::Scratch& s, hipStream_t st) {
+                  const cqr::Scratch& s, hipStream_t st) {
   const int64_t mp = p.mp;
   if (w <= kLeaf) {
+    const int panel = (int)(c / p.cfg.b);   // in the configuration's numbering
     double* P = Q + c * ldq;
     if (p.cfg.panel != CQR_PANEL_CHOLQR2) {
       colpanel(p, P, ldq, w, R + c + c * ldr, ldr, panel, s, st);
@@ -510,19 +563,19 @@ void factor_panel(cqr_plan_s& p, double* Q, int64_t ldq, double* R, int64_t ldr,
     }
     tn(p, PH_GRAM, P, ldq, P, ldq, w, w, p.mp, s.G, w, nullptr, 0, s, st);
     const cqr::PanelArgs a = panel_args(p, P, ldq, w, nullptr, s.G, w, nullptr, R, ldr, c, panel, s);
-    panel_first(p, a, true, st);
+    panel_first(p, a, true, s, st);
     panel_second(p, a, st);
     return;
   }
   int h = (w / 2 + 15) / 16 * 16;
   if (h >= w) h = w / 2;
-  factor_panel(p, Q, ldq, R, ldr, c, h, panel, s, st);
+  factor_panel(p, Q, ldq, R, ldr, c, h, s, st);
   for (int pass = 0; pass < 2; ++pass) {
     tn(p, PH_INPANEL, Q + c * ldq, ldq, Q + (c + h) * ldq, ldq, h, w - h, mp, s.S, h, R + c + (c + h) * ldr,
        ldr, s, st);
     nn(p, PH_INPANEL, Q + (c + h) * ldq, ldq, Q + c * ldq, ldq, s.S, h, mp, w - h, h, s, st);
   }
-  factor_panel(p, Q, ldq, R, ldr, c + h, w - h, panel, s, st);
+  factor_panel(p, Q, ldq, R, ldr, c + h, w - h, s, st);
 }
 
 }  // namespace
@@ -597,17 +650,18 @@ cqr_status coded_qr_plan_create(const cqr_config* cfg, const double* v_tilde, co
   p->ftol = tolerated(*p);
 
   // Workspace layout.
-  const int64_t n = c.n, b = c.b, N = p->N;
+  p->pw = inner_width(*p);
+  const int64_t n = c.n, b = std::min(p->pw, n), N = p->N;
   int64_t maxTiles = 1;
   auto tiles = [](int64_t M, int64_t Nc) { return ((M + kTile - 1) / kTile) * ((Nc + kTile - 1) / kTile); };
   maxTiles = std::max(maxTiles, tiles(b, N - b));          // trailing update
   maxTiles = std::max(maxTiles, tiles(n - b, b));          // re-projection
   maxTiles = std::max(maxTiles, tiles(b, b));              // within-panel projection, Gram
-  // four partial tiles per output tile: large products split up to ~1280
-  // workgroups (32 KB per partial tile)
-  p->npart = std::max<int64_t>(1024, 4 * maxTiles);
+  // four partial tiles per output tile (32 KB each): large products split up to
+  // ~1280 workgroups of at most four tiles, so never into more than 8 x 1280
+  p->npart = std::max<int64_t>(1024, std::min<int64_t>(4 * maxTiles, 8 * 1280));
   p->nS = std::max<int64_t>(n * b, (int64_t)kLeaf * kLeaf);   // S with the fused Gram rows: c1 x b, c1 <= n
-  p->ninfo = 64 + (int)(n / b);
+  p->ninfo = 64 + (int)((n + b - 1) / b);
   size_t off = align256(sizeof(int) * (size_t)p->ninfo);
   p->off_part = off;  off = align256(off + sizeof(double) * (size_t)p->npart * kTile * kTile);
   p->off_part2 = off; off = align256(off + sizeof(double) * (size_t)p->npart * kTile * kTile);
@@ -720,8 +774,8 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
                            void* ws, size_t ws_bytes, hipStream_t st) {
   drop_pending_error();
   if (!p || !Q || !R || !ws) return CQR_EINVAL;
-  const int64_t n = p->cfg.n, b = p->cfg.b, N = p->N, mp = p->mp;
-  const int npan = (int)(n / b);
+  const int64_t n = p->cfg.n, N = p->N, mp = p->mp;
+  const int npan = (int)(n / p->cfg.b);
   if (ldq < mp || ldr < p->rrows || pb < 0 || pe > npan || pb > pe) return CQR_EINVAL;
   if (ws_bytes < p->ws_bytes || (reinterpret_cast<uintptr_t>(ws) & 255)) return CQR_ENOMEM;
   cqr::Scratch s = scratch_of(*p, ws);
@@ -730,7 +784,9 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     prof(*p, PH_OTHER, 0.0, 4.0 * p->ninfo, st, [&] { cqr::launch_zero_ints(s.info, p->ninfo, st); });
     prof(*p, PH_OTHER, 0.0, 8.0 * n * N, st, [&] { cqr::launch_fill_zero(R, ldr, n, N, st); });
   }
-  const bool la = p->cfg.lookahead && pe - pb > 1 && side_ready(*p);
+  // the call's columns; w: the width of all panels where it is a leaf's
+  const int64_t w = p->pw, cb = pb * (int64_t)p->cfg.b, ce = pe * (int64_t)p->cfg.b;
+  const bool la = p->cfg.lookahead && ce - cb > panel_width(*p, cb) && side_ready(*p);
   const hipStream_t caller = st;
   if (la) {
     // both lookahead streams start after everything already queued on the
@@ -754,16 +810,42 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
   // the next panels' FP64 re-projection removes them and adds their
   // coefficients into R.
   const int lowp = p->cfg.precision == CQR_TRAIL_FP32 ? 1 : p->cfg.precision == CQR_TRAIL_BF16X3 ? 2 : 0;
-  // Panel k's update of columns [from, to):  R_bar = Qbar^T Q_t -> R[panel, from:];  Q_t -= Qbar R_bar
-  auto trail = [&](int64_t c0, int64_t from, int64_t to, const cqr::Scratch& sc, hipStream_t ss) {
+  // Update of columns [from, to) by the panel of b columns at c0:  R_bar = Qbar^T Q_t -> R[panel, from:];  Q_t -= Qbar R_bar
+  auto trail = [&](int64_t c0, int64_t b, int64_t from, int64_t to, const cqr::Scratch& sc, hipStream_t ss) {
     double* Rb = R + c0 + from * ldr;
     const double* P = Q + c0 * ldq;
     tn(*p, PH_TRAIL_TN, P, ldq, Q + from * ldq, ldq, (int)b, (int)(to - from), mp, Rb, ldr, nullptr, 0, sc, ss, -1,
        lowp);
     nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, P, ldq, Rb, ldr, mp, (int)(to - from), (int)b, sc, ss);
   };
+  // Panels in pairs (a, b = a+1): columns further right take both panels'
+  // updates at once, R rows = [Pa Pb]^T Q_t and Q_t -= [Pa Pb] R, so the
+  // trailing matrix is read and written half as often and both products run at
+  // twice the panel width's rate.  The kPairNear panels after the pair, which
+  // the chain needs sooner, take each panel's update by itself.  Pb's
+  // coefficients then come from columns that still carry their components along
+  // Pa; as Pb^T Pa is at rounding level the difference is too, and the next
+  // panels' re-projection removes it -- hence only with re-projection.  Only in
+  // FP64: reduced-precision coefficients keep the column state they are rounded
+  // from.
+  // The chain's re-projection fills the GPU, its panel passes do not: the pair's
+  // product is queued behind the next panel's re-projection and its update
+  // behind the one after, so that they run beside the passes (n = 4096: 13.4 ms
+  // queued at once, 12.8 so).
+  const bool pairs = la && p->cfg.reproject && lowp == 0 && mp * N * 8 > kPairBytes &&
+                     p->cfg.panel == CQR_PANEL_CHOLQR2;
+  int64_t far_c0 = -1, far_from = 0;     // the last pair and the columns its update has not been queued for
+  bool far_coef = false;                 // their coefficients are queued
+  auto pair_product = [&](int64_t c0, int64_t from, const cqr::Scratch& sc, hipStream_t ss) {
+    tn(*p, PH_TRAIL_TN, Q + c0 * ldq, ldq, Q + from * ldq, ldq, 2 * (int)w, (int)(N - from), mp, R + c0 + from * ldr,
+       ldr, nullptr, 0, sc, ss);
+  };
+  auto pair_update = [&](int64_t c0, int64_t from, const cqr::Scratch& sc, hipStream_t ss) {
+    nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, Q + c0 * ldq, ldq, R + c0 + from * ldr, ldr, mp, (int)(N - from),
+       2 * (int)w, sc, ss);
+  };
   bool deferred = false;       // a wide panel's update of the columns after the next panel, not yet forked
-  int64_t def_c0 = 0, def_from = 0;
+  int64_t def_c0 = 0, def_b = 0, def_from = 0;
   bool side_pending = false;   // ev_side marks side-stream work the chain has not waited for
   bool side_tail = false;      // side-stream work queued after the last ev_side record
   // the chain waits for the side stream's update of the next panel's columns
@@ -772,8 +854,25 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     side_pending = false;
     return hipStreamWaitEvent(st, p->ev_side, 0);
   };
+  // queue the next part of the last pair's update (all: what is left of it)
+  // behind what the chain has been given so far
+  auto far_step = [&](bool all) -> hipError_t {
+    if (far_c0 < 0) return hipSuccess;
+    hipError_t e = hipEventRecord(p->ev_main, st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(p->side, p->ev_main, 0);
+    if (e != hipSuccess) return e;
+    if (!far_coef) pair_product(far_c0, far_from, s2, p->side);
+    if (far_coef || all) {
+      pair_update(far_c0, far_from, s2, p->side);
+      far_c0 = -1;
+    }
+    far_coef = true;
+    side_tail = true;
+    return hipSuccess;
+  };
   // the chain waits for everything queued on the side stream
   auto join_side_all = [&]() -> hipError_t {
+    if (hipError_t e = far_step(true); e != hipSuccess) return e;
     if (side_tail) {
       if (hipError_t e = hipEventRecord(p->ev_side, p->side); e != hipSuccess) return e;
       side_pending = true;
@@ -782,11 +881,11 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     return join_side();
   };
   // panel k's update of columns [c1 + b, N) on the side stream
-  auto fork_side = [&](int64_t c0, int64_t from) -> hipError_t {
+  auto fork_side = [&](int64_t c0, int64_t b, int64_t from) -> hipError_t {
     hipError_t e = hipEventRecord(p->ev_main, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(p->side, p->ev_main, 0);
     if (e != hipSuccess) return e;
-    trail(c0, from, N, s2, p->side);
+    trail(c0, b, from, N, s2, p->side);
     e = hipEventRecord(p->ev_side, p->side);
     if (e == hipSuccess) {
       side_pending = true;
@@ -794,11 +893,15 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     }
     return e;
   };
-  for (int k = pb; k < pe; ++k) {
-    const int64_t c0 = (int64_t)k * b, c1 = c0 + b;
+  int64_t c1 = cb;
+  for (int k = 0; c1 < ce; ++k) {
+    const int64_t c0 = c1, b = std::min(panel_width(*p, c0), ce - c0);
+    c1 = c0 + b;
+    const int pk = (int)(c0 / p->cfg.b);    // its panel in the configuration's numbering
     double* P = Q + c0 * ldq;
-    const bool next = la && k + 1 < pe;     // panel k+1 is factored in this call
-    if (b <= kLeaf && p->cfg.panel == CQR_PANEL_CHOLQR2) {
+    const int64_t bn = la ? std::min(panel_width(*p, c1), ce - c1) : 0;   // the next panel, factored in this call
+    const bool next = bn > 0;
+    if (w <= kLeaf && p->cfg.panel == CQR_PANEL_CHOLQR2) {
       // First Cholesky-QR pass.  With re-projection its Gram matrix comes from
       // the same product as the coefficients, [Q[:, :c0] | P]^T P: since the
       // re-projection coefficients S are at rounding level, P^T P equals the
@@ -808,7 +911,7 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
       int64_t ldw1 = b;
       bool chol1 = false;   // first Cholesky pass already launched
       cqr::NnArgs split{};
-      if (p->cfg.reproject && k > 0) {
+      if (p->cfg.reproject && c0 > 0) {
         // S = Q[:, :c0]^T P (rows < c0, also added into R[:c0, panel]);  P -= Q[:, :c0] S.
         // The first Cholesky pass needs only the Gram rows and the update only
         // S, so when the update splits over K the Cholesky runs in its launch
@@ -817,11 +920,20 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
         W1 = s.S + c0;
         ldw1 = c1;
         chol1 = nn_chol(*p, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0,
-                        cqr::chol_args(W1, ldw1, (int)b, k, s), s, st, split);
+                        cqr::chol_args(W1, ldw1, (int)b, pk, s), s, st, split);
         if (!chol1) nn(*p, PH_REPROJ_NN, P, ldq, Q, ldq, s.S, c1, mp, (int)b, (int)c0, s, st);
       } else {
         tn(*p, PH_GRAM, P, ldq, P, ldq, (int)b, (int)b, mp, s.G, b, nullptr, 0, s, st);
       }
+      // first, second: the panel's place in its pair; the pair before goes on with
+      // its update
+      const bool first = pairs && (k & 1) == 0 && next, second = pairs && (k & 1) == 1;
+      if (first || second)
+        if (hipError_t e = far_step(false); e != hipSuccess) return hip_fail(e);
+      // columns of the early update: all right of the next panel, or, in pairs,
+      // up to the end of the kPairNear panels after the pair
+      const int64_t ncol =
+          std::min<int64_t>(N - c1 - b, first ? kPairNear * b : second ? (kPairNear - 1) * b : N);
       // With lookahead the second pass also updates the next panel, whose
       // columns must first carry panel k-1's update from the side stream.  (The
       // wait is queued before panel k's early update records its own event.)
@@ -833,22 +945,24 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
       // P^T Q_t), and the update Q_t -= P R_t waits for the finished panel P.
       // X alternates between two buffers: the chain writes panel k+1's copy
       // before it waits for panel k's update.
-      const bool early = next && c1 + b < N && s.X;
+      // (In reduced precision only where the first pass runs in the
+      // re-projection's launches, see panel_first.)
+      const bool early = next && c1 + b < N && s.X && (lowp == 0 || chol1);
       cqr::PanelArgs pa = panel_args(*p, P, ldq, (int)b, next ? Q + c1 * ldq : nullptr, W1, ldw1,
-                                     chol1 ? &split : nullptr, R, ldr, c0, k, s);
+                                     chol1 ? &split : nullptr, R, ldr, c0, pk, s);
       if (early) {
         pa.X = s.X + (k & 1) * s.xstride;
         pa.ldx = s.ldx;
         pa.Tcopy = s.T2;
-        pa.fb = s.fb + k;
+        pa.fb = s.fb + c0 / w;
       }
-      panel_first(*p, pa, !chol1, st);
+      panel_first(*p, pa, !chol1, s, st);
       cqr::TnArgs ea{};
       if (early) {
         hipError_t e = hipEventRecord(p->ev_main, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(p->side, p->ev_main, 0);
         if (e != hipSuccess) return hip_fail(e);
-        ea = tn_early(*p, pa.X, s.ldx, Q + (c1 + b) * ldq, ldq, (int)b, (int)(N - c1 - b), s2, p->side, lowp);
+        ea = tn_early(*p, pa.X, s.ldx, Q + (c1 + b) * ldq, ldq, (int)b, (int)ncol, s2, p->side, lowp);
       }
       // P <- P1 R2^{-1}, and with lookahead R[panel, next] = (P1 R2^{-1})^T
       // Q_next, Q_next -= P R[panel, next]
@@ -864,31 +978,42 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
           // columns after them are updated while the chain moves on (the
           // chain touches them only after join_side_all).
           double* Rb = R + c0 + (c1 + b) * ldr;
-          tn_tmul(*p, ea, s.T2, (int)b, Rb, ldr, p->side, s.fb + k, P, ldq);
-          const int64_t near = std::min<int64_t>(b, N - c1 - b);
+          tn_tmul(*p, ea, s.T2, (int)b, Rb, ldr, p->side, s.fb + c0 / w, P, ldq);
+          const int64_t near = pairs ? ncol : std::min<int64_t>(b, ncol);
           nn(*p, PH_TRAIL_NN, Q + (c1 + b) * ldq, ldq, P, ldq, Rb, ldr, mp, (int)near, (int)b, s2, p->side);
           e = hipEventRecord(p->ev_side, p->side);
           if (e != hipSuccess) return hip_fail(e);
           side_pending = true;
-          if (c1 + b + near < N) {
-            nn(*p, PH_TRAIL_NN, Q + (c1 + b + near) * ldq, ldq, P, ldq, Rb + near * ldr, ldr, mp,
-               (int)(N - c1 - b - near), (int)b, s2, p->side);
+          if (near < ncol) {
+            nn(*p, PH_TRAIL_NN, Q + (c1 + b + near) * ldq, ldq, P, ldq, Rb + near * ldr, ldr, mp, (int)(ncol - near),
+               (int)b, s2, p->side);
             side_tail = true;
+          }
+          if (second && c1 + kPairNear * b < N) {
+            far_c0 = c0 - b;
+            far_from = c1 + kPairNear * b;
+            far_coef = false;
           }
         } else if (c1 + b < N) {
           // the remaining columns on the side stream
-          if (hipError_t e = fork_side(c0, c1 + b); e != hipSuccess) return hip_fail(e);
+          if (hipError_t e = fork_side(c0, b, c1 + b); e != hipSuccess) return hip_fail(e);
         }
       } else if (c1 < N) {
         if (hipError_t e = join_side_all(); e != hipSuccess) return hip_fail(e);
-        trail(c0, c1, N, s, st);
+        // (the columns right of the panels near the pair lack its first panel too)
+        const int64_t to = second ? std::min<int64_t>(c1 + kPairNear * b, N) : N;
+        trail(c0, b, c1, to, s, st);
+        if (to < N) {
+          pair_product(c0 - b, to, s, st);
+          pair_update(c0 - b, to, s, st);
+        }
       }
       continue;
     }
     // Panels wider than a Cholesky-QR leaf, and every panel of the
     // column-wise modes: re-projection, recursive panel, then the update (the
     // next panel's columns first with lookahead).
-    if (p->cfg.reproject && k > 0) {
+    if (p->cfg.reproject && c0 > 0) {
       tn(*p, PH_REPROJ_TN, Q, ldq, P, ldq, (int)c0, (int)b, mp, s.S, c0, R + c0 * ldr, ldr, s, st);
       nn(*p, PH_REPROJ_NN, P, ldq, Q, ldq, s.S, c0, mp, (int)b, (int)c0, s, st);
     }
@@ -897,23 +1022,24 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     // large products run one after the other instead of sharing the GPU, and
     // the update overlaps this panel's factorization, whose kernels are small.
     if (deferred) {
-      if (hipError_t e = fork_side(def_c0, def_from); e != hipSuccess) return hip_fail(e);
+      if (hipError_t e = fork_side(def_c0, def_b, def_from); e != hipSuccess) return hip_fail(e);
       deferred = false;
     }
-    factor_panel(*p, Q, ldq, R, ldr, c0, (int)b, k, s, st);
+    factor_panel(*p, Q, ldq, R, ldr, c0, (int)b, s, st);
     if (c1 >= N) continue;
     if (hipError_t e = join_side_all(); e != hipSuccess) return hip_fail(e);
-    if (next && c1 + b < N) {
-      trail(c0, c1, c1 + b, s, st);
+    if (next && c1 + bn < N) {
+      trail(c0, b, c1, c1 + bn, s, st);
       deferred = true;
       def_c0 = c0;
-      def_from = c1 + b;
+      def_b = b;
+      def_from = c1 + bn;
     } else {
-      trail(c0, c1, N, s, st);
+      trail(c0, b, c1, N, s, st);
     }
   }
   if (deferred)
-    if (hipError_t e = fork_side(def_c0, def_from); e != hipSuccess) return hip_fail(e);
+    if (hipError_t e = fork_side(def_c0, def_b, def_from); e != hipSuccess) return hip_fail(e);
   if (hipError_t e = join_side_all(); e != hipSuccess) return hip_fail(e);
   if (la) {
     // the caller's stream waits for the chain (which has joined the updates)

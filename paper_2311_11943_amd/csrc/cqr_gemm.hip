@@ -1295,8 +1295,11 @@ void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
 
 static void launch_tn_sum(const TnArgs& a, hipStream_t st) {
   // one batch of 16 loads per thread covers up to 16 splits; beyond that the
-  // splits are shared by 4 or 16 groups of threads
-  if (a.nsplit <= 16)
+  // splits are shared by 4 or 16 groups of threads, or (seq) only the elements
+  // by more workgroups
+  if (a.seq && a.nsplit > 16)
+    hipLaunchKernelGGL((tn_reduce_split_kernel<1, 1>), dim3(a.ntiles * 64), dim3(64), 0, st, a);
+  else if (a.nsplit <= 16)
     hipLaunchKernelGGL(tn_reduce_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a);
   else if (a.nsplit <= 64)
     hipLaunchKernelGGL((tn_reduce_split_kernel<4, 4>), dim3(a.ntiles * 16), dim3(256), 0, st, a);
@@ -1667,10 +1670,22 @@ __device__ __forceinline__ bool gram_load(int tid, const double* W, int64_t ldw,
   return *flag != 0;
 }
 
+// chol_blocked out of line, so that its registers do not add to those of the
+// kernels that call it: they run beside products of 128 registers whose
+// workgroups leave 256 a lane when they end, and a kernel that needs more waits
+// for a product's whole grid.
+__device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
+                                                     double* prow, const double* dg) {
+  bool bad = false;
+  chol_blocked(threadIdx.x, nb, Rl, Tl, prow, dg, bad);
+  return bad;
+}
+
 // First Cholesky-QR pass by one workgroup: R1 <- chol(W), T <- R1^{-1} (both
 // left in Rl and Tl).  Breakdown (a pivot at most kCholBreak times its diagonal
 // entry): R1 = T = I, so the transform leaves the panel as it is, and info[1]
 // tells the second pass.  store: write R1 (and T, if a.T) and info[1].
+template <bool INLINE>
 __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
                                            double* prow, double* dg, int* flag, bool store) {
   const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6, w = a.w;
@@ -1678,7 +1693,10 @@ __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf
   __syncthreads();
   if (tid == 0) *flag = 0;
   bool bad = false;
-  chol_blocked(tid, (w + 15) / 16, Rl, Tl, prow, dg, bad);    // (barriers inside)
+  if (INLINE)
+    chol_blocked(tid, (w + 15) / 16, Rl, Tl, prow, dg, bad);      // (barriers inside)
+  else
+    bad = chol_exact((w + 15) / 16, Rl, Tl, prow, dg);
   if (bad) *flag = 1;
   __syncthreads();
   const bool broke = *flag != 0;
@@ -1702,15 +1720,6 @@ __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf
   if (tid == 0) a.info[1] = broke;
 }
 
-// The exact factorization in a second pass that needs it (rare): out of line,
-// so that its registers do not add to those of the usual path.
-__device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                                     double* prow, const double* dg) {
-  bool bad = false;
-  chol_blocked(threadIdx.x, nb, Rl, Tl, prow, dg, bad);
-  return bad;
-}
-
 // First pass's transform, and the second pass's Gram product from the same
 // rows: a workgroup walks strips of 16 rows of the panel; each strip of
 // P (- the split partials of the re-projection update) is multiplied by
@@ -1722,15 +1731,19 @@ __device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf 
 // first pass's Cholesky itself (each of them the same: cheaper than a launch
 // of one workgroup before this one); otherwise T comes from memory (the
 // factorization ran beside the split update, nn_chol_kernel).
+// (gpart == nullptr: the transform alone, for the modes that form the Gram
+// product by itself.)
 // Latency-bound: 16-row strips let a short panel fill many workgroups.  FULL:
 // w = 64, no column masks; NEXT: with Q_next.
 template <bool CHOL, bool FULL, bool NEXT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void panel_first_kernel(PanelArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void panel_first_kernel(PanelArgs a) {
   __builtin_amdgcn_s_setprio(2);   // panel chain
   __shared__ double sT[kLeaf][kLeaf + 1];
-  __shared__ double sR[CHOL ? kLeaf : 1][kLeaf + 1];
-  __shared__ double sP[16][kLeaf + 1];      // the strip before, then after the transform
-  __shared__ double sQ[NEXT ? 16 : 1][kLeaf + 1];   // Q_next's rows of the strip
+  // R1 while it is formed, then the strip before and after its transform and
+  // Q_next's rows of it.  (At most 72 KB in all: what a workgroup of the update
+  // that runs beside leaves when it ends.)
+  __shared__ double sR[CHOL ? kLeaf : (NEXT ? 32 : 16)][kLeaf + 1];
+  double (*sP)[kLeaf + 1] = sR, (*sQ)[kLeaf + 1] = sR + 16;
   __shared__ double prow[16];
   __shared__ double dg[kLeaf];
   __shared__ int flag;
@@ -1758,7 +1771,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   };
   if ((int)blockIdx.x < strips) load(blockIdx.x);
   if constexpr (CHOL) {
-    chol_first(a.c, sR, sT, prow, dg, &flag, blockIdx.x == 0);
+    chol_first<false>(a.c, sR, sT, prow, dg, &flag, blockIdx.x == 0);
+    __syncthreads();
   } else {
     double tv[16];
 #pragma unroll
@@ -1816,6 +1830,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         if (a.X) a.X[i + j * a.ldx] = acc[r];
       }
     }
+    if (!a.gpart) continue;
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1836,6 +1851,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         }
     }
   }
+  if (!a.gpart) return;
   const int tiles = NEXT ? 2 : 1;
   double* mine = a.gpart + part_off(blockIdx.x, tiles, 0, wave) + lane;
 #pragma unroll
@@ -1879,24 +1895,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int tx = lane, ty = wave;
   const bool last = blockIdx.x + 1 == gridDim.x;
   const int tiles = (int)((a.mrows + 63) / 64);
-  // rows i = 64 tile + 16 wave + li: columns 4 m + g of P, 16 y + 4 r + g of Q_next
+  // rows i = 64 tile + 16 wave + li: columns 16 y + 4 r + g of Q_next; of P,
+  // the operand of product m: column 4 m + g, what the accumulators of the
+  // transform hold for m = 4 y + r (NEXT), or 16 (m / 4) + 4 g + m % 4
   // (outside the panel: row or column 0, meeting zeros of T, or not stored)
   double xa[16], cv[16];
+  auto col = [&](int m) { return NEXT ? 4 * m + g : 16 * (m >> 2) + 4 * g + (m & 3); };
   auto load = [&](double (&v)[16], const double* M, int tile) {
     const int64_t i = (int64_t)tile * 64 + 16 * wave + li, ic = i < a.mrows ? i : 0;
 #pragma unroll
     for (int m = 0; m < 16; ++m) {
-      const int j = 4 * m + g;
+      const int j = col(m);
       v[m] = M[ic + (j < w ? j : 0) * a.ldp];
     }
   };
   auto mask = [&](double (&v)[16]) {
     if (!FULL) {
 #pragma unroll
-      for (int m = 0; m < 16; ++m) v[m] = 4 * m + g < w ? v[m] : 0.0;
+      for (int m = 0; m < 16; ++m) v[m] = col(m) < w ? v[m] : 0.0;
     }
   };
-  const double* Gn = a.G + (int64_t)kLeaf * w;    // P1^T Q_next (ld w)
+  const double* Gn = a.Gn;
   double xr[16];
   if (!last) {
     load(xa, a.P, blockIdx.x);
@@ -1960,7 +1979,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int m = 0; m < 16; ++m)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) pf[y] = mfma(sT[4 * m + g][16 * y + li], xa[m], pf[y]);
+        for (int y = 0; y < 4; ++y) pf[y] = mfma(sT[col(m)][16 * y + li], xa[m], pf[y]);
       if (tile + (int)gridDim.x - 1 < tiles) load(xa, a.P, tile + gridDim.x - 1);
       // the accumulators hold P[i][4 m + g] for m = 4 y + r: the operand of the
       // second product, lane for lane
@@ -2033,16 +2052,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // of them (their partial Gram blocks, 64 KB each with Q_next, are written and
 // read back), 256 for panels of more than 32768 rows, where the rows' own bytes
 // outweigh the partials'.
-int panel_first_blocks(int64_t mrows) {
-  const int64_t strips = (mrows + 15) / 16, cap = mrows > 32768 ? 256 : 128;
+int panel_first_blocks(int64_t mrows, bool gram) {
+  const int64_t strips = (mrows + 15) / 16, cap = mrows > 32768 || !gram ? 256 : 128;
   const int64_t per = (strips + cap - 1) / cap;
   return (int)((strips + per - 1) / per);
 }
 
 void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st) {
-  const dim3 grid((unsigned)panel_first_blocks(a.mrows));
+  const dim3 grid((unsigned)panel_first_blocks(a.mrows, a.gpart != nullptr));
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
-  const bool full = a.w == kLeaf, next = a.Qn != nullptr;
+  const bool full = a.w == kLeaf, next = a.Qn && a.gpart;
   switch ((chol ? 4 : 0) | (full ? 2 : 0) | (next ? 1 : 0)) {
     case 0: go(panel_first_kernel<false, false, false>); break;
     case 1: go(panel_first_kernel<false, false, true>); break;
@@ -2055,12 +2074,12 @@ void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st) {
   }
 }
 
-// The Gram partials of launch_panel_first summed into G (ld w; G_next from
-// column kLeaf on).
+// The Gram partials of launch_panel_first summed into G (ld w; Gn from column
+// kLeaf on).
 void launch_panel_reduce(const PanelArgs& a, hipStream_t st) {
   TnArgs t{};
   t.M = t.M2 = a.w; t.N = a.Qn ? kLeaf + a.w : a.w;
-  t.nsplit = panel_first_blocks(a.mrows);
+  t.nsplit = panel_first_blocks(a.mrows, true);
   t.tilesN = t.ntiles = a.Qn ? 2 : 1;
   t.C = a.G; t.ldc = a.w;
   t.part = a.gpart;
@@ -2674,7 +2693,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ int flag;
   if ((int)blockIdx.x == a.ntiles) {
     if (blockIdx.y == 0)
-      chol_first(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
+      chol_first<true>(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
                  reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), prow, dg, &flag, true);
     return;
   }

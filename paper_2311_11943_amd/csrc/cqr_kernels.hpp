@@ -112,6 +112,7 @@ struct TnArgs {
   int bf3;            // split-BF16 product (tnb_kernel): each FP64 operand as hi + mid + lo
                       // BF16 parts, six part products on BF16 MFMA with FP32 sums over
                       // 32 k-values, FP64 sums across them (output layout as f32)
+  int seq;            // sum the splits one after the other, in one order for every count
   int lower;          // square product, 128 x 128 blocks above the diagonal left out (quad only)
 };
 
@@ -183,14 +184,14 @@ struct PanelArgs {
   const double* T;                  // or formed from c.W by the kernel itself
   CholArgs c;
   double* X; int64_t ldx;           // second destination of the first pass's panel (or nullptr)
-  double* gpart;                    // Gram partials (panel_first_blocks x 2 tiles)
-  double* G;                        // P1^T P1 (ld w) and, from column kLeaf on, P1^T Q_next
+  double* gpart;                    // Gram partials (panel_first_blocks x 2 tiles), or nullptr
+  double* G; double* Gn;            // P1^T P1 and P1^T Q_next (ld w)
   // second pass
   double* Rout; double* Rbar; int64_t ldr;   // R_panel = R2 R1; the next panel's coefficients
   double* Tcopy;                    // copy of R2^{-1} (w x w, ld w), or nullptr
   int* fb;                          // set to 1 when the column-wise fallback ran (or nullptr)
 };
-int panel_first_blocks(int64_t mrows);
+int panel_first_blocks(int64_t mrows, bool gram);
 void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st);
 void launch_panel_reduce(const PanelArgs& a, hipStream_t st);
 void launch_panel_second(const PanelArgs& a, hipStream_t st);
