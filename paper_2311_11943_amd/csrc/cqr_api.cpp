@@ -432,7 +432,7 @@ void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64
 }
 
 // Column-wise panel modes (CGS2, ICGS, MGS): a grid of workgroups
-// orthogonalises the leaf P (m' x w) column by column, one launch per step,
+// orthogonalises the leaf P (m' x w) column by column, one launch per column,
 // and stores R[leaf, leaf].  Flops: 4 m' w^2 for CGS2 (two projections, each
 // a product and an update), 2 m' w^2 for MGS; bytes: the panel read and
 // written once (the minimum).
@@ -447,7 +447,12 @@ void colpanel(cqr_plan_s& p, double* P, int64_t ldq, int w, double* Rout, int64_
   a.work = s.colw;
   const double mult = a.mode == cqr::COLWISE_MGS ? 2.0 : 4.0;
   prof(p, PH_COLPANEL, mult * (double)p.mp * w * w, 16.0 * (double)p.mp * w, st,
-       [&] { cqr::launch_colpanel(a, st); });
+       [&] {
+         if (p.cfg.precision == CQR_FP64)
+           cqr::launch_colpanel(a, st);
+         else
+           cqr::launch_colgrid(a, st);
+       });
 }
 
 // The product W = X^T B of an update that starts before its panel is

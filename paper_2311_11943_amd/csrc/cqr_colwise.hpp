@@ -15,8 +15,9 @@
 // butterfly inside each wavefront (after four exchange steps lane l holds its
 // lane group's sum for column l mod 16), two more exchanges across the lane
 // groups, and (for the workgroup sum) a fixed-order sum over the waves in
-// LDS, so results do not depend on scheduling.  colgrid_kernel, the
-// multi-workgroup CGS2 / ICGS / MGS panel modes, uses the wavefront part.
+// LDS, so results do not depend on scheduling.  colstep_kernel and
+// colmgs_kernel, the multi-workgroup CGS2 / ICGS / MGS panel modes, use the
+// wavefront part.
 #pragma once
 #include "cqr_kernels.hpp"
 

@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace cqr {
 
@@ -2102,317 +2103,344 @@ void launch_panel_second(const PanelArgs& a, hipStream_t st) {
 
 // A panel leaf orthogonalised column by column (the CGS2, ICGS and MGS panel
 // modes) by a grid of workgroups, each owning one slab of rows.  A column
-// needs a sum over all rows before every update, so each step of the method
-// is one launch: it first reduces the partial sums every workgroup of the
-// previous launch left (all workgroups sum them redundantly, in the same
-// fixed order, so they take identical decisions), then works on its own
-// slab and leaves its partial sums for the next launch.  Kernel boundaries
-// order the steps; nothing waits inside a launch.
+// needs a sum over all rows before every update, so each step of the method is
+// one launch: it first reduces the partial sums every workgroup of the previous
+// launch left (all workgroups sum them redundantly, in the same fixed order, so
+// they take identical decisions), then works on its own slab and leaves its
+// partial sums for the next launch.  Kernel boundaries order the steps; nothing
+// waits inside a launch.
 //
-// CGS2 / ICGS, column j:
-//   PROJECT(j)  s1 = the reduced P[:, <j]^T p_j; column j-1 normalised by its
-//               r (known now); p_j -= P[:, <j] s1; partials of ||p_j||^2 and,
-//               speculatively, of P[:, <j]^T p_j for a second projection.
-//   REORTH(j)   second projection when CGS2, or when ICGS finds
-//               ||p_j||^2 < eta^2 ||p_j before||^2 (the DGKS test); partials
-//               of ||p_j||^2, of ||p_{j+1}||^2 and of P[:, <=j]^T p_{j+1}
-//               (column j not yet normalised: that product is divided by
-//               r_jj in PROJECT(j+1)).
-// MGS, column i (the paper's sequential MGS):
-//   MGS(i)      r_{i-1,i-1} and r_{i-1,c} = u_{i-1}^T u_c / r_{i-1,i-1} from
-//               the reduced sums; q_{i-1} = u_{i-1} / r_{i-1,i-1};
-//               u_c -= r_{i-1,c} q_{i-1} for c >= i; partials of ||u_i||^2 and
-//               of u_i^T u_c for c > i.
-// FINISH normalises the last column.  Workgroup 0 writes R.
+// CGS2 / ICGS, one launch per column.  Step j finishes column j-1 and projects
+// column j for the first time, both from sums over the same rows:
+//   q_{j-2}   = w'_{j-2} / r, r its norm (summed by the step before);
+//   w'_{j-1}  = w_{j-1} - Q a, a = Q^T w_{j-1} (the second projection; CGS2
+//               always, ICGS when ||w_{j-1}|| < eta ||p_{j-1}||, the DGKS test);
+//   p'_j = w_j = p_j - Q t - w'_{j-1} e, t = Q^T p_j, and e = w'_{j-1}^T p_j /
+//               ||w'_{j-1}||^2 from the sums at hand: w'^T p = w^T p - a^T t,
+//               ||w'||^2 = ||w||^2 - ||a||^2;
+//   partials for step j+1: Q^T w_j, Q^T p_{j+1} (w'_{j-1} among Q's columns, not
+//               yet normalised: those two are divided by its r there), ||w_j||^2,
+//               w_j^T p_{j+1}, ||p_{j+1}||^2, ||w'_{j-1}||^2.
+// e enters only the first projection.  Where the second projection changed
+// w_{j-1} by more than half (||a||^2 > ||w||^2 / 2, a column nearly dependent on
+// its panel) e's relative accuracy is poor, and ICGS takes column j's second
+// projection whatever its test says.
+// MGS (the paper's sequential MGS), step i: q_{i-1} = u_{i-1} / r; u_c -=
+// r_{i-1,c} q_{i-1} for c >= i; partials of ||u_i||^2 and of u_i^T u_c for c > i.
 //
-// A thread loads the columns a step touches in its row into registers at
-// once (the first row block before the reduction of the previous partial
-// sums, so that the two memory latencies overlap), computes the update and
-// the step's inner products from them, and stores what changed; one row per
-// thread up to 65536 rows.  The wavefront sums of every 16-slot chunk are
-// formed first and exchanged through LDS once per row block.  Partial sums:
-// slots [0, 64) inner products (whole 16-slot chunks are written), 64-66 the
-// squared norms (all three written by every launch).
-enum : int { CG_START = 0, CG_PROJECT = 1, CG_REORTH = 2, CG_FINISH = 3, CG_MGS = 4 };
+// Bound by latency: w + 2 dependent launches a leaf.  A workgroup takes 64 rows
+// (more row blocks beyond kColGridMax workgroups); its wave q holds columns
+// 16 q .. 16 q + 15 of them, a row per lane, so that the four waves share a
+// row's work and the code stays short (the launches' time is largely that of
+// fetching it); a wave's sums over its rows end in one transposing butterfly per
+// 16 inner products and go straight to memory.  (Two launches per column with 64
+// columns a thread took 10 us each: the n = 2048 factorization with ICGS panels
+// 48.3 ms, now 23.4: about 7 us a launch and 3 between dependent ones.)
+// Partial sums: slots [0, 64) and [64, 128) inner products, 128 .. 131 the others.
 constexpr int kColThreads = 256;
-constexpr int kSlotNA = 64, kSlotNB = 65, kSlotNC = 66;
+enum : int { kSlotT = 64, kSlotW = 128, kSlotU = 129, kSlotP = 130, kSlotN = 131 };
+static_assert(kSlotN < kColSlots, "slots");
 
-// Row r's columns [lo, hi) into v (zeros elsewhere) and its columns e0 and
-// e1 (e1 < 0: none) into x0, x1, addressed as a uniform column base plus the
-// row's 32-bit byte offset in the slab that starts at row r0.
-__device__ __forceinline__ void colgrid_load_row(double (&v)[kLeaf], double& x0, double& x1, const double* P,
-                                                 int64_t r0, int64_t ld, int64_t r, bool act, int lo, int hi, int e0,
-                                                 int e1) {
-  const char* const slab = reinterpret_cast<const char*>(P + r0);
-  const uint32_t off = act ? (uint32_t)(r - r0) * 8u : 0u;
-#pragma unroll
-  for (int c = 0; c < kLeaf; ++c)
-    v[c] = (act && c >= lo && c < hi) ? *reinterpret_cast<const double*>(slab + c * ld * 8 + off) : 0.0;
-  x0 = act ? P[r + e0 * ld] : 0.0;
-  x1 = act && e1 >= 0 ? P[r + e1 * ld] : 0.0;
+// r from a squared norm; a zero or non-finite norm flags the panel as exactly
+// rank-deficient and leaves the column unnormalised
+__device__ __forceinline__ double col_diag(const ColArgs& a, double r2, bool lead) {
+  if (!(r2 > 0.0) || !isfinite(r2)) {
+    if (lead && a.info[0] == 0) a.info[0] = 1 + a.panel;
+    r2 = 1.0;
+  }
+  return sqrt(r2);
 }
 
-template <int kind>
-__global__ __launch_bounds__(kColThreads) void colgrid_kernel(ColArgs a, int G, int64_t rb, int j, int par) {
+// sum over the wavefront
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+
+// red[0 .. kColSlots) = the previous launch's partial sums over G = 32, 64 or 128
+// workgroups, in a fixed order, 16 or 32 loads of a thread in flight: two threads
+// for each of the first 128 slots, a wave for each of the four others.
+__device__ __forceinline__ void col_reduce(const double* in, int G, double* red, double* half) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), slot = tid & 127, h = wave >> 1;
+  const double* y = in + 128 + wave + lane * kColSlots;
+  const double y0 = y[lane < G ? 0 : -lane * kColSlots], y1 = G > 64 ? y[64 * kColSlots] : 0.0;
+  const double* p = in + h * (G / 2) * kColSlots + slot;
+  double acc = 0.0;
+  auto batch = [&](auto n) {
+    constexpr int kN = decltype(n)::value;
+    double t[kN];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) t[k] = p[k * kColSlots];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < kN; ++k) acc += t[k];
+    p += kN * kColSlots;
+  };
+  if (G == 32) {
+    batch(std::integral_constant<int, 16>{});
+  } else {
+    for (int g = 0; g < G / 2; g += 32) batch(std::integral_constant<int, 32>{});
+  }
+  if (h) half[slot] = acc;
+  const double n = wave_sum((lane < G ? y0 : 0.0) + y1);
+  if (lane == 0) red[128 + wave] = n;
+  __syncthreads();
+  if (!h) red[slot] = acc + half[slot];
+  __syncthreads();
+}
+
+// Row r (a valid one) of the wave's 16 columns from c0 on, of which the first
+// `cols` are used and the others zero.  All or none are loaded, through one
+// advancing address.
+__device__ __forceinline__ void col_load(double (&v)[16], const double* P, int64_t ld, int64_t r, int c0, int cols,
+                                         int w) {
+  if (cols <= 0) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = 0.0;
+    return;
+  }
+  const double* p = P + r + c0 * ld;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    v[c] = *p;
+    p += c0 + c + 1 < w ? ld : 0;
+  }
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = c < cols ? v[c] : 0.0;
+}
+
+// CGS2 / ICGS step j (0 <= j <= w + 1)
+__global__ __launch_bounds__(kColThreads) void colstep_kernel(ColArgs a, int G, int64_t rb, int j, int par) {
   __builtin_amdgcn_s_setprio(2);   // panel chain
-  __shared__ double red[kColSlots];
-  __shared__ double tmp[kColThreads];
-  __shared__ double wsum[kColThreads / 64][kLeaf + kColChunk];   // per-wavefront sums of every slot
-  __shared__ double coef[kLeaf + kColChunk];                     // zero beyond the step's coefficients
-  const int tid = threadIdx.x, g = blockIdx.x, w = a.w;
+  __shared__ double red[kColSlots], half[128];
+  // per column: coefficients of the two projections, scale (1, or 1 / r of the
+  // column that is not yet normalised)
+  __shared__ double ca[kLeaf], ct[kLeaf], cs[kLeaf];
+  __shared__ double sums[2][4][64];
+  __shared__ double s_aa, s_at;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = blockIdx.x;
+  const int w = a.w, c0 = 16 * wave;
   const int64_t ld = a.ldp;
   double* const P = a.P;
   const int64_t r0 = (int64_t)g * rb, r1 = min(a.mrows, r0 + rb);
   const int64_t bufsz = (int64_t)kColGridMax * kColSlots;
-  const double* in = a.work + (par ^ 1) * bufsz;
   double* out = a.work + par * bufsz + (int64_t)g * kColSlots;
-  double* state = a.work + 2 * bufsz;   // [0] ||p_j||^2 before its first projection, [1] after it, [2] second taken
+  const double* st_in = a.work + 2 * bufsz + 4 * (par ^ 1);   // [0] ||p_{j-1}||^2, [1] e of the step before, [2] force
+  double* st_out = a.work + 2 * bufsz + 4 * par;
   const bool lead = g == 0 && tid == 0;
+  const int nq = j < 2 ? 0 : j - 1;       // finished columns; the last of them not yet normalised
+  const bool haw = j >= 1 && j <= w, hap = j < w, han = j + 1 < w;    // w_{j-1}, p_j, p_{j+1} exist
+  const int kn = nq - 1 - c0, kw = j - 1 - c0;     // columns nq - 1 and j - 1 in the wave's registers (if 0 .. 15)
 
-  // inner-product slots this launch reads [rlo, rhi) and writes [wlo, whi);
-  // columns a row holds in registers [lo, hi); single columns e0 and e1
-  int rlo = 0, rhi = 0, wlo = 0, whi = 0, lo = 0, hi = 0, e0 = 0, e1 = -1;
-  if constexpr (kind == CG_PROJECT) {   // e0 = p_j, e1 = column j-1
-    rhi = j; whi = j; hi = j; e0 = j; e1 = j - 1;
-  }
-  if constexpr (kind == CG_REORTH) {    // e0 = p_j, e1 = p_{j+1}
-    rhi = j; whi = j + 1 < w ? j + 1 : 0; hi = j; e0 = j; e1 = j + 1 < w ? j + 1 : -1;
-  }
-  if constexpr (kind == CG_MGS) {       // e0 = u_j, e1 = u_{j-1}
-    if (j > 0) { rlo = j; rhi = w; }
-    wlo = j + 1; whi = w; lo = j; hi = w; e0 = j; e1 = j - 1;
-  }
-  if constexpr (kind == CG_FINISH) e0 = w - 1;
-
-  double v[kLeaf], x0 = 0.0, x1 = 0.0;
-  // the first row block is loaded before the reduction below, which it does
-  // not depend on, so the two memory latencies overlap
-  const int nit = (int)((rb + kColThreads - 1) / kColThreads);
-  colgrid_load_row(v, x0, x1, P, r0, ld, r0 + tid, r0 + tid < r1, lo, hi, e0, e1);
-  // the state words a step uses, read before the reduction below (workgroup 0
-  // of the same launch writes only words the step does not read: PROJECT
-  // writes [0] and reads [1], [2]; REORTH writes [1], [2] and reads [0])
-  double st0 = 0.0, st1 = 0.0, st2 = 0.0;
-  if constexpr (kind == CG_REORTH) st0 = state[0];
-  if constexpr (kind == CG_PROJECT || kind == CG_FINISH) {
-    st1 = state[1];
-    st2 = state[2];
-  }
-
-  for (int c = tid; c < kLeaf + kColChunk; c += kColThreads) coef[c] = 0.0;
-  // reduce the previous launch's partials: its inner products in [rlo, rhi)
-  // and the three norms; thread (si, q) sums workgroups q, q + Q, ... in order
-  if (!(kind == CG_START || (kind == CG_MGS && j == 0))) {
-    const int nd = rhi - rlo, ns = nd + 3, Q = kColThreads / ns;
-    const int si = tid % ns, q = tid / ns;
-    const int slot = si < nd ? rlo + si : kSlotNA + (si - nd);
-    if (q < Q) {
-      double acc = 0.0;
-      int h = q;
-      for (; h + 3 * Q < G; h += 4 * Q) {
-        const double y0 = in[(int64_t)h * kColSlots + slot], y1 = in[(int64_t)(h + Q) * kColSlots + slot];
-        const double y2 = in[(int64_t)(h + 2 * Q) * kColSlots + slot], y3 = in[(int64_t)(h + 3 * Q) * kColSlots + slot];
-        acc += y0;
-        acc += y1;
-        acc += y2;
-        acc += y3;
+  double e = 0.0;
+  bool second = false;
+  double acca[16], acct[16], sw = 0.0, su = 0.0, sp = 0.0, sn = 0.0;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) acca[c] = acct[c] = 0.0;
+  for (int64_t rr = r0; rr < r1; rr += 64) {
+    // (rows past the last count as zero)
+    const int64_t row = min(rr + lane, r1 - 1);
+    const bool act = rr + lane < r1;
+    double v[16];
+    col_load(v, P, ld, row, c0, nq - c0, w);
+    double xw = haw ? P[row + (j - 1) * ld] : 0.0, xp = hap ? P[row + j * ld] : 0.0;
+    double xn = han ? P[row + (j + 1) * ld] : 0.0;
+    if (rr == r0) {
+      // the first block's loads are under way: the reduction of the previous
+      // launch's sums, this step's coefficients and column j-1 of R
+      double n0 = 0.0, e_prev = 0.0, force = 0.0, inv = 1.0, r = 1.0;
+      if (j >= 1) {
+        n0 = st_in[0];
+        e_prev = st_in[1];
+        force = st_in[2];
+        col_reduce(a.work + (par ^ 1) * bufsz, G, red, half);
       }
-      for (; h < G; h += Q) acc += in[(int64_t)h * kColSlots + slot];
-      tmp[q * ns + si] = acc;
-    }
-    __syncthreads();
-    if (tid < ns) {
-      double s = 0.0;
-      for (int k = 0; k < Q; ++k) s += tmp[k * ns + tid];
-      red[tid < nd ? rlo + tid : kSlotNA + (tid - nd)] = s;
-    }
-  }
-  __syncthreads();
-  // r from a squared norm; a zero or non-finite norm flags the panel as
-  // exactly rank-deficient and leaves the column unnormalised
-  auto diag = [&](double r2) {
-    if (!(r2 > 0.0) || !isfinite(r2)) {
-      if (lead && a.info[0] == 0) a.info[0] = 1 + a.panel;
-      r2 = 1.0;
-    }
-    return sqrt(r2);
-  };
-
-  if constexpr (kind == CG_FINISH) {
-    // r of the last column, which is normalised; zeros below R's diagonal
-    const double r = diag(a.mode == COLWISE_MGS ? red[kSlotNA] : (st2 != 0.0 ? red[kSlotNC] : st1));
-    const double inv = 1.0 / r;
-    if (lead) a.Rout[(w - 1) + (int64_t)(w - 1) * a.ldr] = r;
-    if (g == 0)
-      for (int e = tid; e < w * w; e += kColThreads) {
-        const int i = e % w, c = e / w;
-        if (i > c) a.Rout[i + (int64_t)c * a.ldr] = 0.0;
-      }
-    for (int it = 0; it < nit; ++it) {
-      const int64_t r = r0 + (int64_t)it * kColThreads + tid;
-      if (it > 0) colgrid_load_row(v, x0, x1, P, r0, ld, r, r < r1, lo, hi, e0, e1);
-      if (r < r1) P[r + (w - 1) * ld] = x0 * inv;
-    }
-  } else {
-    // this step's coefficients, decision and R entries
-    double inv = 1.0;
-    bool second = false;
-    if constexpr (kind == CG_PROJECT) {
-      if (j > 0) {
-        const double r = diag(st2 != 0.0 ? red[kSlotNC] : st1);
+      if (j >= 2) {
+        r = col_diag(a, red[kSlotN], lead);
         inv = 1.0 / r;
-        if (lead) a.Rout[(j - 1) + (int64_t)(j - 1) * a.ldr] = r;
       }
-      if (tid < j) coef[tid] = tid == j - 1 ? red[tid] * inv : red[tid];
-      __syncthreads();
-      if (g == 0) {
-        if (tid < j) a.Rout[tid + (int64_t)j * a.ldr] = coef[tid];
-        if (tid == 0) state[0] = red[kSlotNA];
-      }
-    } else if constexpr (kind == CG_REORTH) {
-      const double n1 = red[kSlotNB];
-      second = j > 0 && (a.mode == COLWISE_CGS2 || n1 < a.eta * a.eta * st0);
-      if (second && tid < j) coef[tid] = red[tid];
-      __syncthreads();
-      if (g == 0) {
-        if (second && tid < j) a.Rout[tid + (int64_t)j * a.ldr] += coef[tid];
-        if (tid == 0) {
-          state[1] = n1;
-          state[2] = second ? 1.0 : 0.0;
+      const double n1 = red[kSlotW];
+      second = haw && j >= 2 && (a.mode == COLWISE_CGS2 || force != 0.0 || n1 < a.eta * a.eta * n0);
+      if (wave == 0) {
+        // (slots from nq on hold nothing)
+        const double s = lane == nq - 1 ? inv : 1.0;
+        const double ai = second && lane < nq ? red[lane] * s : 0.0, ti = hap && lane < nq ? red[kSlotT + lane] * s : 0.0;
+        ca[lane] = ai;
+        ct[lane] = ti;
+        cs[lane] = s;
+        const double aa = wave_sum(ai * ai), at = wave_sum(ai * ti);
+        if (lane == 0) {
+          s_aa = aa;
+          s_at = at;
+        }
+        if (g == 0 && lane < nq) {
+          double* Rc = a.Rout + (int64_t)(j - 1) * a.ldr + lane;
+          if (haw) *Rc = (lane == nq - 1 ? e_prev * r : *Rc) + ai;   // first projection (the step before's), second
+          if (hap) Rc[a.ldr] = ti;
+          if (lane == nq - 1) Rc[-a.ldr] = r;                        // (row and column j - 2)
         }
       }
-    } else if constexpr (kind == CG_MGS) {
-      if (j > 0) {
-        const double r = diag(red[kSlotNA]);
-        inv = 1.0 / r;
-        if (tid >= j && tid < w) coef[tid] = red[tid] * inv;
-        if (lead) a.Rout[(j - 1) + (int64_t)(j - 1) * a.ldr] = r;
-      }
       __syncthreads();
-      if (g == 0 && j > 0 && tid >= j && tid < w) a.Rout[(j - 1) + (int64_t)tid * a.ldr] = coef[tid];
+      const bool both = haw && hap;
+      const double w2 = n1 - s_aa;
+      e = both && !(w2 <= 0.0) ? (red[kSlotU] - s_at) / w2 : 0.0;
+      if (lead) {
+        st_out[0] = j >= 1 ? red[kSlotP] : 0.0;      // ||p_j||^2 before its first projection
+        st_out[1] = e;
+        st_out[2] = both && second && !(s_aa <= 0.5 * n1) ? 1.0 : 0.0;
+      }
     }
+    if (!act) {
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = 0.0;
+      xw = xp = xn = 0.0;
+    }
+    double s = 0.0, t = 0.0, qn = 0.0;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      v[c] *= cs[c0 + c];
+      qn = c == kn ? v[c] : qn;
+      s += v[c] * ca[c0 + c];
+      t += v[c] * ct[c0 + c];
+    }
+    if (rr > r0) __syncthreads();   // the block before is done with the sums
+    sums[0][wave][lane] = s;
+    sums[1][wave][lane] = t;
+    __syncthreads();                // (and every wave has read the columns stored below)
+    s = sums[0][0][lane] + sums[0][1][lane] + sums[0][2][lane] + sums[0][3][lane];
+    t = sums[1][0][lane] + sums[1][1][lane] + sums[1][2][lane] + sums[1][3][lane];
+    const double wf = xw - s, pf = xp - t - wf * e;
+    if (act) {
+      if (kn >= 0 && kn < 16) P[row + (nq - 1) * ld] = qn;
+      if (wave == 0) {
+        if (second) P[row + (j - 1) * ld] = wf;
+        if (hap && j >= 1) P[row + j * ld] = pf;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+      const double x = c == kw ? wf : v[c];
+      acca[c] += x * pf;
+      acct[c] += x * xn;
+    }
+    sw += pf * pf;
+    su += pf * xn;
+    sp += xn * xn;
+    sn += wf * wf;
+  }
+  // this workgroup's partial sums
+  if (hap && kw >= 0) {
+    const double x = colwise_wave_sum16(acca), y = colwise_wave_sum16(acct);
+    if (lane < 16) {
+      out[c0 + lane] = x;
+      out[kSlotT + c0 + lane] = y;
+    }
+  }
+  const double x = wave_sum(wave == 0 ? sw : wave == 1 ? su : wave == 2 ? sp : sn);
+  if (lane == 0) out[kSlotW + wave] = x;
+  // after the last step: zeros below R's diagonal
+  if (j == w + 1 && g == 0)
+    for (int q = tid; q < w * w; q += kColThreads)
+      if (q % w > q / w) a.Rout[q % w + (int64_t)(q / w) * a.ldr] = 0.0;
+}
 
-    double total = 0.0;   // threads < kColSlots: this workgroup's sum for slot tid
-    for (int it = 0; it < nit; ++it) {
-      const int64_t r = r0 + (int64_t)it * kColThreads + tid;
-      const bool act = r < r1;
-      if (it > 0) colgrid_load_row(v, x0, x1, P, r0, ld, r, act, lo, hi, e0, e1);
-      double na = 0.0, nb = 0.0, nc = 0.0;
-      if constexpr (kind == CG_START) {
-        na = x0 * x0;
-      } else if constexpr (kind == CG_PROJECT) {
-        // column j-1 normalised; p_j -= P[:, <j] s1; ||p_j||^2; P[:, <j]^T p_j
-        double x = x0;
-        if (j > 0) {
-          const double qp = x1 * inv;
-          if (act) P[r + (j - 1) * ld] = qp;
+// MGS step i (0 <= i <= w)
+__global__ __launch_bounds__(kColThreads) void colmgs_kernel(ColArgs a, int G, int64_t rb, int i, int par) {
+  __builtin_amdgcn_s_setprio(2);   // panel chain
+  __shared__ double red[kColSlots], half[128];
+  __shared__ double coef[kLeaf];          // r_{i-1,c} of the columns c in [i, w), zero elsewhere
+  __shared__ double su[2][64];            // u_i of the row block
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = blockIdx.x;
+  const int w = a.w, c0 = 16 * wave;
+  const int64_t ld = a.ldp;
+  double* const P = a.P;
+  const int64_t r0 = (int64_t)g * rb, r1 = min(a.mrows, r0 + rb);
+  const int64_t bufsz = (int64_t)kColGridMax * kColSlots;
+  double* out = a.work + par * bufsz + (int64_t)g * kColSlots;
+  const bool lead = g == 0 && tid == 0;
+  const bool mine = c0 + 16 > i;          // some of the wave's columns are still to be orthogonalised
+  const int ki = i - c0;                  // column i in the wave's registers (if 0 .. 15)
+  double inv = 1.0;
+  double acc[16], sn = 0.0;
 #pragma unroll
-          for (int c = 0; c < kLeaf; ++c)
-            if (c + 1 == j) v[c] = qp;
-        }
-#pragma unroll
-        for (int c = 0; c < kLeaf; ++c) x -= v[c] * coef[c];
-        if (act) P[r + j * ld] = x;
-        nb = x * x;
-#pragma unroll
-        for (int c = 0; c < kLeaf; ++c) v[c] *= x;
-      } else if constexpr (kind == CG_REORTH) {
-        double x = x0;
-        const double y = x1;
-        if (second) {
-#pragma unroll
-          for (int c = 0; c < kLeaf; ++c) x -= v[c] * coef[c];
-          if (act) P[r + j * ld] = x;
-          nc = x * x;
-        }
-        // the next column's first projection: P[:, <=j]^T p_{j+1}, ||p_{j+1}||^2
-        na = y * y;
-#pragma unroll
-        for (int c = 0; c < kLeaf; ++c) v[c] = c == j ? x * y : v[c] * y;
-      } else {   // CG_MGS
-        // q_{j-1} = u_{j-1} / r; u_c -= r_{j-1,c} q_{j-1} for c >= j;
-        // ||u_j||^2 and u_j^T u_c for c > j
-        double u = x0;
-        if (j > 0) {
-          const double q = x1 * inv;
-          if (act) P[r + (j - 1) * ld] = q;
-          u -= coef[j] * q;
-          const uint32_t off = act ? (uint32_t)(r - r0) * 8u : 0u;
-          char* const wslab = reinterpret_cast<char*>(P + r0);
-#pragma unroll
-          for (int c = 0; c < kLeaf; ++c) {
-            v[c] -= coef[c] * q;
-            if (act && c >= j && c < w) *reinterpret_cast<double*>(wslab + c * ld * 8 + off) = v[c];
-          }
-        }
-        na = u * u;
-#pragma unroll
-        for (int c = 0; c < kLeaf; ++c) v[c] *= u;
-      }
-      // workgroup sums of this row block (the chunks covering [wlo, whi),
-      // then the norms): every wavefront butterfly first, independent of one
-      // another, then one exchange through LDS; each slot's total adds the
-      // wavefronts in order, then the row blocks in order
-      double xs[kLeaf / kColChunk + 1];
-#pragma unroll
-      for (int k = 0; k < kLeaf / kColChunk; ++k) {
-        xs[k] = 0.0;
-        if (whi > wlo && (k + 1) * kColChunk > wlo && k * kColChunk < whi) {
-          double v16[kColChunk];
-#pragma unroll
-          for (int c = 0; c < kColChunk; ++c) v16[c] = v[k * kColChunk + c];
-          xs[k] = colwise_wave_sum16(v16);
-        }
-      }
-      {
-        double n16[kColChunk];
-#pragma unroll
-        for (int c = 0; c < kColChunk; ++c) n16[c] = 0.0;
-        n16[0] = na;
-        n16[1] = nb;
-        n16[2] = nc;
-        xs[kLeaf / kColChunk] = colwise_wave_sum16(n16);
-      }
-      const int wave = tid >> 6, lane = tid & 63;
-      if (lane < kColChunk) {
-#pragma unroll
-        for (int k = 0; k <= kLeaf / kColChunk; ++k) wsum[wave][k * kColChunk + lane] = xs[k];
-      }
-      __syncthreads();
-      if (tid < kColSlots) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int q = 0; q < kColThreads / 64; ++q) sacc += wsum[q][tid];
-        total += sacc;
-      }
-      __syncthreads();
+  for (int c = 0; c < 16; ++c) acc[c] = 0.0;
+  for (int64_t rr = r0; rr < r1; rr += 64) {
+    const int64_t row = min(rr + lane, r1 - 1);
+    const bool act = rr + lane < r1;
+    double v[16];
+    col_load(v, P, ld, row, c0, mine ? w - c0 : 0, w);
+    double xq = i > 0 ? P[row + (i - 1) * ld] : 0.0;
+    if (rr == r0 && i > 0) {
+      col_reduce(a.work + (par ^ 1) * bufsz, G, red, half);
+      const double r = col_diag(a, red[kSlotW], lead);
+      inv = 1.0 / r;
+      if (lead) a.Rout[(i - 1) + (int64_t)(i - 1) * a.ldr] = r;
+      if (tid < kLeaf) coef[tid] = tid >= i && tid < w ? red[tid] * inv : 0.0;
+      if (g == 0 && tid >= i && tid < w) a.Rout[(i - 1) + (int64_t)tid * a.ldr] = red[tid] * inv;
     }
-    const int k = tid / kColChunk;
-    const bool chunk = whi > wlo && (k + 1) * kColChunk > wlo && k * kColChunk < whi && tid < kLeaf;
-    if (chunk || (tid >= kSlotNA && tid <= kSlotNC)) out[tid] = total;
+    if (!act) {
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = 0.0;
+      xq = 0.0;
+    }
+    __syncthreads();                // the coefficients; every wave has read column i - 1
+    if (i > 0) {
+      const double q = xq * inv;
+      if (act && wave == 0) P[row + (i - 1) * ld] = q;
+      if (mine) {
+        double* p = P + row + c0 * ld;
+#pragma unroll
+        for (int c = 0; c < 16; ++c, p += ld) {
+          v[c] -= coef[c0 + c] * q;
+          if (act && c >= ki && c0 + c < w) *p = v[c];
+        }
+      }
+    }
+    if (i < w) {
+      double u = 0.0;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) u = c == ki ? v[c] : u;
+      const int buf = (rr - r0) >> 6 & 1;
+      if (ki >= 0 && ki < 16) su[buf][lane] = u;
+      __syncthreads();
+      u = su[buf][lane];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) acc[c] += v[c] * u;
+      sn += u * u;
+    }
+  }
+  if (i < w) {
+    if (mine) {
+      const double x = colwise_wave_sum16(acc);
+      if (lane < 16) out[c0 + lane] = x;
+    }
+    if (wave == 0) {
+      const double n = wave_sum(sn);
+      if (lane == 0) out[kSlotW] = n;
+    }
+  } else if (g == 0) {
+    for (int q = tid; q < w * w; q += kColThreads)
+      if (q % w > q / w) a.Rout[q % w + (int64_t)(q / w) * a.ldr] = 0.0;
   }
 }
 
-// The launches of one leaf: 2w + 2 for CGS2 / ICGS, w + 1 for MGS.  One row
-// per thread while the rows fit kColGridMax workgroups, more beyond.
+// The launches of one leaf: w + 2 for CGS2 / ICGS, w + 1 for MGS; whole row
+// blocks of 64 shared evenly by 32 or 64 workgroups (128 from 16384 rows on:
+// their sums are read by every workgroup of the next launch).  Workgroups left
+// without rows leave zeros.
 void launch_colpanel(const ColArgs& a, hipStream_t st) {
-  const int G = (int)std::min<int64_t>(kColGridMax, std::max<int64_t>(1, (a.mrows + kColThreads - 1) / kColThreads));
-  const int64_t rb = (a.mrows + G - 1) / G;
+  const int64_t blocks = (a.mrows + 63) / 64;
+  const int G = blocks <= 32 ? 32 : blocks <= 256 ? 64 : kColGridMax;
+  const int64_t per = (blocks + G - 1) / G;
   int par = 0;
-  auto go = [&](auto kern, int j) {
-    hipLaunchKernelGGL(kern, dim3(G), dim3(kColThreads), 0, st, a, G, rb, j, par);
-    par ^= 1;
-  };
-  if (a.mode == COLWISE_MGS) {
-    for (int i = 0; i < a.w; ++i) go(colgrid_kernel<CG_MGS>, i);
-  } else {
-    go(colgrid_kernel<CG_START>, 0);
-    for (int j = 0; j < a.w; ++j) {
-      go(colgrid_kernel<CG_PROJECT>, j);
-      go(colgrid_kernel<CG_REORTH>, j);
-    }
-  }
-  go(colgrid_kernel<CG_FINISH>, a.w - 1);
+  const bool mgs = a.mode == COLWISE_MGS;
+  for (int j = 0; j <= (mgs ? a.w : a.w + 1); ++j, par ^= 1)
+    if (mgs)
+      hipLaunchKernelGGL(colmgs_kernel, dim3(G), dim3(kColThreads), 0, st, a, G, 64 * per, j, par);
+    else
+      hipLaunchKernelGGL(colstep_kernel, dim3(G), dim3(kColThreads), 0, st, a, G, 64 * per, j, par);
 }
 
 CholArgs chol_args(const double* W, int64_t ldw, int w, int panel, const Scratch& s) {

@@ -196,15 +196,18 @@ void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st);
 void launch_panel_reduce(const PanelArgs& a, hipStream_t st);
 void launch_panel_second(const PanelArgs& a, hipStream_t st);
 
-// One panel leaf orthogonalised column by column (colgrid_kernel): the rows
-// are split over up to kColGridMax workgroups, and each launch takes one step
-// of the method on every slab, leaving per-workgroup partial sums (kColSlots
-// each) that every workgroup of the next launch reduces in the same order.
+// One panel leaf orthogonalised column by column (colstep_kernel,
+// colmgs_kernel): the rows are split over up to kColGridMax workgroups, and each
+// launch takes one step of the method on every slab, leaving per-workgroup
+// partial sums (kColSlots each) that every workgroup of the next launch reduces
+// in the same order.
 enum : int { COLWISE_CGS2 = 0, COLWISE_ICGS = 1, COLWISE_MGS = 2 };
-constexpr int kColGridMax = 256;
-constexpr int kColSlots = 68;       // 64 inner products, three squared norms, one spare
-// partial sums (two buffers, alternating by launch) and four state words
-constexpr int64_t kColWorkDoubles = 2 * (int64_t)kColGridMax * kColSlots + 4;
+constexpr int kColGridMax = 128;
+constexpr int kColSlots = 132;      // two sets of 64 inner products, four others
+// partial sums and state words, two buffers alternating by launch (colstep_kernel:
+// kColGridMax x kColSlots and four; colgrid_kernel: 256 x 68, and four in all)
+constexpr int64_t kColWorkDoubles = 2 * (256 * (int64_t)68 + 4);
+static_assert(kColGridMax * kColSlots <= 256 * 68, "scratch");
 struct ColArgs {
   double* P; int64_t ldp; int64_t mrows;
   int w, mode;                      // w <= kLeaf; mode: COLWISE_CGS2 / _ICGS / _MGS
@@ -214,6 +217,7 @@ struct ColArgs {
   double* work;                     // kColWorkDoubles of scratch
 };
 void launch_colpanel(const ColArgs& a, hipStream_t st);
+void launch_colgrid(const ColArgs& a, hipStream_t st);   // the reduced-precision modes
 
 CholArgs chol_args(const double* W, int64_t ldw, int w, int panel, const Scratch& s);
 
