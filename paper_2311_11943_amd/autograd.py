@@ -26,10 +26,19 @@ from . import cqr
 
 
 def _colmajor(t: torch.Tensor, rows: int, cols: int, device) -> torch.Tensor:
-    """Column-major FP64 copy of t (zeros when t is None)."""
-    out = cqr.col_major(rows, cols, device)
-    if t is not None:
-        out.copy_(t)
+    """t as a column-major FP64 matrix on the device, to be read only: t itself
+    where it is one (the cotangents the library's own backward passes on are),
+    else a copy; zeros when t is None."""
+    if t is None:
+        return cqr.col_major(rows, cols, device)
+    if (type(t) in (torch.Tensor, torch.nn.Parameter) and t.layout == torch.strided
+            and t.dtype == torch.float64 and t.device == device and tuple(t.shape) == (rows, cols)
+            and not (t.is_neg() or t._is_zerotensor())
+            and (rows == 1 or t.stride(0) == 1) and (cols == 1 or t.stride(1) >= rows)
+            and t.data_ptr() % 16 == 0):
+        return t
+    out = cqr._col_major_empty(rows, cols, device)
+    out.copy_(t)
     return out
 
 
@@ -37,7 +46,7 @@ def _factor(A, engine, schedule):
     """Encode A and factor it with the schedule's erasures and recoveries;
     returns the encoded matrix and R."""
     c = engine.cfg
-    At, R = engine.alloc()
+    At, R = engine._alloc_empty()
     At[:c.m, :c.n].copy_(A)
     engine.encode(At)
     k = 0
@@ -86,8 +95,8 @@ class CodedSolveFunction(torch.autograd.Function):
     def forward(ctx, Q, R1, B, engine):
         c = engine.cfg
         Bc = _colmajor(B, c.m, B.shape[1], Q.device)
-        Qpost = cqr.col_major(c.m, c.n, Q.device)
-        Bpost = cqr.col_major(c.m, B.shape[1], Q.device)
+        Qpost = cqr._col_major_empty(c.m, c.n, Q.device)
+        Bpost = cqr._col_major_empty(c.m, B.shape[1], Q.device)
         engine.postorth(Q, Qpost, Bc, Bpost)
         X = engine.solve(Qpost, R1, Bpost)
         ctx.engine = engine

@@ -147,6 +147,12 @@ def col_major(rows: int, cols: int, device, dtype=None):
     return torch.zeros((cols, rows), dtype=dt, device=device).t()
 
 
+def _col_major_empty(rows: int, cols: int, device):
+    """col_major without the zeros, for buffers that a call writes whole."""
+    import torch
+    return torch.empty((cols, rows), dtype=torch.float64, device=device).t()
+
+
 def to_device_colmajor(a: np.ndarray, device):
     """Copy a numpy matrix to the device in column-major layout."""
     import torch
@@ -391,6 +397,11 @@ class CodedQR:
         c = self.cfg
         return col_major(c.mp, c.N, self.device), col_major(self.r_rows, c.N, self.device)
 
+    def _alloc_empty(self):
+        """alloc() without A~'s zeros, for callers that copy A in and encode: the two write all of A~."""
+        c = self.cfg
+        return _col_major_empty(c.mp, c.N, self.device), col_major(self.r_rows, c.N, self.device)
+
     def encode(self, At):
         _check(coded_qr_encode(self.plan, At), "coded_qr_encode")
 
@@ -426,7 +437,7 @@ class CodedQR:
     def solve(self, Qpost, R, Bpost, X=None, ws=None):
         """X = R_1^{-1} Qpost^T Bpost (n x nrhs, column-major, on the device)."""
         nrhs = Bpost.shape[1]
-        X = col_major(self.cfg.n, nrhs, self.device) if X is None else X
+        X = _col_major_empty(self.cfg.n, nrhs, self.device) if X is None else X
         ws = self.solve_workspace(nrhs) if ws is None else ws
         _check(coded_qr_solve(self.plan, Qpost, R, Bpost, X, ws), "coded_qr_solve")
         return X
@@ -437,7 +448,7 @@ class CodedQR:
 
     def backward(self, Q, R, dQ, dR, dA=None):
         """dA (m x n) from the cotangents of Q~[:, :n] and R_1 (coded_qr_backward)."""
-        dA = col_major(self.cfg.m, self.cfg.n, self.device) if dA is None else dA
+        dA = _col_major_empty(self.cfg.m, self.cfg.n, self.device) if dA is None else dA
         ws = self._bytes_buffer(coded_qr_backward_workspace_bytes(self.plan))
         _check(coded_qr_backward(self.plan, Q, R, dQ, dR, dA, ws), "coded_qr_backward")
         return dA
@@ -445,9 +456,9 @@ class CodedQR:
     def solve_backward(self, Qpost, R, Bpost, X, dX):
         """(dQ~ (m' x n), dR_1 (n x n), dB (m x nrhs)) from dX (coded_qr_solve_backward)."""
         c = self.cfg
-        dQ = col_major(c.mp, c.n, self.device)
-        dR = col_major(c.n, c.n, self.device)
-        dB = col_major(c.m, X.shape[1], self.device)
+        dQ = _col_major_empty(c.mp, c.n, self.device)
+        dR = _col_major_empty(c.n, c.n, self.device)
+        dB = _col_major_empty(c.m, X.shape[1], self.device)
         ws = self._bytes_buffer(coded_qr_solve_backward_workspace_bytes(self.plan, X.shape[1]))
         _check(coded_qr_solve_backward(self.plan, Qpost, R, Bpost, X, dX, dQ, dR, dB, ws),
                "coded_qr_solve_backward")
@@ -457,7 +468,7 @@ class CodedQR:
         """encode -> factor with scheduled erasures/recoveries -> post-orth.
         A_dev: m x n column-major device tensor.  Returns (At, R, Qpost, Bpost)."""
         c = self.cfg
-        At, R = self.alloc()
+        At, R = self._alloc_empty()
         At[:c.m, :c.n].copy_(A_dev)
         self.encode(At)
         k = 0
@@ -470,8 +481,8 @@ class CodedQR:
             self.recover(At, R, nodes)
         Qpost = Bpost = None
         if c.kv > 0:
-            Qpost = col_major(c.m, c.n, self.device)
+            Qpost = _col_major_empty(c.m, c.n, self.device)
             if B is not None:
-                Bpost = col_major(c.m, B.shape[1], self.device)
+                Bpost = _col_major_empty(c.m, B.shape[1], self.device)
             self.postorth(At, Qpost, B, Bpost)
         return At, R, Qpost, Bpost
