@@ -388,6 +388,7 @@ void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B,
   cqr::TnArgs a = cqr::tn_setup(A, lda, B, ldb, M, N, K, C, ldc, C2, ldc2, s, 0, lowp);
   if (M2 >= 0) a.M2 = M2;
   a.seq = p.cfg.precision != CQR_FP64;
+  if (!a.seq) cqr::tn_small(a);
   a.prio = chain_phase(phase);
   const double fl = 2.0 * M * N * (double)K, by = 8.0 * ((double)K * M + (double)K * N);
   const double out = 8.0 * (double)M * N * (C2 ? 3.0 : 1.0);
@@ -405,6 +406,7 @@ void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B,
 void tn_lower(cqr_plan_s& p, const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
               int64_t ldc, const cqr::Scratch& s, hipStream_t st) {
   cqr::TnArgs a = cqr::tn_setup_lower(A, lda, B, ldb, N, K, C, ldc, s);
+  cqr::tn_small(a);
   a.prio = 1;
   const double share = a.lower ? 0.5 : 1.0;
   const double fl = share * 2.0 * N * N * (double)K, by = 16.0 * (double)K * N, out = share * 8.0 * (double)N * N;
@@ -469,6 +471,7 @@ cqr::TnArgs tn_early(cqr_plan_s& p, const double* X, int64_t ldx, const double* 
   const int tiles = (N + kTile - 1) / kTile;
   const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(kEarlyBlocks / tiles, p.mp / 256));
   cqr::TnArgs a = cqr::tn_setup(X, ldx, B, ldb, w, N, p.mp, s.part, w, nullptr, 0, s, ns, lowp);
+  if (p.cfg.precision == CQR_FP64) cqr::tn_small(a);
   a.prio = chain_phase(PH_TRAIL_TN);
   const double fl = 2.0 * w * N * (double)p.mp, by = 8.0 * (double)p.mp * ((double)w + N);
   const double out = a.nsplit > 1 ? partial_bytes(a.nsplit, a.ntiles) : 8.0 * (double)w * N;

@@ -1070,6 +1070,100 @@ __global__ __launch_bounds__(256) void tn_direct_kernel(TnArgs a) {
   tn_store(a, acc, tile, split, wave, lane, i0, j0, false);
 }
 
+// --------------------------------------------------------------------------
+// The same product where 64 x 64 tiles would leave the chip idle: a panel of a
+// small matrix has a few such tiles, and a depth too short to split, so a few
+// compute units would do all of the work behind their matrix cores (a 16-column
+// panel of 320 rows: 5 tiles of 10 slabs, 16 us, of which most is padding of
+// 16 columns to 64).  Here a workgroup forms 16 x 16 outputs and its 16 waves
+// share the depth, 16 k-values at a time in turn, straight from memory (the
+// operands of such products are in cache), two chunks ahead; the
+// waves' sums are added through LDS in order, so there are no partials and no
+// second launch.
+// --------------------------------------------------------------------------
+
+constexpr int kSmallWaves = 16;
+// A workgroup reads its 32 columns at some 40-70 GB/s, so the depth it can take
+// is short: at 2304 rows the split product and its reduction are as fast (one
+// tile: 17.4 us and 5 against 17.3), at 4608 faster (17.5 and 5 against 32.6).
+// From two workgroups per CU on the 64 x 64 tiles' fewer reads win (1386 rows x
+// 16 x 4096: 256 of them, 33 us against 12; x 64 x 4096: 33 against 43).
+constexpr int64_t kSmallDepth = 2048;
+constexpr int64_t kSmallGrid = 512;
+
+template <int TAG, bool VEC>
+__global__ __launch_bounds__(64 * kSmallWaves) void tns_kernel(TnArgs a) {
+  if (a.prio) __builtin_amdgcn_s_setprio(2);
+  __shared__ double red[kSmallWaves][4][64];
+  const int tilesM = (a.M + 15) / 16;
+  const int i0 = blockIdx.x % tilesM * 16, j0 = blockIdx.x / tilesM * 16;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // columns outside the matrix read column 0 and feed only unstored outputs
+  // lane group g holds k-values 2g, 2g + 1, 8 + 2g, 9 + 2g of a chunk: a load
+  // takes 64 contiguous bytes of each column
+  const double* pa = a.A + (int64_t)(i0 + li < a.M ? i0 + li : 0) * a.lda + 2 * g;
+  const double* pb = a.B + (int64_t)(j0 + li < a.N ? j0 + li : 0) * a.ldb + 2 * g;
+  const int nfull = (int)(a.K / 16);
+  const int mine = (nfull - wave + kSmallWaves - 1) / kSmallWaves;      // the wave's whole chunks
+  v4d acc = v4d{0, 0, 0, 0};
+  double x0[8], x1[8], y0[8], y1[8];
+  auto load = [&](double (&x)[8], int q) {
+    const int64_t k = 16 * (int64_t)(wave + q * kSmallWaves);
+    if constexpr (VEC) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const v2d u = *reinterpret_cast<const v2d*>(pa + k + 8 * h), v = *reinterpret_cast<const v2d*>(pb + k + 8 * h);
+        x[2 * h] = u.x; x[2 * h + 1] = u.y; x[4 + 2 * h] = v.x; x[5 + 2 * h] = v.y;
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        x[s] = pa[k + (s & 1) + 4 * (s & 2)];
+        x[4 + s] = pb[k + (s & 1) + 4 * (s & 2)];
+      }
+    }
+  };
+  auto mac = [&](const double (&x)[8]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = mfma(x[4 + s], x[s], acc);
+  };
+  if (mine > 0) load(x0, 0);
+  if (mine > 1) load(x1, 1);
+#pragma unroll 1
+  for (int q = 0; q < mine; q += 4) {
+    if (q + 2 < mine) load(y0, q + 2);
+    if (q + 3 < mine) load(y1, q + 3);
+    mac(x0);
+    if (q + 1 < mine) mac(x1);
+    if (q + 4 < mine) load(x0, q + 4);
+    if (q + 5 < mine) load(x1, q + 5);
+    if (q + 2 < mine) mac(y0);
+    if (q + 3 < mine) mac(y1);
+  }
+  if (const int64_t k0 = 16 * (int64_t)nfull; k0 < a.K && wave == nfull % kSmallWaves) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int64_t k = k0 + (s & 1) + 4 * (s & 2);
+      const bool in = k + 2 * g < a.K;
+      x0[s] = in ? pa[k] : 0.0;
+      x0[4 + s] = in ? pb[k] : 0.0;
+    }
+    mac(x0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[r];
+  __syncthreads();
+  if (tid >= 256) return;
+  const int i = i0 + li, j = j0 + 4 * wave + g;              // element r = wave of the waves' accumulators
+  double v = 0.0;
+#pragma unroll
+  for (int e = 0; e < kSmallWaves; ++e) v += red[e][wave][lane];
+  if (i >= a.M || j >= a.N) return;
+  a.C[i + (int64_t)j * a.ldc] = v;
+  if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] += v;
+}
+
 // Sum the split partials in split order; write C (and C2 +=).  A workgroup of G
 // groups of 64 threads takes U of a wave quadrant's 16 element slots per lane;
 // each group sums a contiguous range of the splits and the groups' sums are
@@ -1229,10 +1323,12 @@ TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int 
 TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
                       int64_t ldc, const Scratch& s) {
   const int t = (N + 2 * kTile - 1) / (2 * kTile), tiles = (N + kTile - 1) / kTile;
-  // (at least 1024 rows a split: its partials then take an eighth of the bytes
-  // of its operands)
-  const int ns = (int)std::min<int64_t>(pick_split_quad(t * (t + 1) / 2, K, s.npart, tiles * tiles),
-                                        std::max<int64_t>(1, K / 1024));
+  // (at least 1024 rows a split where that fills the GPU: its partials then take
+  // an eighth of the bytes of its operands.  One block of 2304 rows in two
+  // splits left all but two CUs idle: 155 us, 20 in nine.)
+  const int blocks = t * (t + 1) / 2;
+  const int ns = (int)std::min<int64_t>(pick_split_quad(blocks, K, s.npart, tiles * tiles),
+                                        std::max<int64_t>((512 + blocks - 1) / blocks, K / 1024));
   TnArgs a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s);
   if (!a.quad) return a;
   a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s, ns);
@@ -1240,8 +1336,39 @@ TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb
   return a;
 }
 
+bool tn_small(TnArgs& a) {
+  const int64_t wgs = ((int64_t)a.M + 15) / 16 * ((a.N + 15) / 16);
+  if (a.f32 || a.bf3 || a.K > kSmallDepth || wgs > kSmallGrid) return false;
+  a.small = 1;
+  a.nsplit = 1;
+  a.lower = 0;
+  return true;
+}
+
+template <bool VEC>
+static void launch_tns_as(const TnArgs& a, dim3 grid, int tag, hipStream_t st) {
+  const dim3 threads(64 * kSmallWaves);
+  switch (tag) {
+    case TAG_TRAIL: hipLaunchKernelGGL((tns_kernel<TAG_TRAIL, VEC>), grid, threads, 0, st, a); break;
+    case TAG_REPROJ: hipLaunchKernelGGL((tns_kernel<TAG_REPROJ, VEC>), grid, threads, 0, st, a); break;
+    default: hipLaunchKernelGGL((tns_kernel<TAG_PANEL, VEC>), grid, threads, 0, st, a); break;
+  }
+}
+
+static void launch_tns(const TnArgs& a, dim3 grid, int tag, hipStream_t st) {
+  if (a.vec)
+    launch_tns_as<true>(a, grid, tag, st);
+  else
+    launch_tns_as<false>(a, grid, tag, st);
+}
+
 void launch_tn_product(const TnArgs& a, int tag, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return;
+  if (a.small) {
+    const dim3 grids((unsigned)((a.M + 15) / 16 * ((a.N + 15) / 16)));
+    launch_tns(a, grids, tag, st);
+    return;
+  }
   const dim3 grid(a.ntiles, a.nsplit);
   if (!a.vec) {
     hipLaunchKernelGGL(tn_direct_kernel, grid, dim3(256), 0, st, a);

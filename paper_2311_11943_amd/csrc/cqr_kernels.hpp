@@ -114,6 +114,7 @@ struct TnArgs {
                       // 32 k-values, FP64 sums across them (output layout as f32)
   int seq;            // sum the splits one after the other, in one order for every count
   int lower;          // square product, 128 x 128 blocks above the diagonal left out (quad only)
+  int small;          // 16 x 16 outputs per workgroup, the depth shared by its waves (tns_kernel)
 };
 
 // Choose the split of C = A^T B (stored to C; rows below M2 -- all rows
@@ -129,6 +130,8 @@ TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int 
 // C = A^T B (N x N) of which only the lower triangle is read
 TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
                       int64_t ldc, const Scratch& s);
+// Turn a (FP64) into a product on tns_kernel, unsplit, if it is small enough.
+bool tn_small(TnArgs& a);
 // The product; with nsplit == 1 it stores C (and C2) itself, else partials.
 void launch_tn_product(const TnArgs& a, int tag, hipStream_t st);
 // Sum the partials into C (and C2) in split order (nsplit > 1 only).
