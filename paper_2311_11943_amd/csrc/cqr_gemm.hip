@@ -1468,40 +1468,54 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 // augmented [D | I] with each final row scaled by 1/sqrt(pivot), so D = R^T R
 // gives R (into Rl's block, zero below the diagonal) and T = R^{-1} (into
 // Tl's block).  Lanes 0..15 hold column tx of D, lanes 16..31 column tx of
-// the identity half, 16 rows in registers.  Step j: the D lanes publish row j
-// (by symmetry also column j) through LDS, every lane reads the pivot and the
-// column-j factors, and subtracts.  Only the wave's own LDS traffic orders the
-// steps (in-order LDS within a wave), so there is no block barrier.
+// the identity half, 16 rows in registers.  Step j: row j of D (by symmetry
+// also column j) lies in the D lanes' register j; every lane takes the pivot
+// and the column-j factors from there by readlane, and subtracts.  A serial
+// chain of 16 steps, bound by the latency of each: through LDS, with the
+// results stored as they came, a 64-column factorization took 31 us of its
+// kernel's 35, so 20 of 25.
 __device__ __forceinline__ void chol_diag16(int lane, int o, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                            double* prow, const double* dg, bool& bad) {
+                                            const double* dg, bool& bad) {
   const int tx = lane & 15;
   const bool dl = lane < 16, zl = lane >= 16 && lane < 32;
+  // lane l's value in every lane
+  auto from = [](double x, int l) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
   double c[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i)
     c[i] = dl ? ((i <= tx) ? Rl[o + i][o + tx] : Rl[o + tx][o + i]) : (zl && i == tx ? 1.0 : 0.0);
+  const double least = kCholBreak * dg[o + tx];
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
-    if (dl) prow[tx] = c[j];
-    __builtin_amdgcn_wave_barrier();
-    double piv = prow[j];
-    double fac[16];
-#pragma unroll
-    for (int i = j + 1; i < 16; ++i) fac[i] = prow[i];
-    __builtin_amdgcn_wave_barrier();
     // breakdown: a pivot that is not positive, or below kCholBreak times the
     // column's diagonal entry in the Gram matrix (the column lies within an
     // angle of 1e-7 of the span of the columns before it)
-    if (!(piv > kCholBreak * dg[o + j]) || !isfinite(piv)) {
-      bad = true;
-      piv = 1.0;
-    }
+    double piv = from(c[j], j);
+    const bool ok = piv > from(least, j) && isfinite(piv);
+    bad |= !ok;
+    piv = ok ? piv : 1.0;
     const double inv = rsqrt_nr(piv);
-    const double f = c[j] * inv * inv;
+    const double r = c[j] * inv, f = r * inv;
 #pragma unroll
-    for (int i = j + 1; i < 16; ++i) c[i] -= fac[i] * f;
-    if (dl) Rl[o + j][o + tx] = (tx >= j) ? c[j] * inv : 0.0;
-    if (zl) Tl[o + tx][o + j] = c[j] * inv;
+    for (int i = j + 1; i < 16; ++i) c[i] -= from(c[j], i) * f;
+    c[j] = r;
+    // (each step's updates before the next step: left to itself the compiler
+    // keeps the factors of all steps in scalar registers, spills them, and
+    // updates each row when it is needed, in one long chain)
+#pragma unroll
+    for (int i = j + 1; i < 16; ++i) asm volatile("" : "+v"(c[i]));
+  }
+  if (dl) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) Rl[o + j][o + tx] = (tx >= j) ? c[j] : 0.0;
+  } else if (zl) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) Tl[o + tx][o + j] = c[j];
   }
 }
 
@@ -1513,12 +1527,12 @@ __device__ __forceinline__ void chol_diag16(int lane, int o, double (*Rl)[kLeaf 
 // off-diagonal blocks, one block column per wave: T_ab = -T_aa sum_{c=a+1..b}
 // R_ac T_cb for a = b-1 down to 0.  About three block barriers per 16 columns.
 __device__ __forceinline__ void chol_blocked(int tid, int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                             double* prow, const double* dg, bool& bad) {
+                                             const double* dg, bool& bad) {
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
 #pragma unroll 1
   for (int b = 0; b < nb; ++b) {
     const int o = 16 * b;
-    if (wave == 0) chol_diag16(lane, o, Rl, Tl, prow, dg, bad);
+    if (wave == 0) chol_diag16(lane, o, Rl, Tl, dg, bad);
     __syncthreads();
     if (b + 1 == nb) break;
     // row panel R_bc = T_bb^T W_bc, in place
@@ -1570,25 +1584,24 @@ __device__ __forceinline__ void chol_blocked(int tid, int nb, double (*Rl)[kLeaf
   __syncthreads();
 }
 
-// C = op(A) B for 64 x 64 LDS matrices (row-major, padded): op(A) = A, or
-// A^T when TRANS_A.  UPPER: A and B upper triangular (C[i][j] needs only
-// k in [i, j]; k blocks left of the row block are skipped).  Wave v computes
-// rows 16v..16v+15 and stores C[i][j] (i < w, j < wc) into the column-major
-// global matrix out (ld ldo).
-template <bool TRANS_A, bool UPPER>
+// C = A B for upper triangular w x w LDS matrices (row-major, 64 x 64 with
+// identity padding; C[i][j] needs only k in [i, j]: k blocks left of the row
+// block are skipped).  Wave v computes rows 16v..16v+15 and stores C into the
+// column-major global matrix out (ld ldo).
 __device__ __forceinline__ void lds_mm_store(int tid, const double (*Al)[kLeaf + 1], const double (*Bl)[kLeaf + 1],
-                                             int w, int wc, double* out, int64_t ldo) {
+                                             int w, double* out, int64_t ldo) {
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
   v4d acc[4];
 #pragma unroll
   for (int y = 0; y < 4; ++y) acc[y] = v4d{0, 0, 0, 0};
-  for (int k0 = UPPER ? 16 * wave : 0; k0 < kLeaf; k0 += 16) {
+  for (int k0 = 16 * wave; k0 < w; k0 += 16) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int k = k0 + 4 * g + s;
-      const double xa = TRANS_A ? Al[k][16 * wave + li] : Al[16 * wave + li][k];
+      const double xa = Al[16 * wave + li][k];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[y] = mfma(Bl[k][16 * y + li], xa, acc[y]);
+      for (int y = 0; y < 4; ++y)
+        if (16 * y < w) acc[y] = mfma(Bl[k][16 * y + li], xa, acc[y]);
     }
   }
   const int i = 16 * wave + li;
@@ -1597,7 +1610,7 @@ __device__ __forceinline__ void lds_mm_store(int tid, const double (*Al)[kLeaf +
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int j = 16 * y + 4 * r + g;
-      if (i < w && j < wc) out[i + (int64_t)j * ldo] = acc[y][r];
+      if (i < w && j < w) out[i + (int64_t)j * ldo] = acc[y][r];
     }
 }
 
@@ -1704,24 +1717,26 @@ void launch_tn_reduce_tmul(const TnArgs& a, const double* T, int w, double* out,
 
 // acc = T^T X with T (64 x 64, upper triangular, row-major LDS): wave v forms
 // rows 16v..16v+15, acc[y][r] = (T^T X)[16v + li][16y + 4r + g].  (T^T)[i][k] =
-// T[k][i] vanishes for k > i.  X(k, j): X's entries.
-template <class FX>
-__device__ __forceinline__ void tmul(int tid, const double (*Tl)[kLeaf + 1], v4d (&acc)[4], FX X) {
+// T[k][i] vanishes for k > i.  X(k, j): X's entries, of which the first NB
+// 16-row and 16-column blocks count.
+template <int NB, class FX>
+__device__ __forceinline__ void tmul(int tid, const double (*Tl)[kLeaf + 1], v4d (&acc)[NB], FX X) {
   const int wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int y = 0; y < 4; ++y) acc[y] = v4d{0, 0, 0, 0};
+  for (int y = 0; y < NB; ++y) acc[y] = v4d{0, 0, 0, 0};
+  if (wave >= NB) return;
 #pragma unroll 1
   for (int c = 0; c <= wave; ++c) {
-    double xb[4][4];
+    double xb[4][NB];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) xb[s][y] = X(16 * c + 4 * g + s, 16 * y + li);
+      for (int y = 0; y < NB; ++y) xb[s][y] = X(16 * c + 4 * g + s, 16 * y + li);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const double xa = Tl[16 * c + 4 * g + s][16 * wave + li];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[y] = mfma(xb[s][y], xa, acc[y]);
+      for (int y = 0; y < NB; ++y) acc[y] = mfma(xb[s][y], xa, acc[y]);
     }
   }
 }
@@ -1769,14 +1784,15 @@ __device__ __attribute__((noinline)) bool chol_fallback(const PanelArgs& a, doub
 
 // W (w x w Gram matrix, ld ldw) into Rl, identity-padded, Tl the identity, dg
 // the diagonal; true if some entry is further than 1e-8 from the identity's.
-// flag: a word of LDS.
+// flag: a word of LDS.  NB: the 16-column blocks that W has.
+template <int NB = 4>
 __device__ __forceinline__ bool gram_load(int tid, const double* W, int64_t ldw, int w, double (*Rl)[kLeaf + 1],
                                           double (*Tl)[kLeaf + 1], double* dg, int* flag) {
   const int tx = tid & 63, ty = tid >> 6;
   if (tid == 0) *flag = 0;
-  double v[16];
+  double v[4 * NB];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
+  for (int q = 0; q < 4 * NB; ++q) {
     const int k = ty + 4 * q;   // column (outside W: entry (0, 0), not used)
     const bool in = tx < w && k < w;
     v[q] = W[in ? tx + (int64_t)k * ldw : 0];
@@ -1785,7 +1801,7 @@ __device__ __forceinline__ bool gram_load(int tid, const double* W, int64_t ldw,
   __syncthreads();
   bool far = false;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
+  for (int q = 0; q < 4 * NB; ++q) {
     const int k = ty + 4 * q;
     const double id = tx == k ? 1.0 : 0.0;
     Rl[tx][k] = v[q];
@@ -1802,10 +1818,12 @@ __device__ __forceinline__ bool gram_load(int tid, const double* W, int64_t ldw,
 // kernels that call it: they run beside products of 128 registers whose
 // workgroups leave 256 a lane when they end, and a kernel that needs more waits
 // for a product's whole grid.
-__device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                                     double* prow, const double* dg) {
+// (The LDS arrays go by LDS pointers: by generic ones every access would test
+// for null and add 64-bit addresses.)
+typedef __attribute__((address_space(3))) double lds_double;
+__device__ __attribute__((noinline)) bool chol_exact(int nb, lds_double* Rl, lds_double* Tl, lds_double* dg) {
   bool bad = false;
-  chol_blocked(threadIdx.x, nb, Rl, Tl, prow, dg, bad);
+  chol_blocked(threadIdx.x, nb, (double (*)[kLeaf + 1])(double*)Rl, (double (*)[kLeaf + 1])(double*)Tl, (double*)dg, bad);
   return bad;
 }
 
@@ -1813,24 +1831,24 @@ __device__ __attribute__((noinline)) bool chol_exact(int nb, double (*Rl)[kLeaf 
 // left in Rl and Tl).  Breakdown (a pivot at most kCholBreak times its diagonal
 // entry): R1 = T = I, so the transform leaves the panel as it is, and info[1]
 // tells the second pass.  store: write R1 (and T, if a.T) and info[1].
-template <bool INLINE>
+template <bool INLINE, int NB = 4>
 __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf + 1], double (*Tl)[kLeaf + 1],
-                                           double* prow, double* dg, int* flag, bool store) {
+                                           double* dg, int* flag, bool store) {
   const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6, w = a.w;
-  gram_load(tid, a.W, a.ldw, w, Rl, Tl, dg, flag);
+  gram_load<NB>(tid, a.W, a.ldw, w, Rl, Tl, dg, flag);
   __syncthreads();
   if (tid == 0) *flag = 0;
   bool bad = false;
   if (INLINE)
-    chol_blocked(tid, (w + 15) / 16, Rl, Tl, prow, dg, bad);      // (barriers inside)
+    chol_blocked(tid, (w + 15) / 16, Rl, Tl, dg, bad);      // (barriers inside)
   else
-    bad = chol_exact((w + 15) / 16, Rl, Tl, prow, dg);
+    bad = chol_exact((w + 15) / 16, (lds_double*)&Rl[0][0], (lds_double*)&Tl[0][0], (lds_double*)dg);
   if (bad) *flag = 1;
   __syncthreads();
   const bool broke = *flag != 0;
   if (broke) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4 * NB; ++q) {
       const int k = ty + 4 * q;
       Rl[tx][k] = Tl[tx][k] = (tx == k) ? 1.0 : 0.0;
     }
@@ -1838,7 +1856,7 @@ __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf
   }
   if (!store) return;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
+  for (int q = 0; q < 4 * NB; ++q) {
     const int k = ty + 4 * q;
     if (tx < w && k < w) {
       if (a.T) a.T[tx + k * w] = Tl[tx][k];
@@ -1861,9 +1879,11 @@ __device__ __forceinline__ void chol_first(const CholArgs& a, double (*Rl)[kLeaf
 // factorization ran beside the split update, nn_chol_kernel).
 // (gpart == nullptr: the transform alone, for the modes that form the Gram
 // product by itself.)
-// Latency-bound: 16-row strips let a short panel fill many workgroups.  FULL:
-// w = 64, no column masks; NEXT: with Q_next.
-template <bool CHOL, bool FULL, bool NEXT>
+// Latency-bound: 16-row strips let a short panel fill many workgroups.  NB: the
+// 16-column blocks that the panel's columns fill (the others are left out: 1386
+// x 16 with CHOL 9.3 us, 16.0 with all four; x 35 19.3, 28.8);
+// FULL: w = 64, no column masks; NEXT: with Q_next.
+template <bool CHOL, int NB, bool FULL, bool NEXT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void panel_first_kernel(PanelArgs a) {
   __builtin_amdgcn_s_setprio(2);   // panel chain
   __shared__ double sT[kLeaf][kLeaf + 1];
@@ -1872,7 +1892,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // that runs beside leaves when it ends.)
   __shared__ double sR[CHOL ? kLeaf : (NEXT ? 32 : 16)][kLeaf + 1];
   double (*sP)[kLeaf + 1] = sR, (*sQ)[kLeaf + 1] = sR + 16;
-  __shared__ double prow[16];
   __shared__ double dg[kLeaf];
   __shared__ int flag;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, g = lane >> 4;
@@ -1899,17 +1918,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   if ((int)blockIdx.x < strips) load(blockIdx.x);
   if constexpr (CHOL) {
-    chol_first<false>(a.c, sR, sT, prow, dg, &flag, blockIdx.x == 0);
+    chol_first<false, NB>(a.c, sR, sT, dg, &flag, blockIdx.x == 0);
     __syncthreads();
   } else {
-    double tv[16];
+    double tv[4 * NB];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4 * NB; ++q) {
       const int e = tid + 256 * q, k = e & 63, j = e >> 6;
       tv[q] = (k < w && j < w) ? a.T[k + j * w] : 0.0;
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4 * NB; ++q) {
       const int e = tid + 256 * q;
       sT[e & 63][e >> 6] = tv[q];
     }
@@ -1941,12 +1960,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __builtin_amdgcn_sched_barrier(0);
     v4d acc = v4d{0, 0, 0, 0};
 #pragma unroll
-    for (int k0 = 0; k0 < kLeaf; k0 += 16)
+    for (int k0 = 0; k0 < 16 * NB; k0 += 16) {
+      if (wave >= NB) break;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int k = k0 + 4 * g + e;
         acc = mfma(sT[k][16 * wave + li], sP[li][k], acc);
       }
+    }
     __syncthreads();
     const int64_t i = (int64_t)s * 16 + li;
 #pragma unroll
@@ -1960,6 +1981,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     if (!a.gpart) continue;
     __syncthreads();
+    if (ia0 >= 16 * NB || jb0 >= 16 * NB) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = 4 * g + e;
@@ -1974,6 +1996,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
+          if (ia0 + 16 * x >= 16 * NB || jb0 + 16 * y >= 16 * NB) continue;
           gg[x][y] = mfma(xb[y], xa[x], gg[x][y]);
           if (NEXT) gq[x][y] = mfma(xq[y], xa[x], gq[x][y]);
         }
@@ -2001,20 +2024,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // plus half its diagonal) and T = I - F up to O(|E|^2), below rounding; where
 // E is larger, the exact factorization runs, in each workgroup the same.  That
 // costs less than a launch of one workgroup that the transform has to wait for.
-// The last workgroup takes no rows: it stores R_panel = R2 R1, Rbar and the
-// copy of T for the early update.
+// The last workgroup takes no rows: it stores R_panel = R2 R1 and the copy of T
+// for the early update.
 // Breakdown (flagged by the first pass, or a pivot here): the last workgroup
 // orthogonalises the panel column by column with CGS2 and updates Q_next, the
 // others leave it alone; R_panel = R_cgs2 R1, the panel is marked in a.fb for
 // the update that started from its first pass, and info[2] counts it.  Only a
 // panel that is exactly rank-deficient (a zero column after projection) sets
 // info[0].
-template <bool FULL, bool NEXT>
+// NB: the 16-column blocks that the panel's columns fill (the others are left
+// out: 1386 x 16 with Q_next 6.8 us, 17.0 with all four; x 35 12.9, 17.7), FULL:
+// w = 64 (15.4).
+template <int NB, bool FULL, bool NEXT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void panel_second_kernel(PanelArgs a) {
   __builtin_amdgcn_s_setprio(2);   // panel chain
   __shared__ double sT[kLeaf][kLeaf + 1];
   __shared__ double sB[kLeaf][kLeaf + 1];   // W and R2, then Rbar
-  __shared__ double prow[16];
   __shared__ double dg[kLeaf];
   __shared__ int flag, flag2;
   __shared__ ColwiseLds<256> L;
@@ -2027,58 +2052,56 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // the operand of product m: column 4 m + g, what the accumulators of the
   // transform hold for m = 4 y + r (NEXT), or 16 (m / 4) + 4 g + m % 4
   // (outside the panel: row or column 0, meeting zeros of T, or not stored)
-  double xa[16], cv[16];
+  double xa[4 * NB], cv[4 * NB];
   auto col = [&](int m) { return NEXT ? 4 * m + g : 16 * (m >> 2) + 4 * g + (m & 3); };
-  auto load = [&](double (&v)[16], const double* M, int tile) {
+  auto load = [&](double (&v)[4 * NB], const double* M, int tile) {
     const int64_t i = (int64_t)tile * 64 + 16 * wave + li, ic = i < a.mrows ? i : 0;
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
+    for (int m = 0; m < 4 * NB; ++m) {
       const int j = col(m);
       v[m] = M[ic + (j < w ? j : 0) * a.ldp];
     }
   };
-  auto mask = [&](double (&v)[16]) {
+  auto mask = [&](double (&v)[4 * NB]) {
     if (!FULL) {
 #pragma unroll
-      for (int m = 0; m < 16; ++m) v[m] = col(m) < w ? v[m] : 0.0;
+      for (int m = 0; m < 4 * NB; ++m) v[m] = col(m) < w ? v[m] : 0.0;
     }
   };
-  const double* Gn = a.Gn;
-  double xr[16];
-  if (!last) {
-    load(xa, a.P, blockIdx.x);
-    if (NEXT) {
+  double xr[4 * NB];      // Gn; in the last workgroup R1, identity-padded
+  if (!last) load(xa, a.P, blockIdx.x);
+  if (NEXT || last) {
+    const double* M = last ? a.c.R1 : a.Gn;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int k = ty + 4 * q;
-        const bool in = tx < w && k < w;
-        xr[q] = Gn[in ? tx + k * w : 0];
-        xr[q] = in ? xr[q] : 0.0;
-      }
+    for (int q = 0; q < 4 * NB; ++q) {
+      const int k = ty + 4 * q;
+      const bool in = tx < w && k < w;
+      xr[q] = M[in ? tx + k * w : 0];
+      xr[q] = in ? xr[q] : last && tx == k ? 1.0 : 0.0;
     }
   }
   const bool broke1 = a.c.info[1] != 0;
-  const bool far = gram_load(tid, a.G, w, w, sB, sT, dg, &flag);
+  const bool far = gram_load<NB>(tid, a.G, w, w, sB, sT, dg, &flag);
   if (tid == 0) flag2 = 0;
   __syncthreads();
   if (!far) {
-    double f[16];
+    double f[4 * NB];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4 * NB; ++q) {
       const int i = ty + 4 * q;
       const double e = sB[i][tx];
       f[q] = (i < tx) ? e : (i == tx ? 0.5 * (e - 1.0) : 0.0);
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 4 * NB; ++q) {
       const int i = ty + 4 * q;
       const double id = (i == tx) ? 1.0 : 0.0;
       sB[i][tx] = id + f[q];
       sT[i][tx] = id - f[q];
     }
   } else if (!broke1) {
-    if (chol_exact((w + 15) / 16, sB, sT, prow, dg)) flag2 = 1;
+    if (chol_exact(NB, (lds_double*)&sB[0][0], (lds_double*)&sT[0][0], (lds_double*)dg)) flag2 = 1;
   }
   __syncthreads();
   const bool fallback = broke1 || flag2 != 0;
@@ -2086,41 +2109,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (fallback) return;
     if (NEXT) {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) sB[tx][ty + 4 * q] = xr[q];
+      for (int q = 0; q < 4 * NB; ++q) sB[tx][ty + 4 * q] = xr[q];
       __syncthreads();
-      v4d rb[4];
+      v4d rb[NB];
       tmul(tid, sT, rb, [&](int k, int j) { return sB[k][j]; });
       __syncthreads();
 #pragma unroll
-      for (int y = 0; y < 4; ++y)
+      for (int y = 0; y < NB; ++y)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sB[16 * wave + li][16 * y + 4 * r + g] = rb[y][r];
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * wave + li, j = 16 * y + 4 * r + g;
+          sB[i][j] = rb[y][r];
+          if (blockIdx.x == 0 && i < w && j < w) a.Rbar[i + (int64_t)j * a.ldr] = rb[y][r];
+        }
     }
     __syncthreads();
     for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x - 1) {
       mask(xa);
       if (NEXT) load(cv, a.Qn, tile);         // used after the products
       __builtin_amdgcn_sched_barrier(0);
-      v4d pf[4], acc[4];
+      v4d pf[NB], acc[NB];
 #pragma unroll
-      for (int y = 0; y < 4; ++y) pf[y] = acc[y] = v4d{0, 0, 0, 0};
+      for (int y = 0; y < NB; ++y) pf[y] = acc[y] = v4d{0, 0, 0, 0};
 #pragma unroll
-      for (int m = 0; m < 16; ++m)
+      for (int m = 0; m < 4 * NB; ++m) {
 #pragma unroll
-        for (int y = 0; y < 4; ++y) pf[y] = mfma(sT[col(m)][16 * y + li], xa[m], pf[y]);
+        for (int y = 0; y < NB; ++y) pf[y] = mfma(sT[col(m)][16 * y + li], xa[m], pf[y]);
+      }
       if (tile + (int)gridDim.x - 1 < tiles) load(xa, a.P, tile + gridDim.x - 1);
       // the accumulators hold P[i][4 m + g] for m = 4 y + r: the operand of the
       // second product, lane for lane
       if (NEXT) {
 #pragma unroll
-        for (int m = 0; m < 16; ++m)
+        for (int m = 0; m < 4 * NB; ++m) {
 #pragma unroll
-          for (int y = 0; y < 4; ++y) acc[y] = mfma(sB[4 * m + g][16 * y + li], pf[m >> 2][m & 3], acc[y]);
+          for (int y = 0; y < NB; ++y) acc[y] = mfma(sB[4 * m + g][16 * y + li], pf[m >> 2][m & 3], acc[y]);
+        }
       }
       const int64_t i = (int64_t)tile * 64 + 16 * wave + li;
       if (i < a.mrows) {
 #pragma unroll
-        for (int y = 0; y < 4; ++y)
+        for (int y = 0; y < NB; ++y)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int j = 16 * y + 4 * r + g;
@@ -2133,13 +2162,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     return;
   }
-  // the last workgroup: R1 for R_panel = R2 R1, Rbar, T's copy
-  double r1v[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int k = ty + 4 * q;
-    r1v[q] = (tx < w && k < w) ? a.c.R1[tx + k * w] : (tx == k ? 1.0 : 0.0);
-  }
+  // the last workgroup: T's copy, R_panel = R2 R1
   bool rank_deficient = false;
   if (fallback) {
     rank_deficient = !chol_fallback(a, sB, &L);
@@ -2151,28 +2174,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   } else {
     if (a.Tcopy) {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
+      for (int q = 0; q < 4 * NB; ++q) {
         const int k = ty + 4 * q;
         if (tx < w && k < w) a.Tcopy[tx + k * w] = sT[tx][k];
       }
     }
-    if (NEXT) {
-      v4d rb[4];
-      tmul(tid, sT, rb, [&](int k, int j) { return k < w && j < w ? Gn[k + j * w] : 0.0; });
-#pragma unroll
-      for (int y = 0; y < 4; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * wave + li, j = 16 * y + 4 * r + g;
-          if (i < w && j < w) a.Rbar[i + (int64_t)j * a.ldr] = rb[y][r];
-        }
-    }
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 16; ++q) sT[tx][ty + 4 * q] = r1v[q];
+  for (int q = 0; q < 4 * NB; ++q) sT[tx][ty + 4 * q] = xr[q];
   __syncthreads();
-  lds_mm_store<false, true>(tid, sB, sT, w, w, a.Rout, a.ldr);
+  lds_mm_store(tid, sB, sT, w, a.Rout, a.ldr);
   if (tid == 0 && rank_deficient && a.c.info[0] == 0) a.c.info[0] = 1 + a.c.panel;
 }
 
@@ -2186,20 +2198,31 @@ int panel_first_blocks(int64_t mrows, bool gram) {
   return (int)((strips + per - 1) / per);
 }
 
-void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st) {
+template <bool CHOL, int NB, bool FULL>
+static void launch_panel_first_as(const PanelArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)panel_first_blocks(a.mrows, a.gpart != nullptr));
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
-  const bool full = a.w == kLeaf, next = a.Qn && a.gpart;
-  switch ((chol ? 4 : 0) | (full ? 2 : 0) | (next ? 1 : 0)) {
-    case 0: go(panel_first_kernel<false, false, false>); break;
-    case 1: go(panel_first_kernel<false, false, true>); break;
-    case 2: go(panel_first_kernel<false, true, false>); break;
-    case 3: go(panel_first_kernel<false, true, true>); break;
-    case 4: go(panel_first_kernel<true, false, false>); break;
-    case 5: go(panel_first_kernel<true, false, true>); break;
-    case 6: go(panel_first_kernel<true, true, false>); break;
-    default: go(panel_first_kernel<true, true, true>); break;
+  if (a.Qn && a.gpart)
+    hipLaunchKernelGGL((panel_first_kernel<CHOL, NB, FULL, true>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((panel_first_kernel<CHOL, NB, FULL, false>), grid, dim3(256), 0, st, a);
+}
+
+template <bool CHOL>
+static void launch_panel_first_w(const PanelArgs& a, hipStream_t st) {
+  if (a.w == kLeaf) return launch_panel_first_as<CHOL, 4, true>(a, st);
+  switch ((a.w - 1) / 16) {
+    case 0: return launch_panel_first_as<CHOL, 1, false>(a, st);
+    case 1: return launch_panel_first_as<CHOL, 2, false>(a, st);
+    case 2: return launch_panel_first_as<CHOL, 3, false>(a, st);
+    default: return launch_panel_first_as<CHOL, 4, false>(a, st);
   }
+}
+
+void launch_panel_first(const PanelArgs& a, bool chol, hipStream_t st) {
+  if (chol)
+    launch_panel_first_w<true>(a, st);
+  else
+    launch_panel_first_w<false>(a, st);
 }
 
 // The Gram partials of launch_panel_first summed into G (ld w; Gn from column
@@ -2215,16 +2238,24 @@ void launch_panel_reduce(const PanelArgs& a, hipStream_t st) {
   launch_tn_sum(t, st);
 }
 
-void launch_panel_second(const PanelArgs& a, hipStream_t st) {
+template <int NB, bool FULL>
+static void launch_panel_second_as(const PanelArgs& a, hipStream_t st) {
   const int64_t tiles = (a.mrows + 63) / 64;
   const int64_t per = (tiles + 254) / 255;
   const dim3 grid((unsigned)((tiles + per - 1) / per + 1));
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
-  const bool next = a.Qn != nullptr;
-  if (a.w == kLeaf) {
-    if (next) go(panel_second_kernel<true, true>); else go(panel_second_kernel<true, false>);
-  } else {
-    if (next) go(panel_second_kernel<false, true>); else go(panel_second_kernel<false, false>);
+  if (a.Qn)
+    hipLaunchKernelGGL((panel_second_kernel<NB, FULL, true>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((panel_second_kernel<NB, FULL, false>), grid, dim3(256), 0, st, a);
+}
+
+void launch_panel_second(const PanelArgs& a, hipStream_t st) {
+  if (a.w == kLeaf) return launch_panel_second_as<4, true>(a, st);
+  switch ((a.w - 1) / 16) {
+    case 0: return launch_panel_second_as<1, false>(a, st);
+    case 1: return launch_panel_second_as<2, false>(a, st);
+    case 2: return launch_panel_second_as<3, false>(a, st);
+    default: return launch_panel_second_as<4, false>(a, st);
   }
 }
 
@@ -2843,13 +2874,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                                                                                CholArgs c) {
   __builtin_amdgcn_s_setprio(2);
   __shared__ double smem[2 * NK * (64 + 1)];
-  __shared__ double prow[16];
   __shared__ double dg[kLeaf];
   __shared__ int flag;
   if ((int)blockIdx.x == a.ntiles) {
     if (blockIdx.y == 0)
       chol_first<true>(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
-                 reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), prow, dg, &flag, true);
+                 reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), dg, &flag, true);
     return;
   }
   nn_body<true, TAG_REPROJ>(a, reinterpret_cast<double (*)[NK][64 + 1]>(smem), blockIdx.x, blockIdx.y);
