@@ -373,6 +373,22 @@ constexpr int64_t kPairBytes = (int64_t)160 << 20;
 // Panels after a pair that take each of its panels' updates by itself.
 constexpr int kPairNear = 4;
 
+// Whether the next panel is factored beside the trailing update.  Where the
+// update is as short as the panel's own kernels that gains less than the two
+// streams' events and extra launches cost (us, with and without: 256 x 256, b =
+// 16: 1173, 739; 1024 x 1024, b = 32: 2429, 2135, b = 64: 1249, 1306; 1211 x
+// 1155, b = 35: 2526, 2439; 1536 x 1536, b = 32: 3737, 3948), and where few
+// panels follow there is little to run beside (16384 x 256, b = 64: 617, 585;
+// 65536 x 512, b = 64: 3393, 3482).  The reduced precisions keep the order that
+// their coefficients are rounded in.
+constexpr int64_t kAheadWork = 80 << 20;      // encoded elements x panel width
+constexpr int kAheadPanels = 6;
+bool looks_ahead(const cqr_plan_s& p) {
+  if (!p.cfg.lookahead) return false;
+  if (p.cfg.precision != CQR_FP64 || p.cfg.panel != CQR_PANEL_CHOLQR2) return true;
+  return p.mp * p.N * p.pw >= kAheadWork && p.N > kAheadPanels * (int64_t)p.pw;
+}
+
 // First tile of the Gram partials in the split-partial area: the split
 // re-projection update, whose partials are read by the launch that writes the
 // Gram partials, takes at most 512 tiles (nn_setup), the Gram partials at most
@@ -794,7 +810,7 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
   }
   // the call's columns; w: the width of all panels where it is a leaf's
   const int64_t w = p->pw, cb = pb * (int64_t)p->cfg.b, ce = pe * (int64_t)p->cfg.b;
-  const bool la = p->cfg.lookahead && ce - cb > panel_width(*p, cb) && side_ready(*p);
+  const bool la = looks_ahead(*p) && ce - cb > panel_width(*p, cb) && side_ready(*p);
   const hipStream_t caller = st;
   if (la) {
     // both lookahead streams start after everything already queued on the
