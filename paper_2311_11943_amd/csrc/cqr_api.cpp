@@ -436,6 +436,7 @@ void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64
         int64_t ldb, int64_t M, int N, int K, const cqr::Scratch& s, hipStream_t st) {
   if (M <= 0 || N <= 0 || K <= 0) return;
   cqr::NnArgs a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
+  if (p.cfg.precision == CQR_FP64) cqr::nn_small(a);
   a.prio = chain_phase(phase);
   const double fl = 2.0 * M * N * (double)K, by = 8.0 * ((double)M * K + (double)K * N);
   const double upd = 16.0 * (double)M * N;
@@ -508,17 +509,20 @@ void tn_tmul(cqr_plan_s& p, const cqr::TnArgs& a, const double* T, int w, double
 
 // The split re-projection update C -= A B with the panel's first Cholesky
 // pass (c) run by one extra block of the same launch; the partials (a: their
-// split) are left for panel_first.  Returns false, launching nothing, when the
-// update would not split over K; the caller then runs the update by itself.
+// split) are left for panel_first (none where the update is small).  Returns
+// false, launching nothing, when the update would not split over K; the caller
+// then runs the update by itself.
 bool nn_chol(cqr_plan_s& p, double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb,
              int64_t M, int N, int K, const cqr::CholArgs& c, const cqr::Scratch& s, hipStream_t st, cqr::NnArgs& a) {
   a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
+  if (p.cfg.precision == CQR_FP64) cqr::nn_small(a);
   a.prio = 1;
-  if (K <= cqr::kLeaf || a.nsplit <= 1 || a.tilesN != 1 || N != c.w || c.w > cqr::kLeaf) return false;
+  if (N != c.w || c.w > cqr::kLeaf) return false;
+  if (!a.small && (K <= cqr::kLeaf || a.nsplit <= 1 || a.tilesN != 1)) return false;
   const double fl = 2.0 * M * N * (double)K + 2.0 * c.w * c.w * c.w;
   const double by = 8.0 * ((double)M * K + (double)K * N) + 24.0 * c.w * c.w;
   bool launched = false;
-  prof(p, PH_REPROJ_NN, fl, by + partial_bytes(a.nsplit, a.ntiles), st,
+  prof(p, PH_REPROJ_NN, fl, by + (a.small ? 16.0 * (double)M * N : partial_bytes(a.nsplit, a.ntiles)), st,
        [&] { launched = cqr::launch_nn_chol(a, c, st); });
   return launched;
 }

@@ -2863,26 +2863,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   nn_body<SPLIT, TAG>(a, sB, blockIdx.x, blockIdx.y);
 }
 
+// The same update where 64 x 64 tiles would leave the chip idle, as tns_kernel
+// does for the product: a workgroup forms 16 x 16 elements of C, its 4 waves
+// share the depth, 16 k-values at a time in turn, straight from memory, and
+// their sums are added through LDS in order.  No partials, so the split
+// update's second launch (or its sum in panel_first) goes too.
+constexpr int kSmallNnWaves = 4;
+
+__device__ __forceinline__ void nns_body(const NnArgs& a, double (*red)[4][64], int bx) {
+  const int tilesM = (int)((a.M + 15) / 16);
+  const int64_t i0 = (int64_t)(bx % tilesM) * 16;
+  const int j0 = bx / tilesM * 16;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // rows and columns outside the matrix read row and column 0 and are not stored
+  const int64_t i = i0 + li, ic = i < a.M ? i : 0;
+  const int j = j0 + 4 * wave + g;
+  double* pc = a.C + ic + (int64_t)(j < a.N ? j : 0) * a.ldc;
+  const double old = *pc;
+  const double* pa = a.A + ic + 4 * g * a.lda;
+  const double* pb = a.B + 4 * g + (int64_t)(j0 + li < a.N ? j0 + li : 0) * a.ldb;
+  const int nfull = a.K / 16;
+  const int mine = (nfull - wave + kSmallNnWaves - 1) / kSmallNnWaves;      // the wave's whole chunks
+  v4d acc = v4d{0, 0, 0, 0};
+  double x0[8], x1[8], y0[8], y1[8];
+  auto load = [&](double (&x)[8], int q) {
+    const int k = 16 * (wave + q * kSmallNnWaves);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = pa[(int64_t)(k + s) * a.lda];
+    if (a.vec) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const v2d v = *reinterpret_cast<const v2d*>(pb + k + 2 * h);
+        x[4 + 2 * h] = v.x; x[5 + 2 * h] = v.y;
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x[4 + s] = pb[k + s];
+    }
+  };
+  auto mac = [&](const double (&x)[8]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = mfma(x[4 + s], x[s], acc);
+  };
+  if (mine > 0) load(x0, 0);
+  if (mine > 1) load(x1, 1);
+#pragma unroll 1
+  for (int q = 0; q < mine; q += 4) {
+    if (q + 2 < mine) load(y0, q + 2);
+    if (q + 3 < mine) load(y1, q + 3);
+    mac(x0);
+    if (q + 1 < mine) mac(x1);
+    if (q + 4 < mine) load(x0, q + 4);
+    if (q + 5 < mine) load(x1, q + 5);
+    if (q + 2 < mine) mac(y0);
+    if (q + 3 < mine) mac(y1);
+  }
+  if (const int k0 = 16 * nfull; k0 < a.K && wave == nfull % kSmallNnWaves) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool in = k0 + 4 * g + s < a.K;
+      x0[s] = in ? pa[(int64_t)(k0 + s) * a.lda] : 0.0;
+      x0[4 + s] = in ? pb[k0 + s] : 0.0;
+    }
+    mac(x0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[r];
+  __syncthreads();
+  double v = 0.0;
+#pragma unroll
+  for (int e = 0; e < kSmallNnWaves; ++e) v += red[e][wave][lane];     // element r = wave of the accumulators
+  if (i < a.M && j < a.N) *pc = old - v;
+}
+
+template <int TAG>
+__global__ __launch_bounds__(64 * kSmallNnWaves) void nns_kernel(NnArgs a) {
+  if (a.prio) __builtin_amdgcn_s_setprio(2);
+  __shared__ double red[kSmallNnWaves][4][64];
+  nns_body(a, red, blockIdx.x);
+}
+
 // The re-projection update P -= Q S, split over K, with one extra block that
 // runs the panel's first Cholesky-QR pass: the factorization reads only the
 // Gram rows of the preceding product and the update only its coefficient
 // rows, so the single-block Cholesky runs alongside the update's blocks
 // instead of after them on the panel chain.  Block column x = ntiles holds the
 // Cholesky (its y > 0 blocks exit at once); both uses share the LDS layout
-// size (two 64 x 65 double arrays).
+// size (two 64 x 65 double arrays).  SMALL: the update by nns_body, unsplit,
+// with the Cholesky in the first block.
+template <bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void nn_chol_kernel(NnArgs a,
                                                                                                CholArgs c) {
   __builtin_amdgcn_s_setprio(2);
   __shared__ double smem[2 * NK * (64 + 1)];
   __shared__ double dg[kLeaf];
   __shared__ int flag;
-  if ((int)blockIdx.x == a.ntiles) {
+  if ((int)blockIdx.x == (SMALL ? 0 : a.ntiles)) {
     if (blockIdx.y == 0)
       chol_first<true>(c, reinterpret_cast<double (*)[kLeaf + 1]>(smem),
                  reinterpret_cast<double (*)[kLeaf + 1]>(smem + kLeaf * (kLeaf + 1)), dg, &flag, true);
     return;
   }
-  nn_body<true, TAG_REPROJ>(a, reinterpret_cast<double (*)[NK][64 + 1]>(smem), blockIdx.x, blockIdx.y);
+  if constexpr (SMALL)
+    nns_body(a, reinterpret_cast<double (*)[4][64]>(smem), blockIdx.x - 1);
+  else
+    nn_body<true, TAG_REPROJ>(a, reinterpret_cast<double (*)[NK][64 + 1]>(smem), blockIdx.x, blockIdx.y);
 }
 
 // C -= sum of the split partials (split order).  One block per wave of a
@@ -3230,6 +3316,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   }
 }
 
+static unsigned nns_grid(const NnArgs& a) { return (unsigned)((a.M + 15) / 16 * ((a.N + 15) / 16)); }
+
+// Up to 1280 workgroups (2048 of one slab) the 64 x 64 tiles lose to these (us;
+// 5120 x 64 x 320: 20.4 and 11.1; x 768: 26.1 and 22.9; 2304 x 256 x 64: 6.6
+// and 6.5), beyond a depth of 1024, where each workgroup's reads count, fewer
+// (1386 x 35 x 1386, 258 of them: 18.8 and 17.6; x 64, 344: 18.9 and 19.7).
+bool nn_small(NnArgs& a) {
+  const int64_t wgs = nns_grid(a);
+  if (a.K > 1024 ? wgs * a.K > 400000 : wgs > (a.K <= NK ? 2048 : 1280)) return false;
+  a.small = 1;
+  a.nsplit = 1;
+  return true;
+}
+
 // Operands the LDS-staged update takes, K >= 64 (else the register-staged
 // kernels): 18-22% faster standalone than the register-staged long-K kernel
 // at K = 128 and 256.  At K = 64 it is ~8% slower alone than nn1_kernel but
@@ -3246,7 +3346,9 @@ static bool nnq_ok(const NnArgs& a) {
 
 template <int TAG>
 static void nn_launch_tag(const NnArgs& a, hipStream_t st) {
-  if (a.K <= NK && !nnw_ok(a))
+  if (a.small)
+    hipLaunchKernelGGL((nns_kernel<TAG>), dim3(nns_grid(a)), dim3(64 * kSmallNnWaves), 0, st, a);
+  else if (a.K <= NK && !nnw_ok(a))
     hipLaunchKernelGGL((nn1_kernel<TAG>), dim3(a.ntiles), dim3(256), 0, st, a);
   else if (a.nsplit > 1)
     hipLaunchKernelGGL((nn_kernel<true, TAG>), dim3(a.ntiles, a.nsplit), dim3(256), 0, st, a);
@@ -3285,8 +3387,13 @@ bool launch_nn_adj(const NnArgs& a, hipStream_t st) {
 }
 
 bool launch_nn_chol(const NnArgs& a, const CholArgs& c, hipStream_t st) {
-  if (a.M <= 0 || a.N <= 0 || a.K <= NK || a.nsplit <= 1 || c.w > kLeaf) return false;
-  hipLaunchKernelGGL(nn_chol_kernel, dim3(a.ntiles + 1, a.nsplit), dim3(256), 0, st, a, c);
+  if (a.M <= 0 || a.N <= 0 || a.K <= 0 || c.w > kLeaf) return false;
+  if (a.small) {
+    hipLaunchKernelGGL((nn_chol_kernel<true>), dim3(nns_grid(a) + 1), dim3(256), 0, st, a, c);
+    return true;
+  }
+  if (a.K <= NK || a.nsplit <= 1) return false;
+  hipLaunchKernelGGL((nn_chol_kernel<false>), dim3(a.ntiles + 1, a.nsplit), dim3(256), 0, st, a, c);
   return true;
 }
 

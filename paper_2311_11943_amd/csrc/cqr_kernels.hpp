@@ -154,6 +154,7 @@ struct NnArgs {
   int vec;            // B 16-byte aligned with even ldb (vector B loads)
   double* part;
   int prio;           // raise the waves' issue priority (panel-chain products)
+  int small;          // 16 x 16 elements of C per workgroup (nns_kernel)
   // launch_nn_adj only: C = Cin - sign A B (Cin == nullptr: zero), tri: TRI_* flags
   const double* Cin; int64_t ldcin;
   double sign;
@@ -166,6 +167,8 @@ enum : int { TRI_A_UPPER = 1, TRI_B_LOWER = 2, TRI_B_UPPER = 4, TRI_C_LOWER = 8 
 // encoded matrix and must keep the checksum relations to FP64 rounding.
 NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const double* B, int64_t ldb, int64_t M,
                 int N, int K, const Scratch& s);
+// Turn a into an update by nns_kernel, unsplit, if it is small enough.
+bool nn_small(NnArgs& a);
 void launch_nn_product(const NnArgs& a, int tag, hipStream_t st);
 void launch_nn_reduce(const NnArgs& a, hipStream_t st);   // nsplit > 1 only
 bool launch_nn_adj(const NnArgs& a, hipStream_t st);
