@@ -401,7 +401,8 @@ void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B,
         int64_t K, double* C, int64_t ldc, double* C2, int64_t ldc2, const cqr::Scratch& s, hipStream_t st,
         int M2 = -1, int lowp = 0) {
   if (M <= 0 || N <= 0) return;
-  cqr::TnArgs a = cqr::tn_setup(A, lda, B, ldb, M, N, K, C, ldc, C2, ldc2, s, 0, lowp);
+  cqr::TnArgs a =
+      cqr::tn_setup(A, lda, B, ldb, M, N, K, C, ldc, C2, ldc2, s, 0, lowp, p.cfg.precision == CQR_FP64);
   if (M2 >= 0) a.M2 = M2;
   a.seq = p.cfg.precision != CQR_FP64;
   if (!a.seq) cqr::tn_small(a);

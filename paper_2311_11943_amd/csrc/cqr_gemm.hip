@@ -1252,15 +1252,15 @@ static bool aligned16(const void* p, int64_t ld) {
   return (reinterpret_cast<uintptr_t>(p) % 16 == 0) && (ld % 2 == 0);
 }
 
-static int pick_split(int tiles, int64_t K, int64_t cap) {
+static int pick_split(int tiles, int64_t K, int64_t cap, int64_t rows) {
   // Below 256 workgroups: at most 512 (two resident per CU, so one wave of
   // workgroups; a few over that run as a second wave and cost ~16% at 79
   // tiles).  From 256 on, splits up to ~1280 workgroups: the shorter
   // workgroups even out the last wave (alone, the 128 x 20480 product with
   // depth 24576 runs at 51.6 TFLOP/s with two splits against 44.3 with one).
-  // Each split keeps at least 256 rows (8 slabs).
+  // Each split keeps at least `rows` rows.
   int want = tiles >= 256 ? (1280 + tiles - 1) / tiles : std::max(1, 512 / std::max(1, tiles));
-  int64_t maxs = std::max<int64_t>(1, K / 256);
+  int64_t maxs = std::max<int64_t>(1, K / rows);
   int ns = (int)std::min<int64_t>(want, maxs);
   while (ns > 1 && (int64_t)ns * tiles > cap) --ns;
   return ns;
@@ -1268,18 +1268,43 @@ static int pick_split(int tiles, int64_t K, int64_t cap) {
 
 // The 512-thread products (128 x 128 or two-tile-row; two workgroups per CU,
 // 512 slots): about 1280 workgroups whatever the tile count, so that the last
-// wave of workgroups is short, each split keeping at least 256 rows.  Alone, the 128 x 20480
+// wave of workgroups is short, each split keeping at least `rows` rows.  Alone, the 128 x 20480
 // product of depth 24576 (160 tiles) runs at 60.8 TFLOP/s with 8 splits
 // against 51.5 with the 3 that filling one wave of slots gives.
-static int pick_split_quad(int blocks, int64_t K, int64_t cap, int tiles) {
-  const int64_t maxs = std::max<int64_t>(1, K / 256);
+static int pick_split_quad(int blocks, int64_t K, int64_t cap, int tiles, int64_t rows = 256) {
+  const int64_t maxs = std::max<int64_t>(1, K / rows);
   int ns = (int)std::min<int64_t>((1280 + blocks - 1) / blocks, maxs);
   while (ns > 1 && (int64_t)ns * tiles > cap) --ns;
   return std::max(ns, 1);
 }
 
+// The 128 x 128 products of short duration: as many workgroups as half the slots
+// or all of them (512) hold, where those divide well among the blocks, so a
+// fraction of the partials of 1280 (us, product and sum, 1280, 512 and 256
+// workgroups: 512 x 512 x 5120: 82, 63, 57; 128 x 4096 x 5120: 129, 101, 101;
+// 512 x 512 x 20480: 212, 180, 184).  Longer ones stay with 1280: beside the
+// panel chain the n = 16384 factorization loses 0.8% with 512.
+static int pick_split_wave(int blocks, int64_t K, int64_t cap, int tiles) {
+  if (blocks * K > 350000) return pick_split_quad(blocks, K, cap, tiles);
+  const int slots = blocks * K <= 90000 ? 256 : 512;
+  int ns = (int)std::min<int64_t>(slots / blocks, K / 64);
+  if (blocks * ns < slots - slots / 10 && blocks * (K / 64) > slots) return pick_split_quad(blocks, K, cap, tiles);
+  while (ns > 1 && (int64_t)ns * tiles > cap) --ns;
+  return std::max(ns, 1);
+}
+
+// Least rows of a split: 256 (8 slabs), so that a split's partials stay small
+// against its operands; fewer where the whole product leaves the GPU idle, as
+// long as it stays below a workgroup per CU (us, product and sum; splits of
+// 256, 128 and 64 rows; 64 x 64 x 2304: 17.7, 13.2, 11.7; x 9216: 18.1, 12.6,
+// 11.9; x 20480: 17.5, 13.8, 17.7; 512 x 64 x 2304: 18.4, 14.9, 17.2; 1024 x 64 x
+// 2304: 19.6, 21.1, 23.4).
+static int64_t split_rows(int64_t blocks, int64_t K) {
+  return blocks * (K / 64) <= 224 ? 64 : blocks * (K / 128) <= 256 ? 128 : 256;
+}
+
 TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int M, int N, int64_t K, double* C,
-                int64_t ldc, double* C2, int64_t ldc2, const Scratch& s, int force_split, int lowp) {
+                int64_t ldc, double* C2, int64_t ldc2, const Scratch& s, int force_split, int lowp, bool fine) {
   const bool f32 = lowp != 0;
   TnArgs a{};
   a.A = A; a.lda = lda; a.B = B; a.ldb = ldb;
@@ -1293,14 +1318,18 @@ TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int 
   // products of at least two tile rows and columns: 128 x 128 per workgroup
   // and a depth that is a multiple of 16 (whole slabs in every split)
   // (32 for FP32 products, whose slabs are 32 deep)
-  const bool quad = vec && tilesM >= 2 && tilesN >= 2 && K % (f32 ? 32 : 16) == 0;
+  // (fine: small ones are better spread over 64 x 64 tiles, 128 x 128 x 5120: 16
+  // us against 20, 512 x 128 x 2304: 21 and 27, x 5120: 31 and 26)
+  const bool quad = vec && tilesM >= 2 && tilesN >= 2 && K % (f32 ? 32 : 16) == 0 && !(fine && tiles * K <= 40000);
   // the split-BF16 product on the same 128 x 128 tiles
   const bool bf3 = vec && lowp == 2 && tilesM >= 2 && tilesN >= 2 && K % 32 == 0;
   // the split count fills the grid of workgroups the product launches
   const int blocks = quad || bf3 ? (tilesM + 1) / 2 * ((tilesN + 1) / 2) : pair ? (tilesM + 1) / 2 * tilesN : tiles;
+  const int64_t rows = fine ? split_rows(blocks, K) : 256;
   int ns = force_split > 0 ? force_split
-           : quad || bf3 || pair ? pick_split_quad(blocks, K, s.npart, tiles)
-                           : pick_split(blocks, K, s.npart);
+           : quad && fine        ? pick_split_wave(blocks, K, s.npart, tiles)
+           : quad || bf3 || pair ? pick_split_quad(blocks, K, s.npart, tiles, rows)
+                           : pick_split(blocks, K, s.npart, rows);
   while (ns > 1 && (int64_t)ns * tiles > s.npart) --ns;
   int64_t kchunk = (K + ns - 1) / ns;
   kchunk = (kchunk + KC - 1) / KC * KC;
@@ -1323,15 +1352,10 @@ TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int 
 TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
                       int64_t ldc, const Scratch& s) {
   const int t = (N + 2 * kTile - 1) / (2 * kTile), tiles = (N + kTile - 1) / kTile;
-  // (at least 1024 rows a split where that fills the GPU: its partials then take
-  // an eighth of the bytes of its operands.  One block of 2304 rows in two
-  // splits left all but two CUs idle: 155 us, 20 in nine.)
-  const int blocks = t * (t + 1) / 2;
-  const int ns = (int)std::min<int64_t>(pick_split_quad(blocks, K, s.npart, tiles * tiles),
-                                        std::max<int64_t>((512 + blocks - 1) / blocks, K / 1024));
-  TnArgs a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s);
+  const int ns = pick_split_wave(t * (t + 1) / 2, K, s.npart, tiles * tiles);
+  TnArgs a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s, 0, 0, true);
   if (!a.quad) return a;
-  a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s, ns);
+  a = tn_setup(A, lda, B, ldb, N, N, K, C, ldc, nullptr, 0, s, ns, 0, true);
   a.lower = 1;
   return a;
 }

@@ -125,8 +125,10 @@ struct TnArgs {
 // shape allows it (at least two tile rows and columns, depth a multiple of
 // 32, aligned operands), else FP32; for the mixed-precision coefficient
 // product R_bar = Qbar^T Q_t.
+// fine: splits of fewer than 256 rows where the product is small (split_rows).
 TnArgs tn_setup(const double* A, int64_t lda, const double* B, int64_t ldb, int M, int N, int64_t K, double* C,
-                int64_t ldc, double* C2, int64_t ldc2, const Scratch& s, int force_split = 0, int lowp = 0);
+                int64_t ldc, double* C2, int64_t ldc2, const Scratch& s, int force_split = 0, int lowp = 0,
+                bool fine = false);
 // C = A^T B (N x N) of which only the lower triangle is read
 TnArgs tn_setup_lower(const double* A, int64_t lda, const double* B, int64_t ldb, int N, int64_t K, double* C,
                       int64_t ldc, const Scratch& s);
