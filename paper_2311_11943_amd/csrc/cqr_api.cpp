@@ -372,6 +372,10 @@ int chain_phase(int phase) { return phase != PH_TRAIL_TN && phase != PH_TRAIL_NN
 constexpr int64_t kPairBytes = (int64_t)160 << 20;
 // Panels after a pair that take each of its panels' updates by itself.
 constexpr int kPairNear = 4;
+// Up to this many panels in all (a tall matrix then, by kPairBytes) the chain
+// waits for its next columns of those only, updated by a launch of their own
+// (65536 x 512, b = 64: 2.72 ms, 2.60 so; 65536 x 1024 7.99 and 8.14).
+constexpr int kNearPanels = 12;
 
 // Whether the next panel is factored beside the trailing update.  Where the
 // update is as short as the panel's own kernels that gains less than the two
@@ -391,8 +395,8 @@ bool looks_ahead(const cqr_plan_s& p) {
 
 // First tile of the Gram partials in the split-partial area: the split
 // re-projection update, whose partials are read by the launch that writes the
-// Gram partials, takes at most 512 tiles (nn_setup), the Gram partials at most
-// 512 (panel_first_blocks), of at least 1024.
+// Gram partials, takes at most 512 tiles (nn_setup), the Gram partials two per
+// workgroup (panel_first_blocks) behind them.
 constexpr int kGramPartTile = 512;
 
 double partial_bytes(int nsplit, int ntiles) { return 8.0 * nsplit * ntiles * cqr::kTile * cqr::kTile; }
@@ -489,7 +493,8 @@ cqr::TnArgs tn_early(cqr_plan_s& p, const double* X, int64_t ldx, const double* 
   const int tiles = (N + kTile - 1) / kTile;
   const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(kEarlyBlocks / tiles, p.mp / 256));
   cqr::TnArgs a = cqr::tn_setup(X, ldx, B, ldb, w, N, p.mp, s.part, w, nullptr, 0, s, ns, lowp);
-  if (p.cfg.precision == CQR_FP64) cqr::tn_small(a);
+  a.seq = p.cfg.precision != CQR_FP64;
+  if (!a.seq) cqr::tn_small(a);
   a.prio = chain_phase(PH_TRAIL_TN);
   const double fl = 2.0 * w * N * (double)p.mp, by = 8.0 * (double)p.mp * ((double)w + N);
   const double out = a.nsplit > 1 ? partial_bytes(a.nsplit, a.ntiles) : 8.0 * (double)w * N;
@@ -689,6 +694,7 @@ cqr_status coded_qr_plan_create(const cqr_config* cfg, const double* v_tilde, co
   // four partial tiles per output tile (32 KB each): large products split up to
   // ~1280 workgroups of at most four tiles, so never into more than 8 x 1280
   p->npart = std::max<int64_t>(1024, std::min<int64_t>(4 * maxTiles, 8 * 1280));
+  p->npart = std::max<int64_t>(p->npart, kGramPartTile + 2 * cqr::panel_first_blocks(p->mp, true));
   p->nS = std::max<int64_t>(n * b, (int64_t)kLeaf * kLeaf);   // S with the fused Gram rows: c1 x b, c1 <= n
   p->ninfo = 64 + (int)((n + b - 1) / b);
   size_t off = align256(sizeof(int) * (size_t)p->ninfo);
@@ -1008,7 +1014,7 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
           // chain touches them only after join_side_all).
           double* Rb = R + c0 + (c1 + b) * ldr;
           tn_tmul(*p, ea, s.T2, (int)b, Rb, ldr, p->side, s.fb + c0 / w, P, ldq);
-          const int64_t near = pairs ? ncol : std::min<int64_t>(b, ncol);
+          const int64_t near = pairs && N > kNearPanels * b ? ncol : std::min<int64_t>(b, ncol);
           nn(*p, PH_TRAIL_NN, Q + (c1 + b) * ldq, ldq, P, ldq, Rb, ldr, mp, (int)near, (int)b, s2, p->side);
           e = hipEventRecord(p->ev_side, p->side);
           if (e != hipSuccess) return hip_fail(e);

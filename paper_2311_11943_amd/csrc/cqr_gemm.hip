@@ -1736,7 +1736,18 @@ __global__ __launch_bounds__(256) void tn_reduce_tmul_kernel(TnArgs a, const dou
 void launch_tn_reduce_tmul(const TnArgs& a, const double* T, int w, double* out, int64_t ldo, hipStream_t st,
                            const int* fb, const double* P, int64_t ldp) {
   if (a.M <= 0 || a.N <= 0) return;
-  hipLaunchKernelGGL(tn_reduce_tmul_kernel, dim3(a.ntiles * 4), dim3(256), 0, st, a, T, w, out, ldo, fb, P, ldp);
+  TnArgs b = a;
+  // Four workgroups a tile, one batch of 16 loads after the other: the many
+  // splits of a tall matrix's few tiles (110: 83 us, 288: 105) are summed by more
+  // workgroups first, in place of the coefficients (20 us in all).  Beside the
+  // panel chain the second launch costs more than it gains up to some 72 splits
+  // (16384 x 2048: 9.57 ms, 9.94 with it).
+  if (!a.seq && a.nsplit > 96) {
+    b.C = out; b.ldc = ldo; b.C2 = nullptr;
+    launch_tn_sum(b, st);
+    b.nsplit = 1;
+  }
+  hipLaunchKernelGGL(tn_reduce_tmul_kernel, dim3(b.ntiles * 4), dim3(256), 0, st, b, T, w, out, ldo, fb, P, ldp);
 }
 
 // acc = T^T X with T (64 x 64, upper triangular, row-major LDS): wave v forms
