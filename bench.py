@@ -64,7 +64,7 @@ SINGLE_KERNEL_PHASES = ("trailing_product", "trailing_update", "reproj_product",
 KERNEL_OF = {
     "encode": "encode_fused_kernel / encode_rows_kernel",
     "reproj_product": "tn_lds_kernel<1, false>", "reproj_update": "nn_kernel<*, 1>",
-    "panel_gram": "tn_lds_kernel<2, false>", "panel_chol": "chol_kernel", "panel_transform": "apply_kernel / nn1_apply_kernel",
+    "panel_gram": "tn_lds_kernel<2, false>", "panel_chol": "panel_second_kernel", "panel_transform": "panel_first_kernel",
     "inpanel_projection": "tn/nn <2, false>",
     "trailing_product": "tn_lds_kernel<0, false>", "trailing_update": "nnw_kernel<0>",
     "split_reduce": "tn_reduce_kernel / nn_reduce_kernel", "recover": "lines_kernel",

@@ -84,9 +84,10 @@ typedef enum { CQR_FP64 = 0, CQR_TRAIL_FP32 = 1, CQR_TRAIL_BF16X3 = 2 } cqr_prec
  *     Kaufman-Stewart test, a reading of the paper's unstated criterion).
  *   CQR_PANEL_MGS: the paper's sequential modified Gram-Schmidt within the
  *     panel (its experiments' choice; with reproject = 0 the paper's method).
- * The column-wise modes run one workgroup per panel leaf of up to 64 columns
- * with FP64 norms and wavefront reductions; wider panels are split in halves,
- * the right half projected twice against the left one. */
+ * The column-wise modes take panel leaves of up to 64 columns, the rows shared
+ * by a grid of workgroups and one or two launches per column, with FP64 norms
+ * and sums in a fixed order; wider panels are split in halves, the right half
+ * projected twice against the left one. */
 typedef enum { CQR_PANEL_CHOLQR2 = 0, CQR_PANEL_CGS2 = 1, CQR_PANEL_ICGS = 2, CQR_PANEL_MGS = 3 } cqr_panel;
 
 typedef struct {
@@ -94,14 +95,20 @@ typedef struct {
   int32_t pr, pc;      /* simulated node grid */
   int32_t kv, kh;      /* checksum block-rows (protect Q) / block-columns (protect R) */
   int32_t storage;     /* cqr_storage: which blocks a node failure erases */
-  int32_t b;           /* panel width of the blocked Gram-Schmidt; b | n */
+  int32_t b;           /* panel width of the blocked Gram-Schmidt; b | n.  Failures
+                          are injected at multiples of b.  The columns factored
+                          at once may be fewer or more (CQR_PANEL_CHOLQR2 with
+                          re-projection, lookahead, FP64 and 64 | b: chosen by
+                          the matrix's size); Q and R then differ by rounding */
   int32_t reproject;   /* 1: re-project each panel against all earlier Q columns
                           before factoring it (default); 0: the paper's PBMGS */
   int32_t precision;   /* cqr_precision */
   int32_t lookahead;   /* 1: the panel chain runs on a plan-owned stream while a
                           second plan-owned stream applies each panel's update to
                           the columns right of the next panel; both fork from and
-                          join back to the caller's stream within each call.  The
+                          join back to the caller's stream within each call.  Small
+                          FP64 factorizations, whose updates are as short as the
+                          chain's kernels, stay on the caller's stream.  The
                           update starts from the panel after its first Cholesky
                           pass, its coefficients taken as R2^{-T} (P1^T Q_t), equal
                           to P^T Q_t up to rounding (split products may also sum in
@@ -269,7 +276,8 @@ cqr_status coded_qr_postorth(cqr_plan plan, const double* Q, int64_t ldq, double
  * nrhs >= 1.  ws: caller-owned device workspace, 256-byte aligned, of at least
  * coded_qr_solve_workspace_bytes(plan, nrhs) bytes (the inverted 64 x 64
  * diagonal blocks of R_1 and Y = Qpost^T Bpost); CQR_ENOMEM if smaller or
- * misaligned.  No pivoting and no singularity check: R_1 from coded_qr_factor
+ * misaligned.  While the call runs X holds unfinished blocks that its own
+ * workgroups wait for, so no other work may write X or ws.  No pivoting and no singularity check: R_1 from coded_qr_factor
  * has a positive diagonal whenever its info is 0, and a zero pivot gives
  * non-finite entries of X.
  */
