@@ -117,19 +117,21 @@ bool invert(std::vector<double> a, int n, std::vector<double>& inv) {
 // a multiple of 64: single leaves (64) while the encoded matrix is at most 1 GiB,
 // where their short chain beats the wide panels' better products (n = 8192: 77 ms
 // against 93 with 128 columns and 82 with 256; n = 4096: 12.9 against 16.4 and
-// 19.8); about 512 columns up to 2.5 GiB (n = 12288: 209 ms, 250 with leaves, 215
-// with 256), 1024 beyond (n = 16384: 461 ms, 483 with 512, 536 with 256, 577 with
-// 128).  Without re-projection, in the column-wise modes and in reduced precision
-// (whose coefficients depend on the division) it is b.  This is the largest
-// width of the factorization; panel_width() narrows it towards the last columns.
+// 19.8); about 512 columns beyond (n = 12288: 209 ms, 250 with leaves, 215 with
+// 256; n = 32768: 5.10 s, 5.40 with 256).  1024 gain little more and leave more
+// rounding in A~ - Q~ R (n = 16384 with failures: 675 ms and a residual of
+// 6.4e-14, 678 ms and 4.7e-14 with 512, 3.3e-14 with 128; n = 32768: 5.01 s and
+// 2.1e-13, 1.6e-13 with 512, 1.2e-13 with 256).  Without re-projection, in the
+// column-wise modes and in reduced precision (whose coefficients depend on the
+// division) it is b.  This is the largest width of the factorization;
+// panel_width() narrows it towards the last columns.
 int64_t inner_width(const cqr_plan_s& p) {
   const cqr_config& c = p.cfg;
   if (c.panel != CQR_PANEL_CHOLQR2 || c.precision != CQR_FP64 || !c.reproject || !c.lookahead || c.b % kLeaf)
     return c.b;
   const int64_t bytes = 8 * p.mp * p.N;
   if (bytes <= (int64_t)1 << 30) return kLeaf;
-  const int64_t target = bytes <= (int64_t)5 << 29 ? 512 : 1024;
-  return std::max<int64_t>(c.b, target / c.b * c.b);
+  return std::max<int64_t>(c.b, 512 / c.b * c.b);
 }
 
 // Width of the panel that starts at column c.  What a re-projection leaves of a
