@@ -1469,7 +1469,7 @@ void launch_tn_reduce(const TnArgs& a, hipStream_t st) {
 // inverse, and on the second pass R2 R1 and the lookahead coefficients T^T X.
 // One block of four waves (see chol_blocked for the factorization).  A
 // pivot at most kCholBreak times its column's diagonal entry is a breakdown,
-// handled by the column-wise fallback described at chol_body.
+// handled by the column-wise fallback described at panel_second_kernel.
 // --------------------------------------------------------------------------
 
 // Smallest pivot / diagonal ratio a Cholesky-QR pass accepts: below it a
