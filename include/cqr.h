@@ -99,7 +99,11 @@ typedef struct {
                           are injected at multiples of b.  The columns factored
                           at once may be fewer or more (CQR_PANEL_CHOLQR2 with
                           re-projection, lookahead, FP64 and 64 | b: chosen by
-                          the matrix's size); Q and R then differ by rounding */
+                          the matrix's size); Q and R then differ by rounding,
+                          whose size stays that of panels of b: no update sums
+                          more than b products before it subtracts them, no
+                          coefficient's partial sum covers more rows than b
+                          columns by themselves would give it */
   int32_t reproject;   /* 1: re-project each panel against all earlier Q columns
                           before factoring it (default); 0: the paper's PBMGS */
   int32_t precision;   /* cqr_precision */

@@ -112,19 +112,17 @@ bool invert(std::vector<double> a, int n, std::vector<double>& inv) {
 
 // Columns a factorization takes at once.  The panel width b of the
 // configuration sets the boundaries at which calls may be split and failures
-// strike; between them, with re-projection every division of the columns gives
-// the same factors up to rounding, so the width follows what runs fastest, for b
-// a multiple of 64: single leaves (64) while the encoded matrix is at most 1 GiB,
-// where their short chain beats the wide panels' better products (n = 8192: 77 ms
-// against 93 with 128 columns and 82 with 256; n = 4096: 12.9 against 16.4 and
-// 19.8); about 512 columns beyond (n = 12288: 209 ms, 250 with leaves, 215 with
-// 256; n = 32768: 5.10 s, 5.40 with 256).  1024 gain little more and leave more
-// rounding in A~ - Q~ R (n = 16384 with failures: 675 ms and a residual of
-// 6.4e-14, 678 ms and 4.7e-14 with 512, 3.3e-14 with 128; n = 32768: 5.01 s and
-// 2.1e-13, 1.6e-13 with 512, 1.2e-13 with 256).  Without re-projection, in the
-// column-wise modes and in reduced precision (whose coefficients depend on the
-// division) it is b.  This is the largest width of the factorization;
-// panel_width() narrows it towards the last columns.
+// strike, and how deep the sums of an update are (update_depth); between them,
+// with re-projection every division of the columns gives the same factors up to
+// rounding, so the width follows what runs fastest, for b a multiple of 64:
+// single leaves (64) while the encoded matrix is at most 1 GiB, where their short
+// chain beats the wide panels' better products (n = 8192: 78 ms against 93 with
+// 128 columns and 82 with 256; n = 4096: 13.1 against 14.5 and 15.4); about 512
+// columns beyond (b = 64, n = 12288: 231 ms, 257 with leaves; b = 128, n = 16384:
+// 710 ms, 799 with 128; b = 256, n = 32768: 5.22 s, 5.40 with 256).  Without
+// re-projection, in the column-wise modes and in reduced precision (whose
+// coefficients depend on the division) it is b.  This is the largest width of
+// the factorization; panel_width() narrows it towards the last columns.
 int64_t inner_width(const cqr_plan_s& p) {
   const cqr_config& c = p.cfg;
   if (c.panel != CQR_PANEL_CHOLQR2 || c.precision != CQR_FP64 || !c.reproject || !c.lookahead || c.b % kLeaf)
@@ -401,14 +399,50 @@ bool looks_ahead(const cqr_plan_s& p) {
 // workgroup (panel_first_blocks) behind them.
 constexpr int kGramPartTile = 512;
 
+// Products that an update may sum before it subtracts them from a column: no
+// more than panels of b would, whatever width is factored at once.  The sum's
+// rounding grows with its own size, so a deeper one drifts further from the
+// checksum relations, and a decode amplifies the drift (n = 8192, 16 x 16 grid,
+// b = 256, three storms: |A~ - Q~ R| 1.70e-13 with 256, 2.27e-13 with 512;
+// 1.39e-13 with 128).
+int update_depth(const cqr_plan_s& p) { return p.pw > kLeaf && p.pw > p.cfg.b ? p.cfg.b : 0; }
+// From this depth on the update runs `depth` columns at a time; below, one launch
+// subtracts as it goes (us a step; n = 16384, 128: 752 and 711; n = 8192, 256:
+// 97.1 and 100.0).
+constexpr int kFlushDepth = 256;
+// A pair of panels is one sum up to this depth (n = 6144: the post-orthogonalized
+// basis 5.97e-12 from orthonormal with panels of 48 by themselves, 5.85e-12 in
+// pairs; 64: 5.75e-12, 6.04e-12).
+constexpr int kPairDepth = 96;
+
+// Rows that a split of a wide panel's coefficient product may sum, for the same
+// reason (R's checksum relation): as many as in the product of b columns by
+// itself (n = 4096, 49152 rows, b = 128: |A~ - Q~ R| after three events 6.1e-13
+// with panels of 128, 8.4e-13 with 512 and their own splits).
+int64_t product_chain(const cqr_plan_s& p, int64_t cols) {
+  if (!update_depth(p) || cols <= 0) return 0;
+  const int64_t b = p.cfg.b, blocks = (b + 127) / 128 * ((cols + 127) / 128), tiles = b / kTile * ((cols + 63) / 64);
+  const int64_t cap = std::max<int64_t>(1024, 4 * (b / kTile) * ((p.N + 63) / 64));
+  const int64_t ns = std::max<int64_t>(1, std::min({(1280 + blocks - 1) / blocks, cap / tiles, p.mp / 256}));
+  return ((p.mp + ns - 1) / ns + 31) / 32 * 32;
+}
+
 double partial_bytes(int nsplit, int ntiles) { return 8.0 * nsplit * ntiles * cqr::kTile * cqr::kTile; }
 
 void tn(cqr_plan_s& p, int phase, const double* A, int64_t lda, const double* B, int64_t ldb, int M, int N,
         int64_t K, double* C, int64_t ldc, double* C2, int64_t ldc2, const cqr::Scratch& s, hipStream_t st,
-        int M2 = -1, int lowp = 0) {
+        int M2 = -1, int lowp = 0, int64_t chain = 0) {
   if (M <= 0 || N <= 0) return;
   cqr::TnArgs a =
       cqr::tn_setup(A, lda, B, ldb, M, N, K, C, ldc, C2, ldc2, s, 0, lowp, p.cfg.precision == CQR_FP64);
+  if (chain > 0 && a.kchunk > chain) {
+    // splits of more than `chain` rows: that part of the rows at a time, each added to the ones before
+    const int64_t parts = (a.kchunk + chain - 1) / chain, per = ((K + parts - 1) / parts + 31) / 32 * 32;
+    for (int64_t k = 0; k < K; k += per)
+      tn(p, phase, A + k, lda, B + k, ldb, M, N, std::min(per, K - k), k ? nullptr : C, ldc, k ? C : nullptr, ldc, s,
+         st);
+    return;
+  }
   if (M2 >= 0) a.M2 = M2;
   a.seq = p.cfg.precision != CQR_FP64;
   if (!a.seq) cqr::tn_small(a);
@@ -439,11 +473,21 @@ void tn_lower(cqr_plan_s& p, const double* A, int64_t lda, const double* B, int6
     prof(p, PH_REDUCE, (a.nsplit - 1.0) * share * N * N, pb + out, st, [&] { cqr::launch_tn_reduce(a, st); });
 }
 
+// depth > 0: products summed before they are subtracted from C (see update_depth)
 void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64_t lda, const double* B,
-        int64_t ldb, int64_t M, int N, int K, const cqr::Scratch& s, hipStream_t st) {
+        int64_t ldb, int64_t M, int N, int K, const cqr::Scratch& s, hipStream_t st, int depth = 0) {
   if (M <= 0 || N <= 0 || K <= 0) return;
   cqr::NnArgs a = cqr::nn_setup(C, ldc, A, lda, B, ldb, M, N, K, s);
   if (p.cfg.precision == CQR_FP64) cqr::nn_small(a);
+  // (a small update's four waves each sum a quarter of the products)
+  if (depth > 0 && K > (a.small ? 4 : 1) * depth) {
+    a.small = 0;
+    if (depth >= kFlushDepth || !cqr::nn_flush(a, depth)) {
+      for (int k = 0; k < K; k += depth)
+        nn(p, phase, C, ldc, A + k * lda, lda, B + k, ldb, M, N, std::min(depth, K - k), s, st);
+      return;
+    }
+  }
   a.prio = chain_phase(phase);
   const double fl = 2.0 * M * N * (double)K, by = 8.0 * ((double)M * K + (double)K * N);
   const double upd = 16.0 * (double)M * N;
@@ -609,7 +653,8 @@ void factor_panel(cqr_plan_s& p, double* Q, int64_t ldq, double* R, int64_t ldr,
   for (int pass = 0; pass < 2; ++pass) {
     tn(p, PH_INPANEL, Q + c * ldq, ldq, Q + (c + h) * ldq, ldq, h, w - h, mp, s.S, h, R + c + (c + h) * ldr,
        ldr, s, st);
-    nn(p, PH_INPANEL, Q + (c + h) * ldq, ldq, Q + c * ldq, ldq, s.S, h, mp, w - h, h, s, st);
+    nn(p, PH_INPANEL, Q + (c + h) * ldq, ldq, Q + c * ldq, ldq, s.S, h, mp, w - h, h, s, st,
+       pass == 0 ? update_depth(p) : 0);
   }
   factor_panel(p, Q, ldq, R, ldr, c + h, w - h, s, st);
 }
@@ -852,19 +897,19 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
     double* Rb = R + c0 + from * ldr;
     const double* P = Q + c0 * ldq;
     tn(*p, PH_TRAIL_TN, P, ldq, Q + from * ldq, ldq, (int)b, (int)(to - from), mp, Rb, ldr, nullptr, 0, sc, ss, -1,
-       lowp);
-    nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, P, ldq, Rb, ldr, mp, (int)(to - from), (int)b, sc, ss);
+       lowp, product_chain(*p, to - from));
+    nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, P, ldq, Rb, ldr, mp, (int)(to - from), (int)b, sc, ss, update_depth(*p));
   };
   // Panels in pairs (a, b = a+1): columns further right take both panels'
-  // updates at once, R rows = [Pa Pb]^T Q_t and Q_t -= [Pa Pb] R, so the
-  // trailing matrix is read and written half as often and both products run at
-  // twice the panel width's rate.  The kPairNear panels after the pair, which
-  // the chain needs sooner, take each panel's update by itself.  Pb's
-  // coefficients then come from columns that still carry their components along
-  // Pa; as Pb^T Pa is at rounding level the difference is too, and the next
-  // panels' re-projection removes it -- hence only with re-projection.  Only in
-  // FP64: reduced-precision coefficients keep the column state they are rounded
-  // from.
+  // updates in one launch each, R rows = [Pa Pb]^T Q_t and Q_t -= [Pa Pb] R (its
+  // sums no deeper than a leaf, see update_depth), so the trailing matrix is read
+  // and written half as often and both products run at twice the panel width's
+  // rate.  The kPairNear panels after the pair, which the chain needs sooner,
+  // take each panel's update by itself.  Pb's coefficients then come from columns
+  // that still carry their components along Pa; as Pb^T Pa is at rounding level
+  // the difference is too, and the next panels' re-projection removes it -- hence
+  // only with re-projection.  Only in FP64: reduced-precision coefficients keep
+  // the column state they are rounded from.
   // The chain's re-projection fills the GPU, its panel passes do not: the pair's
   // product is queued behind the next panel's re-projection and its update
   // behind the one after, so that they run beside the passes (n = 4096: 13.4 ms
@@ -879,7 +924,7 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
   };
   auto pair_update = [&](int64_t c0, int64_t from, const cqr::Scratch& sc, hipStream_t ss) {
     nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, Q + c0 * ldq, ldq, R + c0 + from * ldr, ldr, mp, (int)(N - from),
-       2 * (int)w, sc, ss);
+       2 * (int)w, sc, ss, 2 * w > kPairDepth ? (int)w : 0);
   };
   bool deferred = false;       // a wide panel's update of the columns after the next panel, not yet forked
   int64_t def_c0 = 0, def_b = 0, def_from = 0;

@@ -124,7 +124,7 @@ __device__ __forceinline__ void store_quadrant(double* C, int64_t ldc, double* C
     const int x = e >> 3, y = (e >> 2) & 1, r = e & 3;
     const int i = i0 + 16 * x + li, j = j0 + 16 * y + colsub(r, g, f32);
     if (i < M && j < N) {
-      C[i + (int64_t)j * ldc] = v[e];
+      if (C) C[i + (int64_t)j * ldc] = v[e];
       if (C2 && i < M2) C2[i + (int64_t)j * ldc2] = old[e] + v[e];
     }
   }
@@ -697,7 +697,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             const int j = j0 + colsub(r, g, false);
             const double v = acc[2 * xh + x][y][r];
             if (i < a.M && j < a.N) {
-              a.C[i + (int64_t)j * a.ldc] = v;
+              if (a.C) a.C[i + (int64_t)j * a.ldc] = v;
               if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] = old[r] + v;
             }
           }
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int j = j0 + colsub(r, g, true);
             const double v = acc[2 * xh + x][y][r];
             if (i < a.M && j < a.N) {
-              a.C[i + (int64_t)j * a.ldc] = v;
+              if (a.C) a.C[i + (int64_t)j * a.ldc] = v;
               if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] = old[r] + v;
             }
           }
@@ -1013,7 +1013,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int j = j0 + colsub(r, g, true);
             const double v = acc[2 * xh + x][y][r];
             if (i < a.M && j < a.N) {
-              a.C[i + (int64_t)j * a.ldc] = v;
+              if (a.C) a.C[i + (int64_t)j * a.ldc] = v;
               if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] = old[r] + v;
             }
           }
@@ -1160,7 +1160,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void tns_kernel(TnArgs a) {
 #pragma unroll
   for (int e = 0; e < kSmallWaves; ++e) v += red[e][wave][lane];
   if (i >= a.M || j >= a.N) return;
-  a.C[i + (int64_t)j * a.ldc] = v;
+  if (a.C) a.C[i + (int64_t)j * a.ldc] = v;
   if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] += v;
 }
 
@@ -1213,7 +1213,7 @@ __global__ __launch_bounds__(64 * G) void tn_reduce_split_kernel(TnArgs a) {
   double x = 0.0;
 #pragma unroll
   for (int e = 0; e < G; ++e) x += red[e][grp][lane];
-  a.C[i + (int64_t)j * a.ldc] = x;
+  if (a.C) a.C[i + (int64_t)j * a.ldc] = x;
   if (add) a.C2[i + (int64_t)j * a.ldc2] = old + x;
 }
 
@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(TnArgs a) {
   for (int u = 0; u < 4; ++u) {
     const int j = jq + colsub(u, g, a.f32);
     if (j < a.N) {
-      a.C[i + (int64_t)j * a.ldc] = v[u];
+      if (a.C) a.C[i + (int64_t)j * a.ldc] = v[u];
       if (a.C2 && i < a.M2) a.C2[i + (int64_t)j * a.ldc2] = old[u] + v[u];
     }
   }
@@ -3089,7 +3089,9 @@ __device__ __forceinline__ bool nn_tri_tile(const NnArgs& a, int b, int tilesM, 
 // multiple of KC, 16-byte aligned A and B with even leading dimensions, and
 // an even M; tiles take the XCD-aware order.
 // The body for slabs of SK k-values (32 or 16; LDS row pitch SK + 2).
-template <int TAG, int SK>
+// FLUSH: the accumulators are subtracted from C's elements and cleared after
+// every a.flush k-values (a multiple of 32).
+template <int TAG, int SK, bool FLUSH = false>
 __device__ __forceinline__ void nnw_body(const NnArgs& a, double (*sA)[64 * (SK + 2)], double (*sB)[64 * (SK + 2)]) {
   typedef v4d Acc;
   constexpr int LW = SK + 2;         // padded LDS row (doubles)
@@ -3193,6 +3195,14 @@ __device__ __forceinline__ void nnw_body(const NnArgs& a, double (*sA)[64 * (SK 
     compute(1);
     __builtin_amdgcn_sched_barrier(0);
     put(0, ra0, rb0);
+    if constexpr (FLUSH)
+      if ((sl + 2) * SK % a.flush == 0) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          cval[e] -= acc[e >> 3][e >> 2 & 1][e & 3];
+          acc[e >> 3][e >> 2 & 1][e & 3] = 0.0;
+        }
+      }
     __syncthreads();
   }
   if (sl < nsl) compute(0);
@@ -3220,12 +3230,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
 // 16-deep slabs (37 KB of LDS, 148-164 VGPRs), three waves per SIMD: K >= 128,
 // where the update is MFMA-bound in FP64.  Against the 32-deep form, 9% faster
 // alone at K = 128 and 8% at K = 256, and 4% off the n = 16384 step.
-template <int TAG>
+// FLUSH: updates whose sums may not be as deep as K.  C's elements are in
+// registers already, so it costs one subtraction per element and flush (n = 4096,
+// K = 128 with a flush at 64, against nnq_kernel without: the step takes 13.0 ms
+// instead of 12.7, with panels updated one by one 13.3).
+template <int TAG, bool FLUSH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void nnw16_kernel(NnArgs a) {
   if (a.prio) __builtin_amdgcn_s_setprio(2);
   __shared__ double sA[2][64 * (16 + 2)];
   __shared__ double sB[2][64 * (16 + 2)];
-  nnw_body<TAG, 16>(a, sA, sB);
+  nnw_body<TAG, 16, FLUSH>(a, sA, sB);
 }
 
 // 128 x 128 output tile per workgroup (512 threads, 2 x 4 waves, each wave
@@ -3379,9 +3393,20 @@ static bool nnq_ok(const NnArgs& a) {
   return nnw_ok(a) && a.K >= 2 * NK && a.M >= 256 && a.N >= kQuadMinN;
 }
 
+// Only the kernels on nnw_body hold C beside the sums (nnq_kernel has no
+// registers for it), and their slabs come in pairs of 16 k-values.
+bool nn_flush(NnArgs& a, int depth) {
+  if (!nnw_ok(a) || depth % KC) return false;
+  a.flush = depth;
+  a.nsplit = 1;
+  return true;
+}
+
 template <int TAG>
 static void nn_launch_tag(const NnArgs& a, hipStream_t st) {
-  if (a.small)
+  if (a.flush)
+    hipLaunchKernelGGL((nnw16_kernel<TAG, true>), dim3(a.ntiles), dim3(256), 0, st, a);
+  else if (a.small)
     hipLaunchKernelGGL((nns_kernel<TAG>), dim3(nns_grid(a)), dim3(64 * kSmallNnWaves), 0, st, a);
   else if (a.K <= NK && !nnw_ok(a))
     hipLaunchKernelGGL((nn1_kernel<TAG>), dim3(a.ntiles), dim3(256), 0, st, a);

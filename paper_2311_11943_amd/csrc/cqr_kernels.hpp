@@ -93,7 +93,8 @@ struct Scratch {
 // per-kernel profiles map onto the steps of the factorization.
 enum : int { TAG_TRAIL = 0, TAG_REPROJ = 1, TAG_PANEL = 2, TAG_ADJ = 3 };
 
-// C (M x N) [= or +=] A^T B, A: K x M (lda), B: K x N (ldb), split over K.
+// C (M x N) = A^T B, A: K x M (lda), B: K x N (ldb), split over K; C2's first M2
+// rows += A^T B.  Either of C and C2 may be nullptr.
 struct TnArgs {
   const double* A; int64_t lda;
   const double* B; int64_t ldb;
@@ -157,6 +158,7 @@ struct NnArgs {
   double* part;
   int prio;           // raise the waves' issue priority (panel-chain products)
   int small;          // 16 x 16 elements of C per workgroup (nns_kernel)
+  int flush;          // > 0: subtract from C's elements after every `flush` k-values (nn_flush)
   // launch_nn_adj only: C = Cin - sign A B (Cin == nullptr: zero), tri: TRI_* flags
   const double* Cin; int64_t ldcin;
   double sign;
@@ -171,6 +173,9 @@ NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const doub
                 int N, int K, const Scratch& s);
 // Turn a into an update by nns_kernel, unsplit, if it is small enough.
 bool nn_small(NnArgs& a);
+// Have a subtract from C after every `depth` k-values, unsplit; false, changing
+// nothing, where its operands take a kernel that sums all of K first.
+bool nn_flush(NnArgs& a, int depth);
 void launch_nn_product(const NnArgs& a, int tag, hipStream_t st);
 void launch_nn_reduce(const NnArgs& a, hipStream_t st);   // nsplit > 1 only
 bool launch_nn_adj(const NnArgs& a, hipStream_t st);
