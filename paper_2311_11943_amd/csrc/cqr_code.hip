@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 namespace cqr {
 
@@ -133,46 +134,42 @@ void launch_encode_rows(const EncodeArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(encode_rows_kernel, dim3(grid_for(a.bs * a.n)), dim3(kThreads), 0, st, a);
 }
 
-// Shape of a workgroup over one block of rows x cols elements: 2^lg threads
-// along the rows (V rows each), the other threads along the columns, so that
-// short blocks fill a workgroup too.
-struct BlockGrid {
-  int lg, nrow, ncol;       // log2 threads along rows; workgroups along rows and columns
-  unsigned count() const { return (unsigned)nrow * (unsigned)ncol; }
-};
-
-static BlockGrid block_grid(int rows, int cols, int V) {
-  BlockGrid g;
-  g.lg = 4;
-  while (g.lg < 8 && ((int64_t)V << g.lg) < rows) ++g.lg;
-  const int per = V << g.lg, cpw = kThreads >> g.lg;
-  g.nrow = (rows + per - 1) / per;
-  g.ncol = (cols + cpw - 1) / cpw;
-  return g;
+// A block of rows x cols elements, V consecutive rows a thread: consecutive
+// threads go down a column and on into the next, so that every thread of every
+// workgroup but the last has rows, whatever the block's height (runs of 512 rows
+// left a third of the threads without any at 672 rows).
+static unsigned block_grid(int rows, int cols, int V) {
+  return (unsigned)(((int64_t)rows / V * cols + kThreads - 1) / kThreads);
 }
 
 // first row and column of this thread in workgroup b
-__device__ __forceinline__ void block_pos(int lg, int nrow, int b, int V, int& r, int& c) {
-  r = ((b % nrow << lg) + (threadIdx.x & ((1 << lg) - 1))) * V;
-  c = (b / nrow << (8 - lg)) + (threadIdx.x >> lg);
+__device__ __forceinline__ void block_pos(int rows, unsigned b, int V, int& r, int& c) {
+  const unsigned per = (unsigned)rows / V;
+  const uint64_t e = (uint64_t)b * kThreads;
+  const unsigned c0 = (unsigned)(e >> 32 ? e / per : (unsigned)e / per);     // (uniform)
+  const unsigned t = (unsigned)(e - (uint64_t)c0 * per) + threadIdx.x, q = t / per;
+  r = (int)((t - q * per) * V);
+  c = (int)(c0 + q);
 }
 
 // --------------------------------------------------------------------------
 // Code lines: every output block of a line is a fixed linear combination of
 // the line's surviving blocks (coefficients solved on the host).  Several lines
 // share a launch (grid y).  Bound by HBM; a thread takes V consecutive rows of
-// all blocks of its line and requests eight sources before it uses the first
-// (one launch per line with one load in flight per thread: 58 MB in 18 us;
-// the n = 8192 storm, 16 x 16 grid, 40 lines: erasure and recovery 866 us, now
-// 500, 4.6 TB/s).
+// all blocks of its line and requests eight sources (four for a remainder of up
+// to four) before it uses the first (one launch per line with one load in flight
+// per thread: 58 MB in 18 us; the n = 8192 storm, 16 x 16 grid, 40 lines: erasure
+// and recovery 866 us, now 500, 4.6 TB/s; one lost node, n = 8190 on 7 x 5: 53
+// us, now 45).
 // --------------------------------------------------------------------------
-template <int V>
-__global__ __launch_bounds__(kThreads) void lines_kernel(LinesArgs a, int lg, int nrow) {
+template <int V, class Args>
+__global__ __launch_bounds__(kThreads) void lines_kernel(Args a) {
   typedef double vec __attribute__((ext_vector_type(V)));
-  const LineSpec& L = a.line[blockIdx.y];
+  constexpr bool kOne = sizeof(a.line) == sizeof(LineSpec);       // (its line read without an index)
+  const LineSpec& L = a.line[kOne ? 0 : blockIdx.y];
   int r, c;
-  block_pos(lg, nrow, blockIdx.x, V, r, c);
-  if (r >= a.rows || c >= a.cols) return;
+  block_pos(a.rows, blockIdx.x, V, r, c);
+  if (c >= a.cols) return;
   double* base = a.base + L.off + r + (int64_t)c * a.ld;
   const double* coef = a.coef + L.coef;
   const int ns = L.nsrc;
@@ -181,8 +178,8 @@ __global__ __launch_bounds__(kThreads) void lines_kernel(LinesArgs a, int lg, in
   for (int o = 0; o < kMaxOut; ++o)
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[o][e] = 0.0;
-  constexpr int kBatch = 8;
-  for (int s0 = 0; s0 < ns; s0 += kBatch) {
+  auto batch = [&](auto n, int s0) {
+    constexpr int kBatch = decltype(n)::value;
     vec v[kBatch];
 #pragma unroll
     for (int k = 0; k < kBatch; ++k)      // (past the last source: its block again, not used)
@@ -201,7 +198,10 @@ __global__ __launch_bounds__(kThreads) void lines_kernel(LinesArgs a, int lg, in
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-  }
+  };
+  int s0 = 0;
+  for (; ns - s0 > 4; s0 += 8) batch(std::integral_constant<int, 8>{}, s0);
+  if (s0 < ns) batch(std::integral_constant<int, 4>{}, s0);
 #pragma unroll
   for (int o = 0; o < kMaxOut; ++o)
     if (o < L.nout) {
@@ -218,36 +218,84 @@ static bool even_blocks(const double* base, int64_t ld, int rows, int64_t slot, 
   return reinterpret_cast<uintptr_t>(base) % 16 == 0 && ld % 2 == 0 && rows % 2 == 0 && slot % 2 == 0 && off % 2 == 0;
 }
 
+template <class Args>
+static void launch_lines_as(const Args& a, bool two, hipStream_t st) {
+  const unsigned grid = block_grid(a.rows, a.cols, two ? 2 : 1);
+  if (two)
+    hipLaunchKernelGGL((lines_kernel<2, Args>), dim3(grid, a.nlines), dim3(kThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((lines_kernel<1, Args>), dim3(grid, a.nlines), dim3(kThreads), 0, st, a);
+}
+
+// a's lines and coefficients in arguments with less room
+template <class Args>
+static Args lines_in(const LinesArgs& a, int used) {
+  Args s;
+  s.base = a.base; s.ld = a.ld; s.slot = a.slot;
+  s.rows = a.rows; s.cols = a.cols; s.nlines = a.nlines;
+  std::copy(a.line, a.line + a.nlines, s.line);
+  std::copy(a.coef, a.coef + used, s.coef);
+  return s;
+}
+
+// A small event (one lost node: a line of a few blocks per matrix) is bound by
+// its launches, and those by what the host writes for them, so the arguments
+// have the room that the lines need, not the 6 KB of sixteen (n = 256 to 4096,
+// one node erased and recovered: 30.2 us with 6 KB, 28.4 so).
+static_assert(sizeof(LinesArgsOf<1, 32>) <= 384 && sizeof(LinesArgsOf<4, 256>) <= 2400 && sizeof(EraseArgsOf<16>) <= 160,
+              "small arguments");
 void launch_lines(const LinesArgs& a, hipStream_t st) {
   if (a.nlines <= 0) return;
   bool two = true;
   for (int l = 0; l < a.nlines; ++l) two = two && even_blocks(a.base, a.ld, a.rows, a.slot, a.line[l].off);
-  const BlockGrid g = block_grid(a.rows, a.cols, two ? 2 : 1);
-  if (two)
-    hipLaunchKernelGGL(lines_kernel<2>, dim3(g.count(), a.nlines), dim3(kThreads), 0, st, a, g.lg, g.nrow);
+  const LineSpec& last = a.line[a.nlines - 1];
+  const int used = last.coef + last.nsrc * last.nout;
+  if (a.nlines == 1 && used <= 32)
+    launch_lines_as(lines_in<LinesArgsOf<1, 32>>(a, used), two, st);
+  else if (a.nlines <= 4 && used <= 256)
+    launch_lines_as(lines_in<LinesArgsOf<4, 256>>(a, used), two, st);
   else
-    hipLaunchKernelGGL(lines_kernel<1>, dim3(g.count(), a.nlines), dim3(kThreads), 0, st, a, g.lg, g.nrow);
+    launch_lines_as(a, two, st);
 }
 
 // Blocks set to NaN (grid y: the block); bound by its stores.
-template <int V>
-__global__ __launch_bounds__(kThreads) void erase_kernel(EraseArgs a, int lg, int nrow) {
+template <int V, class Args>
+__global__ __launch_bounds__(kThreads) void erase_kernel(Args a) {
   typedef double vec __attribute__((ext_vector_type(V)));
   int r, c;
-  block_pos(lg, nrow, blockIdx.x, V, r, c);
-  if (r >= a.rows || c >= a.cols) return;
+  block_pos(a.rows, blockIdx.x, V, r, c);
+  if (c >= a.cols) return;
   *reinterpret_cast<vec*>(a.base + a.off[blockIdx.y] + r + (int64_t)c * a.ld) = __builtin_nan("");
 }
 
-void launch_erase(const EraseArgs& a, hipStream_t st) {
-  if (a.nblk <= 0) return;
+template <class Args>
+static void launch_erase_as(const Args& a, hipStream_t st) {
   bool two = true;
   for (int k = 0; k < a.nblk; ++k) two = two && even_blocks(a.base, a.ld, a.rows, 0, a.off[k]);
-  const BlockGrid g = block_grid(a.rows, a.cols, two ? 2 : 1);
+  const unsigned grid = block_grid(a.rows, a.cols, two ? 2 : 1);
   if (two)
-    hipLaunchKernelGGL(erase_kernel<2>, dim3(g.count(), a.nblk), dim3(kThreads), 0, st, a, g.lg, g.nrow);
+    hipLaunchKernelGGL((erase_kernel<2, Args>), dim3(grid, a.nblk), dim3(kThreads), 0, st, a);
   else
-    hipLaunchKernelGGL(erase_kernel<1>, dim3(g.count(), a.nblk), dim3(kThreads), 0, st, a, g.lg, g.nrow);
+    hipLaunchKernelGGL((erase_kernel<1, Args>), dim3(grid, a.nblk), dim3(kThreads), 0, st, a);
+}
+
+template <int BLOCKS>
+static void launch_erase_in(const EraseArgs& a, hipStream_t st) {
+  EraseArgsOf<BLOCKS> s;
+  s.base = a.base; s.ld = a.ld; s.rows = a.rows; s.cols = a.cols; s.nblk = a.nblk;
+  std::copy(a.off, a.off + a.nblk, s.off);
+  launch_erase_as(s, st);
+}
+
+// (arguments with the room that the blocks need, as launch_lines)
+void launch_erase(const EraseArgs& a, hipStream_t st) {
+  if (a.nblk <= 0) return;
+  if (a.nblk <= 16)
+    launch_erase_in<16>(a, st);
+  else if (a.nblk <= 64)
+    launch_erase_in<64>(a, st);
+  else
+    launch_erase_as(a, st);
 }
 
 // --------------------------------------------------------------------------

@@ -15,7 +15,7 @@ constexpr int kTile = 64;        // output tile of the split-K product kernel
 // Code lines decoded by one launch.  Line l's blocks lie `slot` elements apart
 // from base + off; out_o = sum_s coef[o * nsrc + s] src_s.
 constexpr int kLinesMax = 16;    // lines a launch
-constexpr int kLinesCoef = 640;  // coefficients a launch (5 KB of kernel arguments); one line has at most 256
+constexpr int kLinesCoef = 640;  // coefficients a launch; one line has at most 256
 struct LineSpec {
   int64_t off;
   int coef;                      // first coefficient
@@ -23,23 +23,29 @@ struct LineSpec {
   uint8_t src[kMaxLine];
   uint8_t dst[kMaxOut];
 };
-struct LinesArgs {
+// LINES and COEF: the room for lines and coefficients (launch_lines picks what
+// the kernel is given)
+template <int LINES, int COEF>
+struct LinesArgsOf {
   double* base;
   int64_t ld, slot;
   int rows, cols, nlines;
-  LineSpec line[kLinesMax];
-  double coef[kLinesCoef];
+  LineSpec line[LINES];
+  double coef[COEF];
 };
+typedef LinesArgsOf<kLinesMax, kLinesCoef> LinesArgs;
 static_assert(kMaxOut * kMaxLine <= kLinesCoef, "a line's coefficients fit one launch");
 
 constexpr int kEraseMax = 256;   // blocks an erasure launch
-struct EraseArgs {
+template <int BLOCKS>
+struct EraseArgsOf {
   double* base;
   int64_t ld;
   int rows, cols;
   int nblk;
-  int64_t off[kEraseMax];
+  int64_t off[BLOCKS];
 };
+typedef EraseArgsOf<kEraseMax> EraseArgs;
 
 struct EncodeArgs {
   double* At;
