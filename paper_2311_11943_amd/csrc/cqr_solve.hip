@@ -22,7 +22,9 @@ constexpr long long kUnset = -1;     // bit pattern of an entry of X not yet sol
 // wave takes every WPC-th run of 64 rows; their sums are added in order.  Bound
 // by reading Q: one wave per column leaves a tall matrix with few columns too
 // little in flight (65536 x 512, one right-hand side: 140 us with one wave per
-// column, 68 with four).
+// column, 68 with four).  The rows after the last whole batch are a batch too,
+// its loads masked: one after the other they took 1350 us of 1024 rows, 64 columns
+// and 1024 right-hand sides, and 530 so (4096 rows, whole batches: 1000).
 template <int WPC>
 __global__ __launch_bounds__(kSolveThreads) void gemv_t_kernel(const double* Q, int64_t ldq, int64_t m, int n,
                                                                const double* B, int64_t ldb, int nrhs, double* Y,
@@ -51,11 +53,25 @@ __global__ __launch_bounds__(kSolveThreads) void gemv_t_kernel(const double* Q, 
 #pragma unroll
         for (int t = 0; t < kRhsChunk; ++t) acc[t] += qv[j] * bv[j][t];
     }
-    for (; i < m; i += 64 * WPC) {
-      const double v = q[i];
+    if (i - lane < m) {             // the last rows, as one batch
+      double qv[kBatch], bv[kBatch][kRhsChunk];
 #pragma unroll
-      for (int t = 0; t < kRhsChunk; ++t)
-        if (t < nr) acc[t] += v * B[i + (int64_t)(r0 + t) * ldb];
+      for (int j = 0; j < kBatch; ++j) {
+        const int64_t r = i + j * 64 * WPC;
+        qv[j] = 0.0;
+#pragma unroll
+        for (int t = 0; t < kRhsChunk; ++t) bv[j][t] = 0.0;
+        if (r >= m) continue;
+        qv[j] = q[r];
+#pragma unroll
+        for (int t = 0; t < kRhsChunk; ++t)
+          if (t < nr) bv[j][t] = B[r + (int64_t)(r0 + t) * ldb];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+        for (int t = 0; t < kRhsChunk; ++t) acc[t] += qv[j] * bv[j][t];
     }
 #pragma unroll
     for (int t = 0; t < kRhsChunk; ++t) {
