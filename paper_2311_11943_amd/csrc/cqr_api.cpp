@@ -368,8 +368,12 @@ int chain_phase(int phase) { return phase != PH_TRAIL_TN && phase != PH_TRAIL_NN
 // Smallest encoded matrix whose panels are updated in pairs: smaller ones stay
 // in the 256 MB cache before HBM, and the pairs' extra launches cost more than
 // the bytes they save (5120 x 2560: 7.06 ms in pairs, 6.65 without; 5120 x 5120:
-// 12.9 against 13.3).
-constexpr int64_t kPairBytes = (int64_t)160 << 20;
+// 12.9 against 13.3).  Where the pair's update is deeper than a slab of the
+// kernels for odd leading dimensions, which read it element by element, the line
+// lies higher (5151 x 5151, b = 51: 39.9 ms in pairs, 38.6 without; 5121 x 5120,
+// b = 40: 44.3, 44.1; 10005 x 3200, b = 64: 23.8, 24.9; 5742 x 5742, b = 55:
+// 28.3, 30.2).
+constexpr int64_t kPairBytes = (int64_t)160 << 20, kPairBytesOdd = (int64_t)240 << 20;
 // Panels after a pair that take each of its panels' updates by itself.
 constexpr int kPairNear = 4;
 // Up to this many panels in all (a tall matrix then, by kPairBytes) the chain
@@ -482,11 +486,12 @@ void nn(cqr_plan_s& p, int phase, double* C, int64_t ldc, const double* A, int64
   // (a small update's four waves each sum a quarter of the products)
   if (depth > 0 && K > (a.small ? 4 : 1) * depth) {
     a.small = 0;
-    if (depth >= kFlushDepth || !cqr::nn_flush(a, depth)) {
+    if (depth >= kFlushDepth) {
       for (int k = 0; k < K; k += depth)
         nn(p, phase, C, ldc, A + k * lda, lda, B + k, ldb, M, N, std::min(depth, K - k), s, st);
       return;
     }
+    cqr::nn_flush(a, depth);
   }
   a.prio = chain_phase(phase);
   const double fl = 2.0 * M * N * (double)K, by = 8.0 * ((double)M * K + (double)K * N);
@@ -914,8 +919,13 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
   // product is queued behind the next panel's re-projection and its update
   // behind the one after, so that they run beside the passes (n = 4096: 13.4 ms
   // queued at once, 12.8 so).
-  const bool pairs = la && p->cfg.reproject && lowp == 0 && mp * N * 8 > kPairBytes &&
-                     p->cfg.panel == CQR_PANEL_CHOLQR2;
+  const bool even = reinterpret_cast<uintptr_t>(Q) % 16 == 0 && ldq % 2 == 0;
+  const bool pairs = la && p->cfg.reproject && lowp == 0 && p->cfg.panel == CQR_PANEL_CHOLQR2 &&
+                     mp * N * 8 > (even || 2 * w <= kLeaf ? kPairBytes : kPairBytesOdd);
+  // products that a pair's update may sum (see update_depth; with odd leading
+  // dimensions and panels of 128 or more, no fewer than those took: 12289 x 6144,
+  // b = 128: 108.6 ms, 110.7 with sums of 64)
+  const int pair_depth = 2 * w > kPairDepth && (even || p->cfg.b < 2 * w) ? kLeaf : 0;
   int64_t far_c0 = -1, far_from = 0;     // the last pair and the columns its update has not been queued for
   bool far_coef = false;                 // their coefficients are queued
   auto pair_product = [&](int64_t c0, int64_t from, const cqr::Scratch& sc, hipStream_t ss) {
@@ -924,7 +934,7 @@ cqr_status coded_qr_factor(cqr_plan p, double* Q, int64_t ldq, double* R, int64_
   };
   auto pair_update = [&](int64_t c0, int64_t from, const cqr::Scratch& sc, hipStream_t ss) {
     nn(*p, PH_TRAIL_NN, Q + from * ldq, ldq, Q + c0 * ldq, ldq, R + c0 + from * ldr, ldr, mp, (int)(N - from),
-       2 * (int)w, sc, ss, 2 * w > kPairDepth ? (int)w : 0);
+       2 * (int)w, sc, ss, pair_depth);
   };
   bool deferred = false;       // a wide panel's update of the columns after the next panel, not yet forked
   int64_t def_c0 = 0, def_b = 0, def_from = 0;

@@ -2812,8 +2812,8 @@ __global__ __launch_bounds__(256) void nn1_kernel(NnArgs a) {
 // current slab is multiplied (A register sets alternate explicitly).  SPLIT:
 // the block's K range is one split and its partial tile is stored for
 // nn_reduce_kernel; otherwise C is updated in place (the path for operands
-// nnw_kernel does not take).
-template <bool SPLIT, int TAG>
+// nnw_kernel does not take), FLUSH: after every slab.
+template <bool SPLIT, int TAG, bool FLUSH = false>
 __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1], int bx, int split) {
   typedef v4d Acc;
   int tm = bx / a.tilesN, tn = bx % a.tilesN;
@@ -2835,6 +2835,14 @@ __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1
   Acc acc[4];
 #pragma unroll
   for (int y = 0; y < 4; ++y) acc[y] = Acc{0, 0, 0, 0};
+  auto flush = [&]() {
+    if constexpr (!FLUSH) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      cval[e] -= acc[e >> 2][e & 3];
+      acc[e >> 2][e & 3] = 0.0;
+    }
+  };
   auto koff = [&](int sl) { return kb + std::min(sl, nfull - 1) * NK; };
   if (nfull > 0) {
     double xa0[16], xa1[16];
@@ -2850,6 +2858,7 @@ __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1
       nn_load_b(t, koff(sl + 1), rb);
       __builtin_amdgcn_sched_barrier(0);
       nn_mma(acc, sB[0], t, xa0);
+      flush();
       __builtin_amdgcn_sched_barrier(0);
       nn_put_b(sB[1], t, rb);
       __syncthreads();
@@ -2857,11 +2866,15 @@ __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1
       nn_load_b(t, koff(sl + 2), rb);
       __builtin_amdgcn_sched_barrier(0);
       nn_mma(acc, sB[1], t, xa1);
+      flush();
       __builtin_amdgcn_sched_barrier(0);
       nn_put_b(sB[0], t, rb);
       __syncthreads();
     }
-    if (sl < nfull) nn_mma(acc, sB[0], t, xa0);
+    if (sl < nfull) {
+      nn_mma(acc, sB[0], t, xa0);
+      flush();
+    }
   }
   const int kt = kb + nfull * NK;
   for (int k0 = kt; k0 < ke; k0 += NK) {
@@ -2871,6 +2884,7 @@ __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1
     nn_load_tail(a, t, k0, ke, xa, sB[buf]);
     __syncthreads();
     nn_mma(acc, sB[buf], t, xa);
+    flush();
     __syncthreads();
   }
   if (SPLIT) {
@@ -2891,11 +2905,11 @@ __device__ __forceinline__ void nn_body(const NnArgs& a, double (*sB)[NK][64 + 1
     }
 }
 
-template <bool SPLIT, int TAG>
+template <bool SPLIT, int TAG, bool FLUSH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void nn_kernel(NnArgs a) {
   if (a.prio) __builtin_amdgcn_s_setprio(2);
   __shared__ double sB[2][NK][64 + 1];
-  nn_body<SPLIT, TAG>(a, sB, blockIdx.x, blockIdx.y);
+  nn_body<SPLIT, TAG, FLUSH>(a, sB, blockIdx.x, blockIdx.y);
 }
 
 // The same update where 64 x 64 tiles would leave the chip idle, as tns_kernel
@@ -3393,19 +3407,20 @@ static bool nnq_ok(const NnArgs& a) {
   return nnw_ok(a) && a.K >= 2 * NK && a.M >= 256 && a.N >= kQuadMinN;
 }
 
-// Only the kernels on nnw_body hold C beside the sums (nnq_kernel has no
-// registers for it), and their slabs come in pairs of 16 k-values.
-bool nn_flush(NnArgs& a, int depth) {
-  if (!nnw_ok(a) || depth % KC) return false;
-  a.flush = depth;
+// nnw16_kernel's slabs come in pairs of 16 k-values, nn_kernel's are of 64 (it
+// subtracts after each); both hold C beside the sums, for which nnq_kernel has no
+// registers.
+void nn_flush(NnArgs& a, int depth) {
+  a.flush = nnw_ok(a) && depth % KC == 0 ? depth : NK;
   a.nsplit = 1;
-  return true;
 }
 
 template <int TAG>
 static void nn_launch_tag(const NnArgs& a, hipStream_t st) {
-  if (a.flush)
+  if (a.flush && nnw_ok(a))
     hipLaunchKernelGGL((nnw16_kernel<TAG, true>), dim3(a.ntiles), dim3(256), 0, st, a);
+  else if (a.flush)
+    hipLaunchKernelGGL((nn_kernel<false, TAG, true>), dim3(a.ntiles), dim3(256), 0, st, a);
   else if (a.small)
     hipLaunchKernelGGL((nns_kernel<TAG>), dim3(nns_grid(a)), dim3(64 * kSmallNnWaves), 0, st, a);
   else if (a.K <= NK && !nnw_ok(a))

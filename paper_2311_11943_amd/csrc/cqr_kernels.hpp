@@ -179,9 +179,8 @@ NnArgs nn_setup(double* C, int64_t ldc, const double* A, int64_t lda, const doub
                 int N, int K, const Scratch& s);
 // Turn a into an update by nns_kernel, unsplit, if it is small enough.
 bool nn_small(NnArgs& a);
-// Have a subtract from C after every `depth` k-values, unsplit; false, changing
-// nothing, where its operands take a kernel that sums all of K first.
-bool nn_flush(NnArgs& a, int depth);
+// Have a subtract from C after every `depth` k-values (at least 64), unsplit.
+void nn_flush(NnArgs& a, int depth);
 void launch_nn_product(const NnArgs& a, int tag, hipStream_t st);
 void launch_nn_reduce(const NnArgs& a, hipStream_t st);   // nsplit > 1 only
 bool launch_nn_adj(const NnArgs& a, hipStream_t st);
