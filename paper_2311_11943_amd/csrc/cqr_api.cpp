@@ -652,7 +652,10 @@ void factor_panel(cqr_plan_s& p, double* Q, int64_t ldq, double* R, int64_t ldr,
     panel_second(p, a, st);
     return;
   }
-  int h = (w / 2 + 15) / 16 * 16;
+  // the left part: half, in whole leaves where the panel is a row of them and
+  // the order of sums is free
+  const bool leaves = w % kLeaf == 0 && p.cfg.precision == CQR_FP64 && p.cfg.panel == CQR_PANEL_CHOLQR2;
+  int h = leaves ? (w / 2 + kLeaf - 1) / kLeaf * kLeaf : (w / 2 + 15) / 16 * 16;
   if (h >= w) h = w / 2;
   factor_panel(p, Q, ldq, R, ldr, c, h, s, st);
   for (int pass = 0; pass < 2; ++pass) {
