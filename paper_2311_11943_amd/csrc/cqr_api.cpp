@@ -117,19 +117,21 @@ bool invert(std::vector<double> a, int n, std::vector<double>& inv) {
 // rounding, so the width follows what runs fastest, for b a multiple of 64:
 // single leaves (64) while the encoded matrix is at most 1 GiB, where their short
 // chain beats the wide panels' better products (n = 8192: 78 ms against 93 with
-// 128 columns and 82 with 256; n = 4096: 13.1 against 14.5 and 15.4); about 512
-// columns beyond (b = 64, n = 12288: 231 ms, 257 with leaves; b = 128, n = 16384:
+// 128 columns and 82 with 256; n = 4096: 13.1 against 14.5 and 15.4) or has fewer
+// than 512 columns (524288 x 384: 10.6 ms, 11.6 in one panel); about 512 columns
+// beyond (b = 64, n = 12288: 231 ms, 257 with leaves; b = 128, n = 16384:
 // 710 ms, 799 with 128; b = 256, n = 32768: 5.22 s, 5.40 with 256).  Without
 // re-projection, in the column-wise modes and in reduced precision (whose
 // coefficients depend on the division) it is b.  This is the largest width of
 // the factorization; panel_width() narrows it towards the last columns.
+constexpr int64_t kWide = 512;
 int64_t inner_width(const cqr_plan_s& p) {
   const cqr_config& c = p.cfg;
   if (c.panel != CQR_PANEL_CHOLQR2 || c.precision != CQR_FP64 || !c.reproject || !c.lookahead || c.b % kLeaf)
     return c.b;
   const int64_t bytes = 8 * p.mp * p.N;
-  if (bytes <= (int64_t)1 << 30) return kLeaf;
-  return std::max<int64_t>(c.b, 512 / c.b * c.b);
+  if (bytes <= (int64_t)1 << 30 || c.n < kWide) return kLeaf;
+  return std::max<int64_t>(c.b, kWide / c.b * c.b);
 }
 
 // Width of the panel that starts at column c.  What a re-projection leaves of a
@@ -386,15 +388,18 @@ constexpr int kNearPanels = 12;
 // streams' events and extra launches cost (us, with and without: 256 x 256, b =
 // 16: 1173, 739; 1024 x 1024, b = 32: 2429, 2135, b = 64: 1249, 1306; 1211 x
 // 1155, b = 35: 2526, 2439; 1536 x 1536, b = 32: 3737, 3948), and where few
-// panels follow there is little to run beside (16384 x 256, b = 64: 617, 585;
-// 65536 x 512, b = 64: 3393, 3482).  The reduced precisions keep the order that
-// their coefficients are rounded in.
+// panels follow there is little to run beside, up to heights at which the
+// second pass's update of the next panel saves reading it again (us, with and
+// without, b = 64: 16384 x 256: 499, 456; 65536 x 512: 2464, 2591; 262144 x 192:
+// 1836, 1808; 524288 x 192: 3547, 3722; 1048576 x 128: 3770, 4046).  The reduced
+// precisions keep the order that their coefficients are rounded in.
 constexpr int64_t kAheadWork = 80 << 20;      // encoded elements x panel width
 constexpr int kAheadPanels = 6;
+constexpr int64_t kAheadTall = 64 << 20;      // encoded elements
 bool looks_ahead(const cqr_plan_s& p) {
   if (!p.cfg.lookahead) return false;
   if (p.cfg.precision != CQR_FP64 || p.cfg.panel != CQR_PANEL_CHOLQR2) return true;
-  return p.mp * p.N * p.pw >= kAheadWork && p.N > kAheadPanels * (int64_t)p.pw;
+  return p.mp * p.N * p.pw >= kAheadWork && (p.N > kAheadPanels * (int64_t)p.pw || p.mp * p.N >= kAheadTall);
 }
 
 // First tile of the Gram partials in the split-partial area: the split
