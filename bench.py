@@ -59,18 +59,6 @@ WORKLOADS = {
 # 64-wide dimension and a long reduction: 16 flop per byte, above the
 # 78.6 TFLOP/s / 8 TB/s ridge); the rest are bound by HBM bytes.
 MFMA_PHASES = {"reproj_product", "reproj_update", "panel_gram", "inpanel_projection", "trailing_product"}
-SINGLE_KERNEL_PHASES = ("trailing_product", "trailing_update", "reproj_product", "panel_gram", "recover",
-                        "postorth")
-KERNEL_OF = {
-    "encode": "encode_fused_kernel / encode_rows_kernel",
-    "reproj_product": "tn_lds_kernel<1, false>", "reproj_update": "nn_kernel<*, 1>",
-    "panel_gram": "tn_lds_kernel<2, false>", "panel_chol": "panel_second_kernel", "panel_transform": "panel_first_kernel",
-    "inpanel_projection": "tn/nn <2, false>",
-    "trailing_product": "tn_lds_kernel<0, false>", "trailing_update": "nnw_kernel<0>",
-    "split_reduce": "tn_reduce_kernel / nn_reduce_kernel", "recover": "lines_kernel",
-    "postorth": "postorth_kernel", "erase": "erase_kernel", "other": "zero_ints_kernel / fill_zero_kernel",
-    "solve": "gemv_t_kernel / trinv_kernel / trsv_flow_kernel",
-}
 
 
 def model_flops(mp, n, d, b, reproject=True):
@@ -712,7 +700,7 @@ def main():
             L["phases"] = phases
             L["overhead"]["T_recov_ms_per_event"] = round(rep["recover"]["ms"] / max(len(sched), 1), 4)
             if li == 0:
-                out["roofline"] = roofline_of(rep, b, leg, args.workload)
+                out["roofline"] = roofline_of(rep, cfg, leg, args.workload)
         q.close()
 
         if not args.no_extras and not args.skip_uncoded:
@@ -785,43 +773,58 @@ PRECISIONS = {
 }
 
 
-def kernel_of(phase: str, b: int, leg: str) -> str:
-    """Kernel symbol behind a single-kernel phase (kernels are template-tagged per use)."""
-    k = KERNEL_OF[phase]
-    if phase == "trailing_update" and b >= 128:
-        # K = b >= 128 and every trailing update spans the checksum columns
-        # (>= 256 of them): the 128 x 128-tile form
-        k = "nnq_kernel<0>"
-    if phase == "trailing_product" and b > 64:
-        # panels of several tile rows: 128 x 128 per workgroup, in FP64, in
-        # FP32 (FP32 slabs in LDS) or as split-BF16 products
-        k = {"fp64": "tnq_kernel<0>", "fp32": "tnf_kernel", "bf16x3": "tnb_kernel<0>"}[leg]
-    elif phase == "trailing_product" and leg in ("fp32", "bf16x3"):
-        # one tile row: the FP32 form of the LDS-staged product (the split-BF16
-        # mode takes it too for such products)
-        k = k.replace("<0, false>", "<0, true>")
-    return k
+def own_width(cfg) -> int:
+    """Columns that a plan factors at once (the library's rule): b, except in FP64
+    with re-projection, lookahead, Cholesky-QR panels and 64 | b."""
+    if cfg.panel or cfg.precision or not cfg.reproject or not cfg.lookahead or cfg.b % 64:
+        return cfg.b
+    if 8 * cfg.mp * cfg.N <= 1 << 30 or cfg.n < 512:
+        return 64
+    return max(cfg.b, 512 // cfg.b * cfg.b)
 
 
-def roofline_of(rep: dict, b: int, leg: str, workload: str) -> dict:
+def kernel_of(phase: str, cfg):
+    """The kernel symbol behind every launch of a phase (kernels are
+    template-tagged per use), or None where several share it."""
+    w, fp64 = own_width(cfg), cfg.precision == 0
+    if phase == "trailing_product":
+        if w > 64:      # 128 x 128 outputs per workgroup: FP64, FP32 (FP32 slabs in LDS) or split BF16
+            return ("tnq_kernel<0>", "tnf_kernel", "tnb_kernel<0>")[cfg.precision]
+        # one tile row: in FP64 shared with pairs of panels and with small products
+        return None if fp64 else "tn_lds_kernel<0, true>"
+    if phase == "trailing_update":
+        if w > cfg.b and cfg.b < 256:       # wide panels' subtract every b products, the last ones' are b deep
+            return None
+        if min(w, cfg.b) >= 128:
+            return "nnq_kernel<0>"
+        return None if fp64 else "nnw_kernel<0>"
+    if phase in ("reproj_product", "panel_gram"):
+        tag = 1 if phase == "reproj_product" else 2
+        if w > 64 and phase == "reproj_product":
+            return f"tnq_kernel<{tag}>"
+        return f"tn_lds_kernel<{tag}, false>" if cfg.mp > 2048 else None    # (shorter ones may be small products)
+    return {"recover": "lines_kernel", "postorth": "postorth_kernel"}.get(phase)
+
+
+def roofline_of(rep: dict, cfg, leg: str, workload: str) -> dict:
     """Roofline of the kernel holding the most time among phases that are exactly
     one kernel symbol (so rocprofv3's per-kernel average describes the same
     launches): algorithmic flops (or bytes) of its launches / their summed
     HIP-event durations on the stream they ran on."""
-    dom = max((k for k in SINGLE_KERNEL_PHASES if rep[k]["launches"]), key=lambda k: rep[k]["ms"])
+    dom = max((k for k in rep if rep[k]["launches"] and kernel_of(k, cfg)), key=lambda k: rep[k]["ms"])
     r = rep[dom]
     f32_product = leg == "fp32" and dom == "trailing_product"
     mfma_peak = PEAK["fp32_mfma_tflops" if f32_product else "fp64_mfma_tflops"]
-    # the rank-b update moves 16 bytes (read and write of C) per 2b flops:
-    # MFMA-bound when b/8 flop/B exceeds the ridge peak / HBM bandwidth
-    update_mfma = dom == "trailing_update" and b / 8.0 > mfma_peak * 1e3 / PEAK["hbm_gbs"]
+    # an update reads and writes C once per launch: MFMA-bound when its flops per
+    # byte exceed the ridge peak / HBM bandwidth
+    update_mfma = dom == "trailing_update" and r["flops"] > r["bytes"] * mfma_peak * 1e3 / PEAK["hbm_gbs"]
     if dom in MFMA_PHASES or update_mfma:
         ach = r["flops"] / (r["ms"] * 1e-3) / 1e12
-        roof = {"kernel": kernel_of(dom, b, leg), "phase": dom, "bound": "mfma", "achieved": round(ach, 3),
+        roof = {"kernel": kernel_of(dom, cfg), "phase": dom, "bound": "mfma", "achieved": round(ach, 3),
                 "peak": mfma_peak, "unit": "TFLOP/s", "frac": round(ach / mfma_peak, 4)}
     else:
         ach = r["bytes"] / (r["ms"] * 1e-3) / 1e9
-        roof = {"kernel": kernel_of(dom, b, leg), "phase": dom, "bound": "hbm", "achieved": round(ach, 1),
+        roof = {"kernel": kernel_of(dom, cfg), "phase": dom, "bound": "hbm", "achieved": round(ach, 1),
                 "peak": PEAK["hbm_gbs"], "unit": "GB/s", "frac": round(ach / PEAK["hbm_gbs"], 4)}
     roof["avg_launch_us"] = round(1e3 * r["ms"] / r["launches"], 3)
     roof["launches"] = r["launches"]
