@@ -254,7 +254,6 @@ void launch_inv_level(const double* R, int64_t ldr, double* Rinv, double* W, int
 }
 
 // C *= s (rows x cols, ld ldc)
-// C *= s (rows x cols, ld ldc)
 __global__ __launch_bounds__(kAdjThreads) void scale_kernel(double* C, int64_t ldc, int64_t rows, int64_t cols,
                                                             double s) {
   const int64_t e = (int64_t)blockIdx.x * kAdjThreads + threadIdx.x;

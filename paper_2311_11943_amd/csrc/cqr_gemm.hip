@@ -2692,10 +2692,6 @@ __device__ __forceinline__ NnTile nn_tile_at(const NnArgs& a, int tm, int tn) {
   return t;
 }
 
-__device__ __forceinline__ NnTile nn_tile(const NnArgs& a, int tile) {
-  return nn_tile_at(a, tile / a.tilesN, tile % a.tilesN);
-}
-
 // XCD-aware tile order for one-pass updates.  Workgroups are dealt to the
 // eight XCDs round-robin (block b runs on XCD b mod 8), and each XCD has its
 // own L2.  Block b takes position start(x) + b / 8 of an order in which the
