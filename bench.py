@@ -363,7 +363,9 @@ def run_adjoint(args):
     relx = ((x.detach() - xw).abs().max() / xw.abs().max()).item()
     mp = cfg.mp
     f_fl = model_flops(mp, n, cfg.N - n, b) + 2.0 * m * n + n * n
-    b_fl = 6.0 * mp * n * n + 2.0 * n ** 3
+    # what the backward's products carry out: Q~^T dQ~ (lower triangle) m' n^2,
+    # Q~ copyltu(M) 2 m' n^2, D R^-T (triangular) m' n^2, R^-1 and R dR^T n^3 / 3 each
+    b_fl = 4.0 * mp * n * n + 2.0 * n ** 3 / 3
     print(json.dumps({
         "metric": "coded-QR least-squares forward + adjoint time", "value": round(fm + bm, 4), "unit": "ms",
         "higher_is_better": False, "steps": args.steps, "warmup": args.warmup,
