@@ -380,7 +380,8 @@ constexpr int64_t kPairBytes = (int64_t)160 << 20, kPairBytesOdd = (int64_t)240 
 constexpr int kPairNear = 4;
 // Up to this many panels in all (a tall matrix then, by kPairBytes) the chain
 // waits for its next columns of those only, updated by a launch of their own
-// (65536 x 512, b = 64: 2.72 ms, 2.60 so; 65536 x 1024 7.99 and 8.14).
+// (ms, all at once and so, b = 64: 65536 x 512: 2.47, 2.38; x 768: 4.69, 4.54;
+// x 1536: 14.98, 15.24; 16 panels, beyond the line, would gain: x 1024: 7.48, 7.37).
 constexpr int kNearPanels = 12;
 
 // Whether the next panel is factored beside the trailing update.  Where the
